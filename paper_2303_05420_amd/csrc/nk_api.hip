@@ -101,7 +101,6 @@ struct Bump {
 constexpr int kPairTile = 16;           // images per side of a pair-order tile
 constexpr int64_t kDefaultChunk = 16384;  // pairs per stage pass for workspace queries
 constexpr int64_t kDefaultChunk64 = 1024;  // the same for 64x64 inputs (4 MiB of pooled output per pair)
-constexpr int64_t kPrepBlocks = 2048;     // images prepared per launch
 
 constexpr size_t kLdsDynamicMax = 160 * 1024 - 1024;  // dynamic LDS per workgroup
 
@@ -181,7 +180,7 @@ MyrtlePlan plan_myrtle(const NetDesc& net, int64_t n1, int64_t n2, bool sym, int
   const size_t tl = (size_t)nk::table_len(net) * sizeof(float2);
   p.tab1 = b.take(tl * n1);
   p.tab2 = sym ? p.tab1 : b.take(tl * n2);
-  const int64_t pb = std::min<int64_t>(std::max(n1, n2), kPrepBlocks);
+  const int64_t pb = nk::prep_slots(sym ? n1 : n1 + n2);
   p.scratch = b.take((size_t)nk::prep_scratch_doubles(net) * sizeof(double) * pb);
   for (int s = 1; s < net.S; ++s) {
     const size_t n = (size_t)(net.hw >> s);
@@ -206,7 +205,7 @@ BwdPlan plan_bwd(const NetDesc& net, int64_t n1, int64_t n2, bool sym, int64_t c
   const size_t img = (size_t)net.hw * net.hw * net.C;
   p.tab1 = b.take(tl * sizeof(float2) * n1);
   p.tab2 = sym ? p.tab1 : b.take(tl * sizeof(float2) * n2);
-  const int64_t pb = std::min<int64_t>(std::max(n1, n2), kPrepBlocks);
+  const int64_t pb = nk::prep_slots(sym ? n1 : n1 + n2);
   p.scratch = b.take((size_t)nk::prep_scratch_doubles(net) * sizeof(double) * pb);
   p.W1 = b.take(tl * sizeof(double) * n1);
   p.W2 = sym ? p.W1 : b.take(tl * sizeof(double) * n2);
@@ -368,7 +367,7 @@ BatchPlan plan_batched(const NetDesc& net, int64_t rows, int64_t ntiles, int64_t
   Bump b;
   p.desc = b.take(sizeof(nk::TileDesc) * (size_t)std::max<int64_t>(ntiles, 1));
   p.tab = b.take((size_t)nk::table_len(net) * sizeof(float2) * rows);
-  const int64_t pb = std::min<int64_t>(std::max<int64_t>(rows, 1), kPrepBlocks);
+  const int64_t pb = nk::prep_slots(std::max<int64_t>(rows, 1));
   p.scratch = b.take((size_t)nk::prep_scratch_doubles(net) * sizeof(double) * pb);
   for (int s = 1; s < net.S; ++s) {
     const size_t n = (size_t)(net.hw >> s);
@@ -593,7 +592,7 @@ MyrtlePlan plan_ntk(const NetDesc& net, int64_t n1, int64_t n2, bool sym, int64_
   const size_t tl = (size_t)nk::table_len(net) * sizeof(float2);
   p.tab1 = b.take(tl * n1);
   p.tab2 = sym ? p.tab1 : b.take(tl * n2);
-  const int64_t pb = std::min<int64_t>(std::max(n1, n2), kPrepBlocks);
+  const int64_t pb = nk::prep_slots(sym ? n1 : n1 + n2);
   p.scratch = b.take((size_t)nk::prep_scratch_doubles(net) * sizeof(double) * pb);
   for (int s = 1; s < net.S; ++s) {
     const size_t n = (size_t)(net.hw >> s);
@@ -762,7 +761,7 @@ KrrGradPlan plan_krr_grad(const NetDesc& net, int64_t n, int64_t m, int64_t c, i
   p.dts = b.take(sizeof(float) * (size_t)m * n);
   p.tab_s = b.take(tl * sizeof(float2) * n);
   p.tab_t = b.take(tl * sizeof(float2) * m);
-  const int64_t pb = std::min<int64_t>(std::max(n, m), kPrepBlocks);
+  const int64_t pb = nk::prep_slots(n + m);
   p.scratch = b.take((size_t)nk::prep_scratch_doubles(net) * sizeof(double) * pb);
   p.krr_bytes = krr_plan(n, std::max(m, c)).total;
   p.krr = b.take(p.krr_bytes);
@@ -1179,8 +1178,8 @@ int nk_myrtle_nngp(const float* x1, int64_t n1, const float* x2, int64_t n2, con
   double* scratch = at<double>(ws, p.scratch);
   {
     ProfScope ps("myrtle_prepare", s);
-    if (nk::launch_prepare(x1, n1, net, tab1, scratch, kPrepBlocks, s)) return hip_fail("prepare kernel");
-    if (!sym && nk::launch_prepare(x2, n2, net, tab2, scratch, kPrepBlocks, s)) return hip_fail("prepare kernel");
+    if (nk::launch_prepare(x1, n1, tab1, sym ? nullptr : x2, n2, tab2, net, scratch, nk::prep_slots(sym ? n1 : n1 + n2), s))
+      return hip_fail("prepare kernel");
   }
   float* bufs[NK_MAX_STAGES] = {nullptr, nullptr, nullptr, nullptr};
   for (int st = 1; st < net.S; ++st) bufs[st] = at<float>(ws, p.buf[st]);
@@ -1215,8 +1214,8 @@ int nk_myrtle_ntk(const float* x1, int64_t n1, const float* x2, int64_t n2, cons
   double* scratch = at<double>(ws, p.scratch);
   {
     ProfScope ps("myrtle_prepare", s);
-    if (nk::launch_prepare(x1, n1, net, tab1, scratch, kPrepBlocks, s)) return hip_fail("prepare kernel");
-    if (!sym && nk::launch_prepare(x2, n2, net, tab2, scratch, kPrepBlocks, s)) return hip_fail("prepare kernel");
+    if (nk::launch_prepare(x1, n1, tab1, sym ? nullptr : x2, n2, tab2, net, scratch, nk::prep_slots(sym ? n1 : n1 + n2), s))
+      return hip_fail("prepare kernel");
   }
   float* bufA[NK_MAX_STAGES] = {nullptr, nullptr, nullptr, nullptr};
   float* bufC[NK_MAX_STAGES] = {nullptr, nullptr, nullptr, nullptr};
@@ -1285,9 +1284,8 @@ int nk_myrtle_nngp_backward(const float* x1, int64_t n1, const float* x2, int64_
   const int64_t img = (int64_t)net.hw * net.hw * net.C;
   {
     ProfScope ps("myrtle_prepare", s);
-    if (nk::launch_prepare(x1, n1, net, tab1, at<double>(ws, p.scratch), kPrepBlocks, s))
-      return hip_fail("prepare kernel");
-    if (!sym && nk::launch_prepare(x2, n2, net, tab2, at<double>(ws, p.scratch), kPrepBlocks, s))
+    if (nk::launch_prepare(x1, n1, tab1, sym ? nullptr : x2, n2, tab2, net, at<double>(ws, p.scratch),
+                           nk::prep_slots(sym ? n1 : n1 + n2), s))
       return hip_fail("prepare kernel");
   }
   if (nk::launch_zero_f64(W1, n1 * tl, s) || nk::launch_zero_f64(xb1, n1 * img, s) || nk::launch_zero_f64(sums, 4, s))
@@ -1459,8 +1457,7 @@ static int krr_mse_grad_impl(const float* x_s, int64_t n, const float* x_t, int6
   float* keep_st = p.keep ? keep_ss + nk::pair_count(n, n, 1) * stage1_out_floats(net) : nullptr;
   {
     ProfScope ps("myrtle_prepare", s);
-    if (nk::launch_prepare(x_s, n, net, tab_s, at<double>(ws, p.scratch), kPrepBlocks, s) ||
-        nk::launch_prepare(x_t, m, net, tab_t, at<double>(ws, p.scratch), kPrepBlocks, s))
+    if (nk::launch_prepare(x_s, n, tab_s, x_t, m, tab_t, net, at<double>(ws, p.scratch), nk::prep_slots(n + m), s))
       return hip_fail("prepare kernel");
   }
   // forward: K_ss (symmetric) and K_ts
@@ -1891,7 +1888,8 @@ int nk_myrtle_nngp_batched(const nk_tile* tiles, int32_t ntiles, const nk_myrtle
   auto prepare_all = [&]() -> int {
     int64_t row = 0;
     for (auto& im : L.images) {
-      if (nk::launch_prepare(im.first, im.second, net, tab + row * nk::table_len(net), scratch, kPrepBlocks, s))
+      if (nk::launch_prepare(im.first, im.second, tab + row * nk::table_len(net), nullptr, 0, nullptr, net, scratch,
+                             nk::prep_slots(L.rows), s))
         return hip_fail("prepare kernel");
       row += im.second;
     }

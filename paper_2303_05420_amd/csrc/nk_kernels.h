@@ -28,11 +28,15 @@ inline int allow_dyn_lds(const void* fn, size_t lds, std::atomic<size_t>* seen) 
 }
 
 struct PrepArgs {
-  const float* x;     // images NHWC
-  int64_t n;          // images in this launch
+  const float* x1;    // images NHWC; n1 of them, then those of x2
+  const float* x2;
+  int64_t n1;
+  int64_t first;      // first image of this launch (of the two sets taken together)
+  int64_t img_floats;
   NetDesc net;
-  float2* tab;        // n * table_len float2
-  double* scratch;    // n_blocks * scratch_per_img doubles (one region per workgroup)
+  float2* tab1;       // table_len float2 per image
+  float2* tab2;
+  double* scratch;    // scratch_per_img doubles per image of the launch
   int64_t scratch_per_img;
 };
 
@@ -129,9 +133,13 @@ struct FcArgs {
   int sym;  // x1 and x2 are the same images: upper-triangle tiles, mirrored
 };
 
+// Variance tables of both image sets (x2 NULL: one set).  Scratch: slots x
+// prep_scratch_doubles(net) doubles, slots = prep_slots(images) images at a time.
+constexpr int64_t kPrepSlots = 2048;
 int64_t prep_scratch_doubles(const NetDesc& net);
-int launch_prepare(const float* x, int64_t n, const NetDesc& net, float2* tab, double* scratch,
-                   int64_t max_blocks, hipStream_t stream);
+int64_t prep_slots(int64_t n);
+int launch_prepare(const float* x1, int64_t n1, float2* tab1, const float* x2, int64_t n2, float2* tab2,
+                   const NetDesc& net, double* scratch, int64_t slots, hipStream_t stream);
 size_t stage_lds_bytes(int N, int D, bool pool, bool seed);
 // ppm: pairs-per-workgroup multiplier (1 or 2) of the stage kernels of tiles
 // of at most 16 x 16 (a kernel-shape choice of the batched pass; results do

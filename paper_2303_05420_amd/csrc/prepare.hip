@@ -11,42 +11,62 @@
 // delta = 2 Delta + {-1, 0, 1}^2, so the diagonal after a pool needs the
 // previous stage's slices |delta| <= 1, which need the stage before's
 // |delta| <= 3, and so on: stage s of S uses slices |delta| <= 2^(S-1-s) - 1.
-// This kernel runs exactly those slices of the self recursion (a few
-// percent of one pair's work per image) and writes, per stage, layer and
-// pixel,
+// These kernels run those slices of the self recursion (a few percent of one
+// pair's work per image) and write, per stage, layer and pixel,
 //   alpha = 1 / sqrt(q)         (0 where q == 0),
 //   beta  = sqrt(q * kappa / 2),
 // where kappa is the factor the next linear step applies to the ReLU output
 // (c inside a stage, c / 16 before a pool, sigma_w2 / n^4 before the final
 // global-average readout).  The pair kernels then form
 // rho = S alpha(i) alpha'(j) and kappa F = beta(i) beta'(j) J1(rho).
+//
+// Split.  One launch per stage; a workgroup owns one coarse slice Delta of
+// the next stage's input (or, for up to three stages, one dy of it) and runs
+// the fine slices 2 Delta + {-1, 0, 1}^2 that feed it, its maps in LDS, the
+// pooled sum in registers: no slice of the full resolution leaves the
+// workgroup.  The slices of -delta are those of delta read at the other
+// pixel, so only half of the coarse slices are formed.  What bounds it is the
+// latency of the float64 acos / sqrt chain of one layer times the layers run
+// in a row: with one workgroup per image walking all slices through global
+// scratch (the first form) that chain was 49 x 3 layers long at Myrtle-10
+// 32x32: a call on 2 and 60 images spent 2.28 ms here (two sets, one after
+// the other), one on 8192 images 18.7 ms.  Now it is 3 x 3 layers long in 15
+// workgroups per image and both sets share a launch: 0.14 ms and 13.1 ms.
 #include "nk_kernels.h"
 
 namespace nk {
 
-
-
 __host__ __device__ inline int prep_R(const NetDesc& net, int s) { return (1 << (net.S - 1 - s)) - 1; }
 
-// doubles of scratch per workgroup
-int64_t prep_scratch_doubles(const NetDesc& net) {
-  int64_t tot = 0;
-  int n0 = net.hw;
-  // q maps (all stages)
-  for (int s = 0; s < net.S; ++s) tot += (int64_t)net.depth[s] * stage_res(net, s) * stage_res(net, s);
-  // two work slices at the largest resolution
-  tot += 2LL * n0 * n0;
-  // input slices of the current stage and output slices of the next (both at most stage 1 / stage 2 sizes)
-  int64_t in_max = 0, out_max = 0;
-  for (int s = 0; s < net.S; ++s) {
-    int R = prep_R(net, s), n = stage_res(net, s);
-    int64_t v = (int64_t)(2 * R + 1) * (2 * R + 1) * n * n;
-    if (s > 0 && v > in_max) in_max = v;
-    if (s > 0 && v > out_max) out_max = v;
+// Slices kept of radius R: delta = 0, and one of each pair (delta, -delta).
+__host__ __device__ inline int prep_half(int R) { return ((2 * R + 1) * (2 * R + 1) + 1) / 2; }
+
+// Workgroups that share a coarse slice (by the dy of its fine slices).  At
+// four stages the 25 coarse slices of the first pool fill the chip by
+// themselves and one workgroup takes all nine fine slices.
+__host__ __device__ inline int prep_parts(const NetDesc& net) { return net.S <= 3 ? 3 : 1; }
+
+// Doubles before stage s's input slices in an image's scratch: the slices of
+// stages 1 .. s - 1, [part][slice][pixel] each.
+__host__ __device__ inline int64_t prep_off(const NetDesc& net, int s) {
+  int64_t t = 0;
+  for (int k = 1; k < s; ++k) t += (int64_t)prep_parts(net) * prep_half(prep_R(net, k)) * stage_res(net, k) * stage_res(net, k);
+  return t;
+}
+
+int64_t prep_scratch_doubles(const NetDesc& net) { return (prep_off(net, net.S) + 31) & ~31LL; }
+
+int64_t prep_slots(int64_t n) { return n < kPrepSlots ? n : kPrepSlots; }
+
+// Position of slice (dy, dx) among the kept ones; *neg where it is -delta
+// that is kept.
+__device__ inline int prep_slice(int dy, int dx, int R, bool* neg) {
+  *neg = dy < 0 || (dy == 0 && dx < 0);
+  if (*neg) {
+    dy = -dy;
+    dx = -dx;
   }
-  tot += in_max + out_max;
-  tot += (int64_t)n0 * n0;  // base map
-  return (tot + 31) & ~31LL;
+  return dy == 0 ? dx : 1 + R + (dy - 1) * (2 * R + 1) + dx + R;
 }
 
 __device__ inline double relu_map64(double s, double q1, double q2) {
@@ -74,64 +94,56 @@ __device__ inline double box9(const double* m, int n, int y, int x) {
   return s;
 }
 
-__global__ __launch_bounds__(256) void prepare_kernel(const PrepArgs args) {
-  const int64_t img = blockIdx.x;
-  if (img >= args.n) return;
-  const NetDesc& net = args.net;
-  const int tid = threadIdx.x, nt = blockDim.x;
-  const int C = net.C;
-  const float* x = args.x + img * (int64_t)net.hw * net.hw * C;
-  const double c = (double)net.sw2 / 9.0, b = (double)net.sb2;
-
-  double* sc = args.scratch + (int64_t)blockIdx.x * args.scratch_per_img;
-  double* qm = sc;  // all q maps
-  int64_t qlen = 0;
-  for (int s = 0; s < net.S; ++s) qlen += (int64_t)net.depth[s] * stage_res(net, s) * stage_res(net, s);
-  const int n0 = net.hw;
-  double* w0 = qm + qlen;
-  double* w1 = w0 + (int64_t)n0 * n0;
-  int64_t in_max = 0;
-  for (int s = 1; s < net.S; ++s) {
-    int R = prep_R(net, s), n = stage_res(net, s);
-    int64_t v = (int64_t)(2 * R + 1) * (2 * R + 1) * n * n;
-    if (v > in_max) in_max = v;
+// Stage input at (pixel i, pixel i + (dy, dx)) of one image, both in the image.
+__device__ inline double prep_input(const PrepArgs& a, const float* x, const double* in, int s, int n, int i, int dy,
+                                    int dx) {
+  const int C = a.net.C;
+  const int j = i + dy * n + dx;
+  if (s == 0) {
+    double v = 0.0;
+    for (int k = 0; k < C; ++k) v += (double)x[i * C + k] * (double)x[j * C + k];
+    return v / C;
   }
-  double* sl_in = w1 + (int64_t)n0 * n0;
-  double* sl_out = sl_in + in_max;
-  double* base = sl_out + in_max;
+  const int R = prep_R(a.net, s), H = prep_half(R), parts = prep_parts(a.net);
+  bool neg;
+  const int h = prep_slice(dy, dx, R, &neg);
+  const double* p = in + (int64_t)h * n * n + (neg ? j : i);
+  double v = p[0];
+  for (int k = 1; k < parts; ++k) v += p[(int64_t)k * H * n * n];
+  return v;
+}
 
-  float2* tab = args.tab + img * (int64_t)table_len(net);
+// Stage s of every image of the launch: `units` workgroups per image, each
+// one (coarse slice, part); the first of them also writes the stage's tables.
+__global__ __launch_bounds__(1024) void prepare_stage_kernel(const PrepArgs args, const int s, const int units) {
+  extern __shared__ double prep_sm[];
+  const NetDesc& net = args.net;
+  const int img = blockIdx.x / units, unit = blockIdx.x - img * units;
+  const int tid = threadIdx.x, nt = blockDim.x;
+  const int64_t gi = args.first + img;  // image of the two sets taken together
+  const bool second = gi >= args.n1;
+  const float* x = (second ? args.x2 + (gi - args.n1) * args.img_floats : args.x1 + gi * args.img_floats);
+  double* sc = args.scratch + (int64_t)img * args.scratch_per_img;
+  const double* in = sc + prep_off(net, s);
+  const double c = (double)net.sw2 / 9.0, b = (double)net.sb2;
+  const int n = stage_res(net, s), n2 = n * n, lg = 31 - __clz(n), D = net.depth[s];
+  double* w0 = prep_sm;
+  double* w1 = w0 + n2;
+  double* q = w1 + n2;
 
-  int64_t qoff = 0;
-  for (int s = 0; s < net.S; ++s) {
-    const int n = stage_res(net, s), D = net.depth[s];
-    const int R = prep_R(net, s);
-    // base map: diagonal of the stage input
-    for (int i = tid; i < n * n; i += nt) {
-      double v;
-      if (s == 0) {
-        v = 0.0;
-        for (int k = 0; k < C; ++k) v += (double)x[i * C + k] * (double)x[i * C + k];
-        v /= C;
-      } else {
-        // input slices of stage s carry radius R; delta = 0 is the centre one
-        const int side = 2 * R + 1;
-        v = sl_in[(int64_t)(R * side + R) * n * n + i];
-      }
-      base[i] = v;
-    }
+  // variance maps of the stage, from the diagonal of its input
+  for (int i = tid; i < n2; i += nt) w0[i] = prep_input(args, x, in, s, n, i, 0, 0);
+  __syncthreads();
+  for (int l = 0; l < D; ++l) {
+    const double* src = l == 0 ? w0 : q + (l - 1) * n2;
+    const double f = l == 0 ? 1.0 : 0.5;
+    for (int i = tid; i < n2; i += nt) q[l * n2 + i] = c * f * box9(src, n, i >> lg, i & (n - 1)) + b;
     __syncthreads();
-    // q maps of this stage
+  }
+  if (unit == 0) {
+    float2* tab = (second ? args.tab2 + (gi - args.n1) * (int64_t)table_len(net)
+                          : args.tab1 + gi * (int64_t)table_len(net)) + table_off(net, s);
     for (int l = 0; l < D; ++l) {
-      double* q = qm + qoff + (int64_t)l * n * n;
-      const double* src = l == 0 ? base : qm + qoff + (int64_t)(l - 1) * n * n;
-      const double f = l == 0 ? 1.0 : 0.5;
-      for (int i = tid; i < n * n; i += nt) q[i] = c * f * box9(src, n, i / n, i % n) + b;
-      __syncthreads();
-    }
-    // tables
-    for (int l = 0; l < D; ++l) {
-      const double* q = qm + qoff + (int64_t)l * n * n;
       // scale of the next linear step on this ReLU output: the next conv (c),
       // through the pools in between (1/16 each; stages without layers only
       // pool), or the global-average readout (sigma_w2 / n^4)
@@ -145,98 +157,93 @@ __global__ __launch_bounds__(256) void prepare_kernel(const PrepArgs args) {
         }
         kappa = s2 < net.S ? c * f : (double)net.sw2 / ((double)n * n * n * n);
       }
-      float2* t = tab + table_off(net, s) + l * n * n;
-      for (int i = tid; i < n * n; i += nt) {
-        double qi = q[i];
-        float al = qi > 0.0 ? (float)(1.0 / sqrt(qi)) : 0.0f;
-        float be = qi > 0.0 ? (float)sqrt(qi * kappa * 0.5) : 0.0f;
-        t[i] = make_float2(al, be);
+      for (int i = tid; i < n2; i += nt) {
+        const double qi = q[l * n2 + i];
+        const float al = qi > 0.0 ? (float)(1.0 / sqrt(qi)) : 0.0f;
+        const float be = qi > 0.0 ? (float)sqrt(qi * kappa * 0.5) : 0.0f;
+        tab[l * n2 + i] = make_float2(al, be);
       }
     }
-    if (s + 1 == net.S) break;
-
-    // run the slices |delta| <= R through this stage and pool them into the
-    // next stage's slices |Delta| <= Rn
-    const int Rn = prep_R(net, s + 1);
-    const int nn = n / 2, side_n = 2 * Rn + 1, side = 2 * R + 1;
-    for (int i = tid; i < side_n * side_n * nn * nn; i += nt) sl_out[i] = 0.0;
-    __syncthreads();
-    for (int dyi = -R; dyi <= R; ++dyi) {
-      for (int dxi = -R; dxi <= R; ++dxi) {
-        // stage input slice: valid where i and i + delta are in the image
-        for (int i = tid; i < n * n; i += nt) {
-          const int y = i / n, xx = i % n, y2 = y + dyi, x2 = xx + dxi;
-          double v = 0.0;
-          if (y2 >= 0 && y2 < n && x2 >= 0 && x2 < n) {
-            if (s == 0) {
-              for (int k = 0; k < C; ++k) v += (double)x[i * C + k] * (double)x[(y2 * n + x2) * C + k];
-              v /= C;
-            } else {
-              v = sl_in[(int64_t)((dyi + R) * side + (dxi + R)) * n * n + i];
-            }
-          }
-          w0[i] = v;
-        }
-        __syncthreads();
-        for (int l = 0; l < D; ++l) {
-          const double* q = qm + qoff + (int64_t)l * n * n;
-          for (int i = tid; i < n * n; i += nt) {
-            const int y = i / n, xx = i % n, y2 = y + dyi, x2 = xx + dxi;
-            double v = 0.0;
-            if (y2 >= 0 && y2 < n && x2 >= 0 && x2 < n) {
-              double sg = c * box9(w0, n, y, xx) + b;
-              v = relu_map64(sg, q[i], q[y2 * n + x2]);
-            }
-            w1[i] = v;
-          }
-          __syncthreads();
-          double* t = w0;
-          w0 = w1;
-          w1 = t;
-        }
-        // pool into next-stage slices: coarse (Delta, I) gathers fine i = 2I + a
-        // with (i + delta) >> 1 == I + Delta in each dimension
-        for (int e = tid; e < side_n * side_n * nn * nn; e += nt) {
-          const int Ii = e % (nn * nn), sl = e / (nn * nn);
-          const int DY = sl / side_n - Rn, DX = sl % side_n - Rn;
-          const int IY = Ii / nn, IX = Ii % nn;
-          double acc = 0.0;
-          for (int ay = 0; ay < 2; ++ay) {
-            const int fy = 2 * IY + ay, gy = fy + dyi;
-            if (gy < 0 || gy >= n || (gy >> 1) != IY + DY) continue;
-            for (int ax = 0; ax < 2; ++ax) {
-              const int fx = 2 * IX + ax, gx = fx + dxi;
-              if (gx < 0 || gx >= n || (gx >> 1) != IX + DX) continue;
-              acc += w0[fy * n + fx];
-            }
-          }
-          sl_out[e] += acc / 16.0;
-        }
-        __syncthreads();
-      }
-    }
-    // next stage input
-    for (int i = tid; i < side_n * side_n * nn * nn; i += nt) sl_in[i] = sl_out[i];
-    __syncthreads();
-    qoff += (int64_t)D * n * n;
   }
+  if (s + 1 == net.S) return;
+
+  // the fine slices of this unit's coarse slice (DY, DX), pooled: coarse
+  // pixel I of it gathers the fine pixels i = 2I + a with (i + delta) >> 1 ==
+  // I + Delta in each dimension
+  const int Rn = prep_R(net, s + 1), nn = n >> 1, H = prep_half(Rn), parts = prep_parts(net);
+  const int h = unit / parts, part = unit - h * parts;
+  int DY, DX;
+  if (h <= Rn) {
+    DY = 0;
+    DX = h;
+  } else {
+    DY = 1 + (h - 1 - Rn) / (2 * Rn + 1);
+    DX = (h - 1 - Rn) % (2 * Rn + 1) - Rn;
+  }
+  const int ey0 = parts == 3 ? part - 1 : -1, ey1 = parts == 3 ? part - 1 : 1;
+  const int IY = tid >> (lg - 1), IX = tid & (nn - 1);  // this thread's coarse pixel (tid < nn * nn)
+  const bool coarse = tid < nn * nn && IY + DY < nn && IX + DX >= 0 && IX + DX < nn;
+  double acc = 0.0;
+  for (int ey = ey0; ey <= ey1; ++ey)
+    for (int ex = -1; ex <= 1; ++ex) {
+      const int dyi = 2 * DY + ey, dxi = 2 * DX + ex;
+      for (int i = tid; i < n2; i += nt) {
+        const int y2 = (i >> lg) + dyi, x2 = (i & (n - 1)) + dxi;
+        w0[i] = (y2 >= 0 && y2 < n && x2 >= 0 && x2 < n) ? prep_input(args, x, in, s, n, i, dyi, dxi) : 0.0;
+      }
+      __syncthreads();
+      for (int l = 0; l < D; ++l) {
+        for (int i = tid; i < n2; i += nt) {
+          const int y = i >> lg, xx = i & (n - 1), y2 = y + dyi, x2 = xx + dxi;
+          double v = 0.0;
+          if (y2 >= 0 && y2 < n && x2 >= 0 && x2 < n)
+            v = relu_map64(c * box9(w0, n, y, xx) + b, q[l * n2 + i], q[l * n2 + y2 * n + x2]);
+          w1[i] = v;
+        }
+        __syncthreads();
+        double* t = w0;
+        w0 = w1;
+        w1 = t;
+      }
+      if (coarse) {
+        // e = -1: the second fine pixel, e = 1: the first, e = 0: both
+        double v = 0.0;
+        for (int ay = ey < 0 ? 1 : 0; ay <= (ey > 0 ? 0 : 1); ++ay)
+          for (int ax = ex < 0 ? 1 : 0; ax <= (ex > 0 ? 0 : 1); ++ax) v += w0[(2 * IY + ay) * n + 2 * IX + ax];
+        acc += v / 16.0;
+      }
+      __syncthreads();
+    }
+  if (tid < nn * nn) sc[prep_off(net, s + 1) + ((int64_t)part * H + h) * nn * nn + tid] = acc;
 }
 
-int launch_prepare(const float* x, int64_t n, const NetDesc& net, float2* tab, double* scratch,
-                   int64_t max_blocks, hipStream_t stream) {
-  const int64_t per = prep_scratch_doubles(net);
-  for (int64_t s = 0; s < n; s += max_blocks) {
-    int64_t cnt = n - s < max_blocks ? n - s : max_blocks;
-    PrepArgs a;
-    a.x = x + s * (int64_t)net.hw * net.hw * net.C;
-    a.n = cnt;
-    a.net = net;
-    a.tab = tab + s * (int64_t)table_len(net);
-    a.scratch = scratch;
-    a.scratch_per_img = per;
-    hipLaunchKernelGGL(prepare_kernel, dim3((unsigned)cnt), dim3(256), 0, stream, a);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return -3;
+int launch_prepare(const float* x1, int64_t n1, float2* tab1, const float* x2, int64_t n2, float2* tab2,
+                   const NetDesc& net, double* scratch, int64_t slots, hipStream_t stream) {
+  static std::atomic<size_t> seen[kMaxDevices];
+  PrepArgs a;
+  a.x1 = x1;
+  a.x2 = x2;
+  a.n1 = n1;
+  a.net = net;
+  a.img_floats = (int64_t)net.hw * net.hw * net.C;
+  a.tab1 = tab1;
+  a.tab2 = tab2;
+  a.scratch = scratch;
+  a.scratch_per_img = prep_scratch_doubles(net);
+  const int64_t n = n1 + (x2 ? n2 : 0);
+  for (int64_t at = 0; at < n; at += slots) {
+    a.first = at;
+    const int64_t cnt = n - at < slots ? n - at : slots;
+    for (int s = 0; s < net.S; ++s) {
+      const int m = stage_res(net, s) * stage_res(net, s);
+      const int units = s + 1 < net.S ? prep_half(prep_R(net, s + 1)) * prep_parts(net) : 1;
+      const int threads = m < 64 ? 64 : (m > 1024 ? 1024 : m);
+      const size_t lds = (size_t)(2 + net.depth[s]) * m * sizeof(double);
+      if (allow_dyn_lds((const void*)prepare_stage_kernel, lds, seen)) return -3;
+      hipLaunchKernelGGL(prepare_stage_kernel, dim3((unsigned)(cnt * units)), dim3((unsigned)threads), lds, stream, a,
+                         s, units);
+      if (hipGetLastError() != hipSuccess) return -3;
+    }
   }
   return 0;
 }
