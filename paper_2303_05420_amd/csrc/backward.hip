@@ -9,322 +9,237 @@
 // bias term contributes v_bar to d/dsigma_b2.  J1' = 1 - acos(rho) / pi uses
 // the acos fit of nk_common.h; nothing differentiates sqrt or acos at rho = 1.
 //
-// Self recursions (prepare_bwd_kernel, float64).  The variance maps are the
-// output of the reduced self recursion of prepare.hip; it is re-run with its
-// intermediate pre-activations kept, and reversed: ReLU partials
+// Self recursions (prep_rev_*, float64).  The variance maps are the output of
+// the reduced self recursion of prepare.hip; it is reversed stage by stage
+// with the ReLU partials
 //   dF/ds = (pi - t)/(2 pi),  dF/dq = sin t sqrt(q'/q) / (4 pi)
 // on the slices, the box chains of the diagonal, the pools and the seed.
+// Per stage, one launch with a workgroup per kept slice (it re-runs the
+// slice's layers from the stage input into LDS and reverses them; a slice
+// delta != 0 stands for -delta too, whose contributions are the same, and
+// counts twice) and one launch with a workgroup per image for the diagonal
+// chain.  The slices of an image meet in its q_bar maps and image gradients
+// through float64 atomic adds, one per pixel, layer and slice.  As in the
+// forward, latency of the acos / sqrt chain is the bound: a workgroup per
+// image that walked all slices through global scratch took 4.75 ms for sets
+// of 20 and 100 images at Myrtle-5 32x32, these launches take 0.50 ms
+// together (slices 0.29, their forward inputs 0.17, chains 0.03).
+#include "prep.h"
 #include "stage_bwd.h"
 
 namespace nk {
 
-// ---------------------------------------------------------------------------
-// Self recursions, float64, one workgroup per image.
-// ---------------------------------------------------------------------------
+// Per image: the stage inputs of prepare.hip, q_bar maps (table layout), and
+// the adjoints of the kept slices of the stage inputs.
+__host__ __device__ inline int64_t rev_qbar_off(const NetDesc& net) { return prep_off(net, net.S); }
 
-__device__ inline double relu_map64b(double s, double q1, double q2, double* ds, double* dq1, double* dq2) {
-  const double qq = q1 * q2;
-  if (!(qq > 0.0)) {
-    *ds = *dq1 = *dq2 = 0.0;
-    return 0.0;
-  }
-  const double nrm = sqrt(qq);
-  double rho = s / nrm;
-  rho = rho > 1.0 ? 1.0 : (rho < -1.0 ? -1.0 : rho);
-  const double th = acos(rho);
-  const double sn = sqrt(fmax(1.0 - rho * rho, 0.0));
-  *ds = (M_PI - th) * (0.5 / M_PI);
-  *dq1 = sn * sqrt(q2 / q1) * (0.25 / M_PI);
-  *dq2 = sn * sqrt(q1 / q2) * (0.25 / M_PI);
-  return nrm * (sn + (M_PI - th) * rho) * (0.5 / M_PI);
+__host__ __device__ inline int64_t rev_slices_off(const NetDesc& net, int s) {
+  int64_t t = prep_off(net, net.S) + table_len(net);
+  for (int k = 1; k < s; ++k) t += (int64_t)prep_half(prep_R(net, k)) * stage_res(net, k) * stage_res(net, k);
+  return t;
 }
 
-__device__ inline double box9b(const double* m, int n, int y, int x) {
-  double s = 0.0;
-  for (int dy = -1; dy <= 1; ++dy) {
-    const int yy = y + dy;
-    if (yy < 0 || yy >= n) continue;
-    for (int dx = -1; dx <= 1; ++dx) {
-      const int xx = x + dx;
-      if (xx < 0 || xx >= n) continue;
-      s += m[yy * n + xx];
-    }
-  }
-  return s;
-}
+int64_t prep_bwd_scratch_doubles(const NetDesc& net) { return (rev_slices_off(net, net.S) + 31) & ~31LL; }
 
-__device__ inline int prep_R2(const NetDesc& net, int s) { return (1 << (net.S - 1 - s)) - 1; }
+int64_t prep_bwd_slots(int64_t n) { return n < kPrepBwdSlots ? n : kPrepBwdSlots; }
 
-// Doubles of scratch per workgroup for prepare_bwd_kernel.
-int64_t prep_bwd_scratch_doubles(const NetDesc& net) {
-  int64_t t = 0;
-  for (int s = 0; s < net.S; ++s) {
-    const int n = stage_res(net, s), R = (1 << (net.S - 1 - s)) - 1, side = 2 * R + 1;
-    const int64_t n2 = (int64_t)n * n;
-    t += net.depth[s] * n2 * 2;              // q maps, q bar
-    t += n2;                                 // base
-    if (s + 1 < net.S) t += (int64_t)side * side * net.depth[s] * n2;  // tape of pre-activations
-    t += (int64_t)side * side * n2 * 2;      // input slices and their adjoints
-  }
-  t += 4LL * net.hw * net.hw;  // work buffers
-  return (t + 31) & ~31LL;
-}
-
-__global__ __launch_bounds__(256) void prepare_bwd_kernel(const PrepBwdArgs args) {
-  const int64_t img = blockIdx.x;
-  if (img >= args.n) return;
-  const NetDesc& net = args.net;
-  const int tid = threadIdx.x, nt = blockDim.x;
-  const int C = net.C;
-  const float* x = args.x + img * (int64_t)net.hw * net.hw * C;
-  const double c = (double)net.sw2 / 9.0, b = (double)net.sb2;
-  const double* W = args.W + img * (int64_t)args.tablen;
-  double* xbar = args.xbar + img * (int64_t)net.hw * net.hw * C;
-
-  // scratch layout (per stage: q, qbar, base, tape, slices in, slices in adjoint)
-  double* sc = args.scratch + (int64_t)blockIdx.x * args.scratch_per_img;
-  double* q_[NK_MAX_STAGES];
-  double* qb_[NK_MAX_STAGES];
-  double* base_[NK_MAX_STAGES];
-  double* tape_[NK_MAX_STAGES];
-  double* sin_[NK_MAX_STAGES];
-  double* sinb_[NK_MAX_STAGES];
-  {
-    double* p = sc;
-    for (int s = 0; s < net.S; ++s) {
-      const int n = stage_res(net, s), R = prep_R2(net, s), side = 2 * R + 1;
-      const int64_t n2 = (int64_t)n * n;
-      q_[s] = p;
-      p += net.depth[s] * n2;
-      qb_[s] = p;
-      p += net.depth[s] * n2;
-      base_[s] = p;
-      p += n2;
-      tape_[s] = p;
-      if (s + 1 < net.S) p += (int64_t)side * side * net.depth[s] * n2;
-      sin_[s] = p;
-      p += (int64_t)side * side * n2;
-      sinb_[s] = p;
-      p += (int64_t)side * side * n2;
-    }
-    (void)p;
-  }
-  double* wA = sc + args.scratch_per_img - 4LL * net.hw * net.hw;
-  double* wB = wA + (int64_t)net.hw * net.hw;
-  double* wC = wB + (int64_t)net.hw * net.hw;
-  double* wD = wC + (int64_t)net.hw * net.hw;
-
-  double accw = 0.0, accb = 0.0;  // d/dsigma_w2 (times sigma_w2), d/dsigma_b2
-
-  // ---------------- forward with tape ----------------
-  for (int s = 0; s < net.S; ++s) {
-    const int n = stage_res(net, s), D = net.depth[s], R = prep_R2(net, s), side = 2 * R + 1;
-    const int64_t n2 = (int64_t)n * n;
-    for (int i = tid; i < n2; i += nt) {
-      double v;
-      if (s == 0) {
-        v = 0.0;
-        for (int k = 0; k < C; ++k) v += (double)x[i * C + k] * (double)x[i * C + k];
-        v /= C;
-      } else {
-        v = sin_[s][(int64_t)(R * side + R) * n2 + i];
-      }
-      base_[s][i] = v;
-    }
-    __syncthreads();
-    for (int l = 0; l < D; ++l) {
-      const double* src = l == 0 ? base_[s] : q_[s] + (l - 1) * n2;
-      const double f = l == 0 ? 1.0 : 0.5;
-      for (int i = tid; i < n2; i += nt) q_[s][l * n2 + i] = c * f * box9b(src, n, i / n, i % n) + b;
-      __syncthreads();
-    }
-    if (s + 1 == net.S) break;
-    const int Rn = prep_R2(net, s + 1), nn = n / 2, side_n = 2 * Rn + 1;
-    double* nxt = sin_[s + 1];
-    for (int i = tid; i < side_n * side_n * nn * nn; i += nt) nxt[i] = 0.0;
-    __syncthreads();
-    for (int dyi = -R; dyi <= R; ++dyi)
-      for (int dxi = -R; dxi <= R; ++dxi) {
-        const int sl = (dyi + R) * side + (dxi + R);
-        for (int i = tid; i < n2; i += nt) {
-          const int y = i / n, xx = i % n, y2 = y + dyi, x2 = xx + dxi;
-          double v = 0.0;
-          if (y2 >= 0 && y2 < n && x2 >= 0 && x2 < n) {
-            if (s == 0) {
-              for (int k = 0; k < C; ++k) v += (double)x[i * C + k] * (double)x[(y2 * n + x2) * C + k];
-              v /= C;
-            } else {
-              v = sin_[s][(int64_t)sl * n2 + i];
-            }
-          }
-          wA[i] = v;
-        }
-        __syncthreads();
-        for (int l = 0; l < D; ++l) {
-          const double* q = q_[s] + l * n2;
-          double* tp = tape_[s] + ((int64_t)sl * D + l) * n2;
-          for (int i = tid; i < n2; i += nt) {
-            const int y = i / n, xx = i % n, y2 = y + dyi, x2 = xx + dxi;
-            double v = 0.0, sg = 0.0;
-            if (y2 >= 0 && y2 < n && x2 >= 0 && x2 < n) {
-              sg = c * box9b(wA, n, y, xx) + b;
-              double d0, d1, d2;
-              v = relu_map64b(sg, q[i], q[y2 * n + x2], &d0, &d1, &d2);
-            }
-            tp[i] = sg;
-            wB[i] = v;
-          }
-          __syncthreads();
-          for (int i = tid; i < n2; i += nt) wA[i] = wB[i];
-          __syncthreads();
-        }
-        for (int e = tid; e < side_n * side_n * nn * nn; e += nt) {
-          const int Ii = e % (nn * nn), sl2 = e / (nn * nn);
-          const int DY = sl2 / side_n - Rn, DX = sl2 % side_n - Rn;
-          const int IY = Ii / nn, IX = Ii % nn;
-          double acc = 0.0;
-          for (int ay = 0; ay < 2; ++ay) {
-            const int fy = 2 * IY + ay, gy = fy + dyi;
-            if (gy < 0 || gy >= n || (gy >> 1) != IY + DY) continue;
-            for (int ax = 0; ax < 2; ++ax) {
-              const int fx = 2 * IX + ax, gx = fx + dxi;
-              if (gx < 0 || gx >= n || (gx >> 1) != IX + DX) continue;
-              acc += wA[fy * n + fx];
-            }
-          }
-          nxt[e] += acc / 16.0;
-        }
-        __syncthreads();
-      }
-  }
-
-  // ---------------- reverse ----------------
-  for (int s = 0; s < net.S; ++s) {
-    const int n = stage_res(net, s), D = net.depth[s];
-    const int64_t n2 = (int64_t)n * n;
-    const int64_t toff = table_off(net, s);
-    for (int l = 0; l < D; ++l)
-      for (int i = tid; i < n2; i += nt) {
-        const double qv = q_[s][l * n2 + i];
-        qb_[s][l * n2 + i] = qv > 0.0 ? W[toff + l * n2 + i] / (2.0 * qv) : 0.0;
-      }
-    const int R = prep_R2(net, s), side = 2 * R + 1;
-    for (int i = tid; i < side * side * n2; i += nt) sinb_[s][i] = 0.0;
-  }
-  __syncthreads();
-
-  for (int s = net.S - 1; s >= 0; --s) {
-    const int n = stage_res(net, s), D = net.depth[s], R = prep_R2(net, s), side = 2 * R + 1;
-    const int64_t n2 = (int64_t)n * n;
-    if (s + 1 < net.S) {
-      const int Rn = prep_R2(net, s + 1), nn = n / 2, side_n = 2 * Rn + 1;
-      const double* pb = sinb_[s + 1];
-      for (int dyi = -R; dyi <= R; ++dyi)
-        for (int dxi = -R; dxi <= R; ++dxi) {
-          const int sl = (dyi + R) * side + (dxi + R);
-          // adjoint of this slice's stage output, from the pooled slices
-          for (int i = tid; i < n2; i += nt) {
-            const int y = i / n, xx = i % n, y2 = y + dyi, x2 = xx + dxi;
-            double v = 0.0;
-            if (y2 >= 0 && y2 < n && x2 >= 0 && x2 < n) {
-              const int IY = y >> 1, IX = xx >> 1, DY = (y2 >> 1) - IY, DX = (x2 >> 1) - IX;
-              if (DY >= -Rn && DY <= Rn && DX >= -Rn && DX <= Rn)
-                v = pb[((int64_t)(DY + Rn) * side_n + (DX + Rn)) * nn * nn + IY * nn + IX] / 16.0;
-            }
-            wA[i] = v;
-          }
-          __syncthreads();
-          for (int l = D - 1; l >= 0; --l) {
-            const double* q = q_[s] + l * n2;
-            const double* tp = tape_[s] + ((int64_t)sl * D + l) * n2;
-            double* qb = qb_[s] + l * n2;
-            // pass 1: sigma bar, q bar at i
-            for (int i = tid; i < n2; i += nt) {
-              const int y = i / n, xx = i % n, y2 = y + dyi, x2 = xx + dxi;
-              double sgb = 0.0, dq2 = 0.0;
-              if (y2 >= 0 && y2 < n && x2 >= 0 && x2 < n) {
-                double d0, d1;
-                relu_map64b(tp[i], q[i], q[y2 * n + x2], &d0, &d1, &dq2);
-                sgb = wA[i] * d0;
-                qb[i] += wA[i] * d1;
-                accw += sgb * (tp[i] - b);
-                accb += sgb;
-              }
-              wB[i] = sgb;
-              wC[i] = wA[i] * dq2;
-            }
-            __syncthreads();
-            // pass 2: q bar at i + delta (a bijection, no races)
-            for (int i = tid; i < n2; i += nt) {
-              const int y = i / n, xx = i % n, y2 = y + dyi, x2 = xx + dxi;
-              if (y2 >= 0 && y2 < n && x2 >= 0 && x2 < n) qb[y2 * n + x2] += wC[i];
-            }
-            __syncthreads();
-            for (int i = tid; i < n2; i += nt) {
-              const int y = i / n, xx = i % n, y2 = y + dyi, x2 = xx + dxi;
-              wA[i] = (y2 >= 0 && y2 < n && x2 >= 0 && x2 < n) ? c * box9b(wB, n, y, xx) : 0.0;
-            }
-            __syncthreads();
-          }
-          // wA = adjoint of the stage-input slice
-          if (s == 0) {
-            for (int i = tid; i < n2; i += nt) {
-              const int y = i / n, xx = i % n, y2 = y + dyi, x2 = xx + dxi;
-              if (y2 >= 0 && y2 < n && x2 >= 0 && x2 < n)
-                for (int k = 0; k < C; ++k) xbar[i * C + k] += wA[i] * (double)x[(y2 * n + x2) * C + k] / C;
-            }
-            __syncthreads();
-            for (int i = tid; i < n2; i += nt) {
-              const int y = i / n, xx = i % n, y2 = y + dyi, x2 = xx + dxi;
-              if (y2 >= 0 && y2 < n && x2 >= 0 && x2 < n)
-                for (int k = 0; k < C; ++k) xbar[(y2 * n + x2) * C + k] += wA[i] * (double)x[i * C + k] / C;
-            }
-          } else {
-            for (int i = tid; i < n2; i += nt) sinb_[s][(int64_t)sl * n2 + i] += wA[i];
-          }
-          __syncthreads();
-        }
-    }
-    // diagonal chain: q_1 = c box(base) + b, q_{l+1} = c box(q_l / 2) + b
-    for (int l = D - 1; l >= 0; --l) {
-      const double* qbl = qb_[s] + l * n2;
-      const double* ql = q_[s] + l * n2;
-      for (int i = tid; i < n2; i += nt) {
-        accw += qbl[i] * (ql[i] - b);
-        accb += qbl[i];
-      }
-      double* dst = l > 0 ? qb_[s] + (l - 1) * n2 : wD;
-      const double f = l > 0 ? 0.5 : 1.0;
-      __syncthreads();
-      for (int i = tid; i < n2; i += nt) {
-        const double v = c * f * box9b(qbl, n, i / n, i % n);
-        if (l > 0)
-          dst[i] += v;
-        else
-          dst[i] = v;
-      }
-      __syncthreads();
-    }
-    if (D > 0) {
-      // wD = adjoint of the base map
-      if (s == 0) {
-        for (int i = tid; i < n2; i += nt)
-          for (int k = 0; k < C; ++k) xbar[i * C + k] += 2.0 * wD[i] * (double)x[i * C + k] / C;
-      } else {
-        for (int i = tid; i < n2; i += nt) sinb_[s][(int64_t)(R * side + R) * n2 + i] += wD[i];
-      }
-    }
-    __syncthreads();
-  }
-  // sums: accw is sum of s_bar (s - b) = sigma_w2 * d/dsigma_w2 contributions
+// accw and accb of the workgroup into sums, one atomic add each.
+__device__ inline void rev_sums(double accw, double accb, double* __restrict__ sums) {
+  __shared__ double part[2][16];
   for (int off = 32; off >= 1; off >>= 1) {
     accw += __shfl_xor(accw, off);
     accb += __shfl_xor(accb, off);
   }
-  if ((tid & 63) == 0) {
-    atomicAdd(&args.sums[0], accw);
-    atomicAdd(&args.sums[1], accb);
+  const int w = threadIdx.x >> 6, nw = (blockDim.x + 63) >> 6;
+  if ((threadIdx.x & 63) == 0) {
+    part[0][w] = accw;
+    part[1][w] = accb;
   }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    double a = 0.0, b = 0.0;
+    for (int k = 0; k < nw; ++k) {
+      a += part[0][k];
+      b += part[1][k];
+    }
+    atomicAdd(&sums[0], a);  // sum of s_bar (s - b) = sigma_w2 * d/dsigma_w2 contributions
+    atomicAdd(&sums[1], b);
+  }
+}
+
+// Reverse of one kept slice of a pooling stage s (maps of at most 32 x 32).
+__global__ __launch_bounds__(1024) void prep_rev_slice_kernel(const PrepRevArgs args, const int s, const int units) {
+  extern __shared__ double rev_sm[];
+  const PrepArgs& fa = args.fwd;
+  const NetDesc& net = fa.net;
+  const int img = blockIdx.x / units, h = blockIdx.x - img * units;
+  const int tid = threadIdx.x, nt = blockDim.x;
+  const int64_t gi = fa.first + img;
+  const bool second = gi >= fa.n1;
+  const float* x = second ? fa.x2 + (gi - fa.n1) * fa.img_floats : fa.x1 + gi * fa.img_floats;
+  double* sc = fa.scratch + (int64_t)img * fa.scratch_per_img;
+  const double* in = sc + prep_off(net, s);
+  double* qbar = sc + rev_qbar_off(net) + table_off(net, s);
+  const double c = (double)net.sw2 / 9.0, b = (double)net.sb2;
+  const int n = stage_res(net, s), n2 = n * n, lg = 31 - __clz(n), D = net.depth[s], R = prep_R(net, s);
+  int dyi, dxi;
+  prep_delta(h, R, &dyi, &dxi);
+  const double wgt = h == 0 ? 1.0 : 2.0;
+  const int dlt = dyi * n + dxi;
+  double* wA = rev_sm;
+  double* wB = wA + n2;
+  double* wC = wB + n2;
+  double* q = wC + n2;
+  double* tape = q + D * n2;
+  // i + delta and i - delta inside the image
+  auto fwd_ok = [&](int i) {
+    const int y = (i >> lg) + dyi, xx = (i & (n - 1)) + dxi;
+    return y >= 0 && y < n && xx >= 0 && xx < n;
+  };
+  auto back_ok = [&](int i) {
+    const int y = (i >> lg) - dyi, xx = (i & (n - 1)) - dxi;
+    return y >= 0 && y < n && xx >= 0 && xx < n;
+  };
+  for (int i = tid; i < n2; i += nt) wA[i] = prep_input(fa, x, in, s, n, i, 0, 0);
+  __syncthreads();
+  prep_variances(wA, q, n, lg, D, c, b);
+
+  // forward, keeping the pre-activations
+  for (int i = tid; i < n2; i += nt) wA[i] = fwd_ok(i) ? prep_input(fa, x, in, s, n, i, dyi, dxi) : 0.0;
+  __syncthreads();
+  for (int l = 0; l < D; ++l) {
+    for (int i = tid; i < n2; i += nt) {
+      double v = 0.0, sg = 0.0;
+      if (fwd_ok(i)) {
+        sg = c * box9(wA, n, i >> lg, i & (n - 1)) + b;
+        if (l + 1 < D) v = relu_map64(sg, q[l * n2 + i], q[l * n2 + i + dlt]);
+      }
+      tape[l * n2 + i] = sg;
+      wB[i] = v;
+    }
+    __syncthreads();
+    double* t = wA;
+    wA = wB;
+    wB = t;
+  }
+
+  // adjoint of the slice's stage output, from the pooled slices
+  {
+    const int Rn = prep_R(net, s + 1), nn = n >> 1;
+    const double* pb = sc + rev_slices_off(net, s + 1);
+    for (int i = tid; i < n2; i += nt) {
+      double v = 0.0;
+      if (fwd_ok(i)) {
+        const int y = i >> lg, xx = i & (n - 1);
+        const int IY = y >> 1, IX = xx >> 1, DY = ((y + dyi) >> 1) - IY, DX = ((xx + dxi) >> 1) - IX;
+        if (DY >= -Rn && DY <= Rn && DX >= -Rn && DX <= Rn) {
+          bool neg;
+          const int hn = prep_slice(DY, DX, Rn, &neg);
+          const int I = IY * nn + IX;
+          v = pb[(int64_t)hn * nn * nn + (neg ? I + DY * nn + DX : I)] / 16.0;
+        }
+      }
+      wA[i] = v;
+    }
+  }
+  __syncthreads();
+
+  double accw = 0.0, accb = 0.0;
+  for (int l = D - 1; l >= 0; --l) {
+    const double* ql = q + l * n2;
+    const double* tp = tape + l * n2;
+    // sigma_bar, and the two sides' q_bar
+    for (int i = tid; i < n2; i += nt) {
+      double sgb = 0.0, q1 = 0.0, q2 = 0.0;
+      if (fwd_ok(i)) {
+        double d0, d1, d2;
+        relu_partials64(tp[i], ql[i], ql[i + dlt], &d0, &d1, &d2);
+        sgb = wA[i] * d0;
+        q1 = wA[i] * d1;
+        q2 = wA[i] * d2;
+        accw += wgt * sgb * (tp[i] - b);
+        accb += wgt * sgb;
+      }
+      wB[i] = sgb;
+      wC[i] = q2;
+      wA[i] = q1;
+    }
+    __syncthreads();
+    for (int i = tid; i < n2; i += nt) {
+      const double g = wA[i] + (back_ok(i) ? wC[i - dlt] : 0.0);
+      atomicAdd(&qbar[l * n2 + i], wgt * g);
+      wA[i] = fwd_ok(i) ? c * box9(wB, n, i >> lg, i & (n - 1)) : 0.0;
+    }
+    __syncthreads();
+  }
+  // wA = adjoint of the stage-input slice
+  if (s == 0) {
+    const int C = net.C;
+    double* xbar = second ? args.xbar2 + (gi - fa.n1) * fa.img_floats : args.xbar1 + gi * fa.img_floats;
+    for (int i = tid; i < n2; i += nt) {
+      const bool f = fwd_ok(i), k = back_ok(i);
+      const double g1 = f ? wA[i] : 0.0, g2 = k ? wA[i - dlt] : 0.0;
+      const int i1 = f ? i + dlt : i, i2 = k ? i - dlt : i;
+      for (int ch = 0; ch < C; ++ch)
+        atomicAdd(&xbar[i * C + ch], wgt * (g1 * (double)x[i1 * C + ch] + g2 * (double)x[i2 * C + ch]) / C);
+    }
+  } else {
+    double* o = sc + rev_slices_off(net, s) + (int64_t)h * n2;
+    for (int i = tid; i < n2; i += nt) o[i] = wA[i];
+  }
+  rev_sums(accw, accb, args.sums);
+}
+
+// Reverse of the diagonal chain of stage s, q_1 = c box(base) + b, q_{l+1} =
+// c box(q_l / 2) + b, after the stage's slices; one workgroup per image.
+__global__ __launch_bounds__(1024) void prep_rev_chain_kernel(const PrepRevArgs args, const int s) {
+  extern __shared__ double rev_sm[];
+  const PrepArgs& fa = args.fwd;
+  const NetDesc& net = fa.net;
+  const int img = blockIdx.x, tid = threadIdx.x, nt = blockDim.x;
+  const int64_t gi = fa.first + img;
+  const bool second = gi >= fa.n1;
+  const float* x = second ? fa.x2 + (gi - fa.n1) * fa.img_floats : fa.x1 + gi * fa.img_floats;
+  const double* W = (second ? args.W2 + (gi - fa.n1) * (int64_t)args.tablen : args.W1 + gi * (int64_t)args.tablen) +
+                    table_off(net, s);
+  double* sc = fa.scratch + (int64_t)img * fa.scratch_per_img;
+  const double* in = sc + prep_off(net, s);
+  const double* qbar = sc + rev_qbar_off(net) + table_off(net, s);
+  const double c = (double)net.sw2 / 9.0, b = (double)net.sb2;
+  const int n = stage_res(net, s), n2 = n * n, lg = 31 - __clz(n), D = net.depth[s];
+  double* w = rev_sm;
+  double* g = w + n2;
+  double* q = g + n2;
+  for (int i = tid; i < n2; i += nt) w[i] = prep_input(fa, x, in, s, n, i, 0, 0);
+  __syncthreads();
+  prep_variances(w, q, n, lg, D, c, b);
+  double accw = 0.0, accb = 0.0;
+  // g = q_bar of layer l: the tables' and the slices' share, and that of layer l + 1
+  for (int i = tid; i < n2; i += nt) w[i] = 0.0;
+  __syncthreads();
+  for (int l = D - 1; l >= 0; --l) {
+    for (int i = tid; i < n2; i += nt) {
+      const double qv = q[l * n2 + i];
+      const double v = (qv > 0.0 ? W[l * n2 + i] / (2.0 * qv) : 0.0) + qbar[l * n2 + i] + w[i];
+      accw += v * (qv - b);
+      accb += v;
+      g[i] = v;
+    }
+    __syncthreads();
+    for (int i = tid; i < n2; i += nt) w[i] = (l > 0 ? 0.5 * c : c) * box9(g, n, i >> lg, i & (n - 1));
+    __syncthreads();
+  }
+  // w = adjoint of the base map (0 without layers)
+  if (s == 0) {
+    const int C = net.C;
+    double* xbar = second ? args.xbar2 + (gi - fa.n1) * fa.img_floats : args.xbar1 + gi * fa.img_floats;
+    for (int i = tid; i < n2; i += nt)
+      for (int ch = 0; ch < C; ++ch) xbar[i * C + ch] += 2.0 * w[i] * (double)x[i * C + ch] / C;
+  } else {
+    double* o = sc + rev_slices_off(net, s);
+    for (int i = tid; i < n2; i += nt) o[i] = (s + 1 < net.S ? o[i] : 0.0) + w[i];
+  }
+  rev_sums(accw, accb, args.sums);
 }
 
 // dx (float) = xbar (double) over n images
@@ -363,23 +278,46 @@ int launch_stage_bwd(int N, const StageBwdArgs& a, bool seed, hipStream_t s) {
   return launch_stage_bwd_small(N, a, seed, s);
 }
 
-int launch_prepare_bwd(const float* x, int64_t n, const NetDesc& net, const double* W, int tablen, double* xbar,
-                       double* sums, double* scratch, int64_t max_blocks, hipStream_t stream) {
-  const int64_t per = prep_bwd_scratch_doubles(net);
-  for (int64_t s = 0; s < n; s += max_blocks) {
-    const int64_t cnt = n - s < max_blocks ? n - s : max_blocks;
-    PrepBwdArgs a;
-    a.x = x + s * (int64_t)net.hw * net.hw * net.C;
-    a.n = cnt;
-    a.net = net;
-    a.W = W + s * (int64_t)tablen;
-    a.tablen = tablen;
-    a.xbar = xbar + s * (int64_t)net.hw * net.hw * net.C;
-    a.sums = sums;
-    a.scratch = scratch;
-    a.scratch_per_img = per;
-    hipLaunchKernelGGL(prepare_bwd_kernel, dim3((unsigned)cnt), dim3(256), 0, stream, a);
-    if (hipGetLastError() != hipSuccess) return -3;
+int launch_prepare_bwd(const float* x1, int64_t n1, const double* W1, double* xbar1, const float* x2, int64_t n2,
+                       const double* W2, double* xbar2, const NetDesc& net, double* sums, double* scratch,
+                       int64_t slots, hipStream_t stream) {
+  static std::atomic<size_t> seen_s[kMaxDevices], seen_c[kMaxDevices];
+  PrepRevArgs a;
+  a.fwd.x1 = x1;
+  a.fwd.x2 = x2;
+  a.fwd.n1 = n1;
+  a.fwd.net = net;
+  a.fwd.img_floats = (int64_t)net.hw * net.hw * net.C;
+  a.fwd.tab1 = a.fwd.tab2 = nullptr;
+  a.fwd.scratch = scratch;
+  a.fwd.scratch_per_img = prep_bwd_scratch_doubles(net);
+  a.W1 = W1;
+  a.W2 = W2;
+  a.tablen = table_len(net);
+  a.xbar1 = xbar1;
+  a.xbar2 = xbar2;
+  a.sums = sums;
+  const int64_t n = n1 + (x2 ? n2 : 0);
+  for (int64_t at = 0; at < n; at += slots) {
+    a.fwd.first = at;
+    const int64_t cnt = n - at < slots ? n - at : slots;
+    if (launch_zero_f64(scratch, cnt * a.fwd.scratch_per_img, stream)) return -3;
+    if (launch_prepare_stages(a.fwd, cnt, net.S - 1, stream)) return -3;
+    for (int s = net.S - 1; s >= 0; --s) {
+      const int m = stage_res(net, s) * stage_res(net, s), D = net.depth[s];
+      if (s + 1 < net.S) {
+        const int units = prep_half(prep_R(net, s));
+        const size_t lds = (size_t)(3 + 2 * D) * m * sizeof(double);
+        if (allow_dyn_lds((const void*)prep_rev_slice_kernel, lds, seen_s)) return -3;
+        hipLaunchKernelGGL(prep_rev_slice_kernel, dim3((unsigned)(cnt * units)), dim3((unsigned)prep_threads(m)), lds,
+                           stream, a, s, units);
+      }
+      const size_t lds = (size_t)(2 + D) * m * sizeof(double);
+      if (allow_dyn_lds((const void*)prep_rev_chain_kernel, lds, seen_c)) return -3;
+      hipLaunchKernelGGL(prep_rev_chain_kernel, dim3((unsigned)cnt), dim3((unsigned)prep_threads(m)), lds, stream, a,
+                         s);
+      if (hipGetLastError() != hipSuccess) return -3;
+    }
   }
   return 0;
 }

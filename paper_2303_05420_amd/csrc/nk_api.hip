@@ -190,8 +190,6 @@ MyrtlePlan plan_myrtle(const NetDesc& net, int64_t n1, int64_t n2, bool sym, int
   return p;
 }
 
-constexpr int64_t kPrepBwdBlocks = 256;  // images per self-recursion adjoint launch
-
 struct BwdPlan {
   size_t tab1 = 0, tab2 = 0, scratch = 0, W1 = 0, W2 = 0, xb1 = 0, xb2 = 0, sums = 0, bscratch = 0;
   size_t buf[NK_MAX_STAGES] = {0, 0, 0, 0}, gbuf[NK_MAX_STAGES] = {0, 0, 0, 0};
@@ -212,7 +210,7 @@ BwdPlan plan_bwd(const NetDesc& net, int64_t n1, int64_t n2, bool sym, int64_t c
   p.xb1 = b.take(img * sizeof(double) * n1);
   p.xb2 = sym ? p.xb1 : b.take(img * sizeof(double) * n2);
   p.sums = b.take(4 * sizeof(double));
-  const int64_t pbb = std::min<int64_t>(std::max(n1, n2), kPrepBwdBlocks);
+  const int64_t pbb = nk::prep_bwd_slots(sym ? n1 : n1 + n2);
   p.bscratch = b.take((size_t)nk::prep_bwd_scratch_doubles(net) * sizeof(double) * pbb);
   for (int s = 1; s < net.S; ++s) {
     const size_t n = (size_t)(net.hw >> s);
@@ -770,7 +768,7 @@ KrrGradPlan plan_krr_grad(const NetDesc& net, int64_t n, int64_t m, int64_t c, i
   p.xb_s = b.take(img * sizeof(double) * n);
   p.xb_t = b.take(img * sizeof(double) * m);
   p.sums = b.take(4 * sizeof(double));
-  const int64_t pbb = std::min<int64_t>(std::max(n, m), kPrepBwdBlocks);
+  const int64_t pbb = nk::prep_bwd_slots(n + m);
   p.bscratch = b.take((size_t)nk::prep_bwd_scratch_doubles(net) * sizeof(double) * pbb);
   for (int s = 1; s < net.S; ++s) {
     const size_t q = (size_t)(net.hw >> s);
@@ -1304,9 +1302,8 @@ int nk_myrtle_nngp_backward(const float* x1, int64_t n1, const float* x2, int64_
     return rc;
   {
     ProfScope ps("myrtle_self_bwd", s);
-    double* bs = at<double>(ws, p.bscratch);
-    if (nk::launch_prepare_bwd(x1, n1, net, W1, tl, xb1, sums, bs, kPrepBwdBlocks, s)) return hip_fail("self adjoint");
-    if (!sym && nk::launch_prepare_bwd(x2, n2, net, W2, tl, xb2, sums, bs, kPrepBwdBlocks, s))
+    if (nk::launch_prepare_bwd(x1, n1, W1, xb1, sym ? nullptr : x2, n2, W2, xb2, net, sums, at<double>(ws, p.bscratch),
+                               nk::prep_bwd_slots(sym ? n1 : n1 + n2), s))
       return hip_fail("self adjoint");
   }
   if (dx1 && nk::launch_cast_grad(xb1, dx1, n1 * img, s)) return hip_fail("cast");
@@ -1493,8 +1490,8 @@ static int krr_mse_grad_impl(const float* x_s, int64_t n, const float* x_t, int6
     // sums.  The targets' chain is run too: their variance maps depend on
     // both sigmas (their image gradient is not returned).
     ProfScope ps("myrtle_self_bwd", s);
-    if (nk::launch_prepare_bwd(x_s, n, net, W_s, tl, xb_s, sums, at<double>(ws, p.bscratch), kPrepBwdBlocks, s) ||
-        nk::launch_prepare_bwd(x_t, m, net, W_t, tl, xb_t, sums, at<double>(ws, p.bscratch), kPrepBwdBlocks, s))
+    if (nk::launch_prepare_bwd(x_s, n, W_s, xb_s, x_t, m, W_t, xb_t, net, sums, at<double>(ws, p.bscratch),
+                               nk::prep_bwd_slots(n + m), s))
       return hip_fail("self adjoint");
   }
   if (dx_s && nk::launch_cast_grad(xb_s, dx_s, n * img, s)) return hip_fail("cast");

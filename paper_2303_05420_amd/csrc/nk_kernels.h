@@ -108,16 +108,14 @@ struct StageBwdArgs {
   double* sums;       // [0]: sigma_w2 * dL/dsigma_w2 terms, [1]: dL/dsigma_b2 terms
 };
 
-struct PrepBwdArgs {
-  const float* x;
-  int64_t n;
-  NetDesc net;
-  const double* W;    // w sums of these images [n][tablen]
+struct PrepRevArgs {
+  PrepArgs fwd;       // images, network and scratch (no tables)
+  const double* W1;   // w sums [image][tablen]
+  const double* W2;
   int tablen;
-  double* xbar;       // += image gradients [n][H W C]
+  double* xbar1;      // += image gradients [image][H W C]
+  double* xbar2;
   double* sums;
-  double* scratch;
-  int64_t scratch_per_img;
 };
 
 struct FcArgs {
@@ -138,6 +136,7 @@ struct FcArgs {
 constexpr int64_t kPrepSlots = 2048;
 int64_t prep_scratch_doubles(const NetDesc& net);
 int64_t prep_slots(int64_t n);
+int launch_prepare_stages(const PrepArgs& a, int64_t cnt, int stages, hipStream_t stream);  // stages 0 .. stages - 1
 int launch_prepare(const float* x1, int64_t n1, float2* tab1, const float* x2, int64_t n2, float2* tab2,
                    const NetDesc& net, double* scratch, int64_t slots, hipStream_t stream);
 size_t stage_lds_bytes(int N, int D, bool pool, bool seed);
@@ -164,9 +163,15 @@ int launch_stage_bwd(int N, const StageBwdArgs& a, bool seed, hipStream_t s);
 int launch_stage_bwd_32(const StageBwdArgs& a, bool seed, hipStream_t s);
 int launch_stage_bwd_16(const StageBwdArgs& a, bool seed, hipStream_t s);
 int launch_stage_bwd_small(int N, const StageBwdArgs& a, bool seed, hipStream_t s);
+// Reverse of the self recursions of both image sets (x2 NULL: one set).
+// Scratch: slots x prep_bwd_scratch_doubles(net) doubles, slots =
+// prep_bwd_slots(images) images at a time.
+constexpr int64_t kPrepBwdSlots = 512;
 int64_t prep_bwd_scratch_doubles(const NetDesc& net);
-int launch_prepare_bwd(const float* x, int64_t n, const NetDesc& net, const double* W, int tablen, double* xbar,
-                       double* sums, double* scratch, int64_t max_blocks, hipStream_t stream);
+int64_t prep_bwd_slots(int64_t n);
+int launch_prepare_bwd(const float* x1, int64_t n1, const double* W1, double* xbar1, const float* x2, int64_t n2,
+                       const double* W2, double* xbar2, const NetDesc& net, double* sums, double* scratch,
+                       int64_t slots, hipStream_t stream);
 int launch_cast_grad(const double* src, float* dst, int64_t n, hipStream_t s);
 int launch_finish_sigma(const double* sums, double sw2, float* dsigma, hipStream_t s);
 // out (cols x rows) = in^T (rows x cols), both dense; rows <= 65535 * 32.

@@ -1,0 +1,123 @@
+// Slices of the float64 self recursion, shared by its forward (prepare.hip)
+// and reverse (backward.hip): which displacement slices a stage needs, where
+// their pooled sums sit in an image's scratch, and the map on one of them.
+#pragma once
+#include "nk_kernels.h"
+
+namespace nk {
+
+__host__ __device__ inline int prep_R(const NetDesc& net, int s) { return (1 << (net.S - 1 - s)) - 1; }
+
+// Slices kept of radius R: delta = 0, and one of each pair (delta, -delta).
+__host__ __device__ inline int prep_half(int R) { return ((2 * R + 1) * (2 * R + 1) + 1) / 2; }
+
+// Workgroups that share a coarse slice (by the dy of its fine slices).  At
+// four stages the 25 coarse slices of the first pool fill the chip by
+// themselves and one workgroup takes all nine fine slices.
+__host__ __device__ inline int prep_parts(const NetDesc& net) { return net.S <= 3 ? 3 : 1; }
+
+// Threads of a workgroup that works on maps of m pixels.
+inline int prep_threads(int m) { return m < 64 ? 64 : (m > 1024 ? 1024 : m); }
+
+// Doubles before stage s's input slices in an image's scratch: the slices of
+// stages 1 .. s - 1, [part][slice][pixel] each.
+__host__ __device__ inline int64_t prep_off(const NetDesc& net, int s) {
+  int64_t t = 0;
+  for (int k = 1; k < s; ++k) t += (int64_t)prep_parts(net) * prep_half(prep_R(net, k)) * stage_res(net, k) * stage_res(net, k);
+  return t;
+}
+
+// Position of slice (dy, dx) among the kept ones; *neg where it is -delta
+// that is kept.
+__device__ inline int prep_slice(int dy, int dx, int R, bool* neg) {
+  *neg = dy < 0 || (dy == 0 && dx < 0);
+  if (*neg) {
+    dy = -dy;
+    dx = -dx;
+  }
+  return dy == 0 ? dx : 1 + R + (dy - 1) * (2 * R + 1) + dx + R;
+}
+
+__device__ inline double relu_map64(double s, double q1, double q2) {
+  double qq = q1 * q2;
+  if (!(qq > 0.0)) return 0.0;
+  double nrm = sqrt(qq);
+  double rho = s / nrm;
+  rho = rho > 1.0 ? 1.0 : (rho < -1.0 ? -1.0 : rho);
+  double th = acos(rho);
+  return nrm * (sqrt(fmax(1.0 - rho * rho, 0.0)) + (M_PI - th) * rho) * (0.5 / M_PI);
+}
+
+// Partial derivatives of the map above.
+__device__ inline void relu_partials64(double s, double q1, double q2, double* ds, double* dq1, double* dq2) {
+  const double qq = q1 * q2;
+  if (!(qq > 0.0)) {
+    *ds = *dq1 = *dq2 = 0.0;
+    return;
+  }
+  double rho = s / sqrt(qq);
+  rho = rho > 1.0 ? 1.0 : (rho < -1.0 ? -1.0 : rho);
+  const double th = acos(rho);
+  const double sn = sqrt(fmax(1.0 - rho * rho, 0.0));
+  *ds = (M_PI - th) * (0.5 / M_PI);
+  *dq1 = sn * sqrt(q2 / q1) * (0.25 / M_PI);
+  *dq2 = sn * sqrt(q1 / q2) * (0.25 / M_PI);
+}
+
+// 3x3 box sum with zero padding over an n x n map.
+__device__ inline double box9(const double* m, int n, int y, int x) {
+  double s = 0.0;
+  for (int dy = -1; dy <= 1; ++dy) {
+    int yy = y + dy;
+    if (yy < 0 || yy >= n) continue;
+    for (int dx = -1; dx <= 1; ++dx) {
+      int xx = x + dx;
+      if (xx < 0 || xx >= n) continue;
+      s += m[yy * n + xx];
+    }
+  }
+  return s;
+}
+
+// The stage's variance maps q[0 .. D) (LDS), from the diagonal of its input in w0.
+__device__ inline void prep_variances(const double* w0, double* q, int n, int lg, int D, double c, double b) {
+  const int n2 = n * n;
+  for (int l = 0; l < D; ++l) {
+    const double* src = l == 0 ? w0 : q + (l - 1) * n2;
+    const double f = l == 0 ? 1.0 : 0.5;
+    for (int i = threadIdx.x; i < n2; i += blockDim.x) q[l * n2 + i] = c * f * box9(src, n, i >> lg, i & (n - 1)) + b;
+    __syncthreads();
+  }
+}
+
+// Displacement (dy, dx) of kept slice h of radius R.
+__device__ inline void prep_delta(int h, int R, int* dy, int* dx) {
+  if (h <= R) {
+    *dy = 0;
+    *dx = h;
+  } else {
+    *dy = 1 + (h - 1 - R) / (2 * R + 1);
+    *dx = (h - 1 - R) % (2 * R + 1) - R;
+  }
+}
+
+// Stage input at (pixel i, pixel i + (dy, dx)) of one image, both in the image.
+__device__ inline double prep_input(const PrepArgs& a, const float* x, const double* in, int s, int n, int i, int dy,
+                                    int dx) {
+  const int C = a.net.C;
+  const int j = i + dy * n + dx;
+  if (s == 0) {
+    double v = 0.0;
+    for (int k = 0; k < C; ++k) v += (double)x[i * C + k] * (double)x[j * C + k];
+    return v / C;
+  }
+  const int R = prep_R(a.net, s), H = prep_half(R), parts = prep_parts(a.net);
+  bool neg;
+  const int h = prep_slice(dy, dx, R, &neg);
+  const double* p = in + (int64_t)h * n * n + (neg ? j : i);
+  double v = p[0];
+  for (int k = 1; k < parts; ++k) v += p[(int64_t)k * H * n * n];
+  return v;
+}
+
+}  // namespace nk

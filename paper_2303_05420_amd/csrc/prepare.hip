@@ -32,86 +32,13 @@
 // 32x32: a call on 2 and 60 images spent 2.28 ms here (two sets, one after
 // the other), one on 8192 images 18.7 ms.  Now it is 3 x 3 layers long in 15
 // workgroups per image and both sets share a launch: 0.14 ms and 13.1 ms.
-#include "nk_kernels.h"
+#include "prep.h"
 
 namespace nk {
-
-__host__ __device__ inline int prep_R(const NetDesc& net, int s) { return (1 << (net.S - 1 - s)) - 1; }
-
-// Slices kept of radius R: delta = 0, and one of each pair (delta, -delta).
-__host__ __device__ inline int prep_half(int R) { return ((2 * R + 1) * (2 * R + 1) + 1) / 2; }
-
-// Workgroups that share a coarse slice (by the dy of its fine slices).  At
-// four stages the 25 coarse slices of the first pool fill the chip by
-// themselves and one workgroup takes all nine fine slices.
-__host__ __device__ inline int prep_parts(const NetDesc& net) { return net.S <= 3 ? 3 : 1; }
-
-// Doubles before stage s's input slices in an image's scratch: the slices of
-// stages 1 .. s - 1, [part][slice][pixel] each.
-__host__ __device__ inline int64_t prep_off(const NetDesc& net, int s) {
-  int64_t t = 0;
-  for (int k = 1; k < s; ++k) t += (int64_t)prep_parts(net) * prep_half(prep_R(net, k)) * stage_res(net, k) * stage_res(net, k);
-  return t;
-}
 
 int64_t prep_scratch_doubles(const NetDesc& net) { return (prep_off(net, net.S) + 31) & ~31LL; }
 
 int64_t prep_slots(int64_t n) { return n < kPrepSlots ? n : kPrepSlots; }
-
-// Position of slice (dy, dx) among the kept ones; *neg where it is -delta
-// that is kept.
-__device__ inline int prep_slice(int dy, int dx, int R, bool* neg) {
-  *neg = dy < 0 || (dy == 0 && dx < 0);
-  if (*neg) {
-    dy = -dy;
-    dx = -dx;
-  }
-  return dy == 0 ? dx : 1 + R + (dy - 1) * (2 * R + 1) + dx + R;
-}
-
-__device__ inline double relu_map64(double s, double q1, double q2) {
-  double qq = q1 * q2;
-  if (!(qq > 0.0)) return 0.0;
-  double nrm = sqrt(qq);
-  double rho = s / nrm;
-  rho = rho > 1.0 ? 1.0 : (rho < -1.0 ? -1.0 : rho);
-  double th = acos(rho);
-  return nrm * (sqrt(fmax(1.0 - rho * rho, 0.0)) + (M_PI - th) * rho) * (0.5 / M_PI);
-}
-
-// 3x3 box sum with zero padding over an n x n map.
-__device__ inline double box9(const double* m, int n, int y, int x) {
-  double s = 0.0;
-  for (int dy = -1; dy <= 1; ++dy) {
-    int yy = y + dy;
-    if (yy < 0 || yy >= n) continue;
-    for (int dx = -1; dx <= 1; ++dx) {
-      int xx = x + dx;
-      if (xx < 0 || xx >= n) continue;
-      s += m[yy * n + xx];
-    }
-  }
-  return s;
-}
-
-// Stage input at (pixel i, pixel i + (dy, dx)) of one image, both in the image.
-__device__ inline double prep_input(const PrepArgs& a, const float* x, const double* in, int s, int n, int i, int dy,
-                                    int dx) {
-  const int C = a.net.C;
-  const int j = i + dy * n + dx;
-  if (s == 0) {
-    double v = 0.0;
-    for (int k = 0; k < C; ++k) v += (double)x[i * C + k] * (double)x[j * C + k];
-    return v / C;
-  }
-  const int R = prep_R(a.net, s), H = prep_half(R), parts = prep_parts(a.net);
-  bool neg;
-  const int h = prep_slice(dy, dx, R, &neg);
-  const double* p = in + (int64_t)h * n * n + (neg ? j : i);
-  double v = p[0];
-  for (int k = 1; k < parts; ++k) v += p[(int64_t)k * H * n * n];
-  return v;
-}
 
 // Stage s of every image of the launch: `units` workgroups per image, each
 // one (coarse slice, part); the first of them also writes the stage's tables.
@@ -134,13 +61,8 @@ __global__ __launch_bounds__(1024) void prepare_stage_kernel(const PrepArgs args
   // variance maps of the stage, from the diagonal of its input
   for (int i = tid; i < n2; i += nt) w0[i] = prep_input(args, x, in, s, n, i, 0, 0);
   __syncthreads();
-  for (int l = 0; l < D; ++l) {
-    const double* src = l == 0 ? w0 : q + (l - 1) * n2;
-    const double f = l == 0 ? 1.0 : 0.5;
-    for (int i = tid; i < n2; i += nt) q[l * n2 + i] = c * f * box9(src, n, i >> lg, i & (n - 1)) + b;
-    __syncthreads();
-  }
-  if (unit == 0) {
+  prep_variances(w0, q, n, lg, D, c, b);
+  if (unit == 0 && args.tab1) {
     float2* tab = (second ? args.tab2 + (gi - args.n1) * (int64_t)table_len(net)
                           : args.tab1 + gi * (int64_t)table_len(net)) + table_off(net, s);
     for (int l = 0; l < D; ++l) {
@@ -173,13 +95,7 @@ __global__ __launch_bounds__(1024) void prepare_stage_kernel(const PrepArgs args
   const int Rn = prep_R(net, s + 1), nn = n >> 1, H = prep_half(Rn), parts = prep_parts(net);
   const int h = unit / parts, part = unit - h * parts;
   int DY, DX;
-  if (h <= Rn) {
-    DY = 0;
-    DX = h;
-  } else {
-    DY = 1 + (h - 1 - Rn) / (2 * Rn + 1);
-    DX = (h - 1 - Rn) % (2 * Rn + 1) - Rn;
-  }
+  prep_delta(h, Rn, &DY, &DX);
   const int ey0 = parts == 3 ? part - 1 : -1, ey1 = parts == 3 ? part - 1 : 1;
   const int IY = tid >> (lg - 1), IX = tid & (nn - 1);  // this thread's coarse pixel (tid < nn * nn)
   const bool coarse = tid < nn * nn && IY + DY < nn && IX + DX >= 0 && IX + DX < nn;
@@ -217,9 +133,23 @@ __global__ __launch_bounds__(1024) void prepare_stage_kernel(const PrepArgs args
   if (tid < nn * nn) sc[prep_off(net, s + 1) + ((int64_t)part * H + h) * nn * nn + tid] = acc;
 }
 
+int launch_prepare_stages(const PrepArgs& a, int64_t cnt, int stages, hipStream_t stream) {
+  static std::atomic<size_t> seen[kMaxDevices];
+  const NetDesc& net = a.net;
+  for (int s = 0; s < stages; ++s) {
+    const int m = stage_res(net, s) * stage_res(net, s);
+    const int units = s + 1 < net.S ? prep_half(prep_R(net, s + 1)) * prep_parts(net) : 1;
+    const size_t lds = (size_t)(2 + net.depth[s]) * m * sizeof(double);
+    if (allow_dyn_lds((const void*)prepare_stage_kernel, lds, seen)) return -3;
+    hipLaunchKernelGGL(prepare_stage_kernel, dim3((unsigned)(cnt * units)), dim3((unsigned)prep_threads(m)), lds,
+                       stream, a, s, units);
+    if (hipGetLastError() != hipSuccess) return -3;
+  }
+  return 0;
+}
+
 int launch_prepare(const float* x1, int64_t n1, float2* tab1, const float* x2, int64_t n2, float2* tab2,
                    const NetDesc& net, double* scratch, int64_t slots, hipStream_t stream) {
-  static std::atomic<size_t> seen[kMaxDevices];
   PrepArgs a;
   a.x1 = x1;
   a.x2 = x2;
@@ -233,17 +163,7 @@ int launch_prepare(const float* x1, int64_t n1, float2* tab1, const float* x2, i
   const int64_t n = n1 + (x2 ? n2 : 0);
   for (int64_t at = 0; at < n; at += slots) {
     a.first = at;
-    const int64_t cnt = n - at < slots ? n - at : slots;
-    for (int s = 0; s < net.S; ++s) {
-      const int m = stage_res(net, s) * stage_res(net, s);
-      const int units = s + 1 < net.S ? prep_half(prep_R(net, s + 1)) * prep_parts(net) : 1;
-      const int threads = m < 64 ? 64 : (m > 1024 ? 1024 : m);
-      const size_t lds = (size_t)(2 + net.depth[s]) * m * sizeof(double);
-      if (allow_dyn_lds((const void*)prepare_stage_kernel, lds, seen)) return -3;
-      hipLaunchKernelGGL(prepare_stage_kernel, dim3((unsigned)(cnt * units)), dim3((unsigned)threads), lds, stream, a,
-                         s, units);
-      if (hipGetLastError() != hipSuccess) return -3;
-    }
+    if (launch_prepare_stages(a, n - at < slots ? n - at : slots, net.S, stream)) return -3;
   }
   return 0;
 }
