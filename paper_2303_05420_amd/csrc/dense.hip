@@ -4,102 +4,212 @@
 // GEMM with float32 or float64 operands and float64 accumulation (optionally
 // compensated), symmetric-matrix loads with a diagonal shift, identity
 // fills, row updates and casts.
-#include "nk_kernels.h"
+#include "mfma64.h"
 
 namespace nk {
 
-constexpr int DN_T = 32;  // output tile side; 256 threads hold 4 outputs each
-
-// C (M x N, double, ldc) = beta C + alpha op(A) B.
-//   op(A) = A (M x K, lda) or, with TA_T, A^T where A is K x M (lda);
-//   B is K x N (ldb), row-major.
-// COMP: each output's sum carries its rounding error (exact product errors
-// by FMA, TwoSum for the additions) and is rounded once -- for sums whose
-// result is later subtracted from a nearly equal quantity.
-template <typename TA, typename TB, bool TA_T, bool COMP>
-__global__ __launch_bounds__(256) void dn_gemm_kernel(const TA* __restrict__ A, int64_t lda,
-                                                      const TB* __restrict__ B, int64_t ldb, double* __restrict__ Cm,
-                                                      int64_t ldc, int64_t M, int64_t N, int64_t K, double alpha,
-                                                      double beta) {
-#pragma clang fp contract(off)
-  __shared__ double sA[DN_T][DN_T + 1];  // sA[row of C][k]
-  __shared__ double sB[DN_T][DN_T + 1];  // sB[k][col of C]
-  const int64_t r0 = (int64_t)blockIdx.y * DN_T, c0 = (int64_t)blockIdx.x * DN_T;
-  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
-  double hi[4] = {0.0, 0.0, 0.0, 0.0}, lo[4] = {0.0, 0.0, 0.0, 0.0};
-  for (int64_t k0 = 0; k0 < K; k0 += DN_T) {
-    for (int y = ty; y < DN_T; y += 8) {
-      // A tile: rows r0 + y of op(A), columns k0 + tx
-      const int64_t r = r0 + y, k = k0 + tx;
-      double av = 0.0;
-      if (r < M && k < K) av = TA_T ? (double)A[k * lda + r] : (double)A[r * lda + k];
-      sA[y][tx] = av;
-      const int64_t kb = k0 + y, cb = c0 + tx;
-      sB[y][tx] = (kb < K && cb < N) ? (double)B[kb * ldb + cb] : 0.0;
-    }
-    __syncthreads();
-    for (int k = 0; k < DN_T; ++k) {
-      const double bv = sB[k][tx];
+// C (M x N, TO, ldc) = beta C + alpha op(A) op(B), plus shift I.
+//   op(A) = A (M x K, lda) or, with A_T, A^T where A is K x M (lda); op(B) = B
+//   (K x N, ldb) or, with B_T, B^T where B is N x K (ldb); all row-major.
+// A workgroup owns a square tile of MB x MB blocks of 16 x 16 on the float64
+// matrix cores; its W waves take every W-th chunk of 16 k each and meet in
+// LDS at the end, in a fixed order, so a tile's sum is spread over a CU
+// however few tiles there are.  Operands come straight from the caches (a
+// lane's four consecutive k of a row, or 16 lanes' consecutive columns), the
+// next chunk's while the current one runs: a chunk is 4 MB^2 instructions of
+// 64 cycles for 8 MB loads.
+// COMP: for sums whose result is later subtracted from a nearly equal
+// quantity.  A chunk starts from zero and its sum is added to the running one
+// with TwoSum, the rounding errors carried and added at the end: what is left
+// is the rounding inside chunks, 16 terms of a sum of K, and one rounding of
+// the result.  (A chain of compensated single products on the vector unit, 4
+// outputs per thread: 3.8 ms for the 1000 x 1000 x 12000 product of a
+// Nystrom solve, now 0.72 ms.)
+// sym: op(B) = op(A)^T; the tiles on and below the diagonal are formed and
+// mirrored.
+template <typename TA, typename TB, typename TO, bool A_T, bool B_T, bool COMP, int MB, int W>
+__global__ __launch_bounds__(64 * W) void dn_gemm_kernel(const TA* __restrict__ A, int64_t lda,
+                                                         const TB* __restrict__ B, int64_t ldb, TO* __restrict__ Cm,
+                                                         int64_t ldc, int64_t M, int64_t N, int64_t K, double alpha,
+                                                         double beta, double shift, int sym, int* __restrict__ info,
+                                                         unsigned ntc) {
+  constexpr int T = 16 * MB, E = T * T;
+  __shared__ double red[(COMP ? 2 : 1) * W * E];
+  const unsigned tr = blockIdx.x / ntc, tc = blockIdx.x - tr * ntc;  // tile row and column
+  if (info && blockIdx.x == 0 && threadIdx.x == 0) info[0] = 0;
+  if (sym && tc > tr) return;
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, i = lane & 15, g = lane >> 4;
+  const int64_t r0 = (int64_t)tr * T, c0 = (int64_t)tc * T;
+  int64_t ra[MB], cb[MB];  // this lane's rows of op(A) and columns of op(B) (past the end: the last one, not stored)
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const double av = sA[ty + 8 * q][k];
-        if (COMP) {
-          const double p = av * bv;
-          const double pe = __builtin_fma(av, bv, -p);
-          const double s = hi[q] + p;
-          const double bb = s - hi[q];
-          lo[q] += ((hi[q] - (s - bb)) + (p - bb)) + pe;
-          hi[q] = s;
+  for (int x = 0; x < MB; ++x) {
+    ra[x] = r0 + 16 * x + i < M ? r0 + 16 * x + i : M - 1;
+    cb[x] = c0 + 16 * x + i < N ? c0 + 16 * x + i : N - 1;
+  }
+  TA av[MB][4];
+  TB bv[MB][4];
+  auto fetch = [&](int64_t k0) {
+    const int64_t k = k0 + 4 * g;
+    if (k0 + 16 <= K) {
+#pragma unroll
+      for (int x = 0; x < MB; ++x) {
+        if constexpr (A_T) {
+#pragma unroll
+          for (int t = 0; t < 4; ++t) av[x][t] = A[(k + t) * lda + ra[x]];
         } else {
-          hi[q] = __builtin_fma(av, bv, hi[q]);
+          load4(A + ra[x] * lda + k, av[x]);
+        }
+        if constexpr (B_T) {
+          load4(B + cb[x] * ldb + k, bv[x]);
+        } else {
+#pragma unroll
+          for (int t = 0; t < 4; ++t) bv[x][t] = B[(k + t) * ldb + cb[x]];
         }
       }
+    } else {
+#pragma unroll
+      for (int x = 0; x < MB; ++x)
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+          const bool in = k + t < K;
+          av[x][t] = in ? (A_T ? A[(k + t) * lda + ra[x]] : A[ra[x] * lda + k + t]) : (TA)0;
+          bv[x][t] = in ? (B_T ? B[cb[x] * ldb + k + t] : B[(k + t) * ldb + cb[x]]) : (TB)0;
+        }
     }
-    __syncthreads();
+  };
+  d4 hi[MB][MB], lo[MB][MB];
+#pragma unroll
+  for (int x = 0; x < MB; ++x)
+#pragma unroll
+    for (int y = 0; y < MB; ++y) hi[x][y] = lo[x][y] = d4{0.0, 0.0, 0.0, 0.0};
+  int64_t k0 = 16 * w;
+  if (k0 < K) fetch(k0);
+  for (; k0 < K; k0 += 16 * W) {
+    double a[MB][4], b[MB][4];
+#pragma unroll
+    for (int x = 0; x < MB; ++x)
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        a[x][t] = (double)av[x][t];
+        b[x][t] = (double)bv[x][t];
+      }
+    if (k0 + 16 * W < K) fetch(k0 + 16 * W);
+    d4 p[MB][MB];
+#pragma unroll
+    for (int x = 0; x < MB; ++x)
+#pragma unroll
+      for (int y = 0; y < MB; ++y) p[x][y] = COMP ? d4{0.0, 0.0, 0.0, 0.0} : hi[x][y];
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+#pragma unroll
+      for (int x = 0; x < MB; ++x)
+#pragma unroll
+        for (int y = 0; y < MB; ++y) p[x][y] = mfma64(a[x][t], b[y][t], p[x][y]);
+#pragma unroll
+    for (int x = 0; x < MB; ++x)
+#pragma unroll
+      for (int y = 0; y < MB; ++y) {
+        if (COMP) {
+          const d4 s = hi[x][y] + p[x][y];
+          const d4 bb = s - hi[x][y];
+          lo[x][y] += (hi[x][y] - (s - bb)) + (p[x][y] - bb);
+          hi[x][y] = s;
+        } else {
+          hi[x][y] = p[x][y];
+        }
+      }
   }
 #pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int64_t r = r0 + ty + 8 * q, c = c0 + tx;
-    if (r < M && c < N) {
-      const double v = alpha * (hi[q] + lo[q]);
-      double* o = Cm + r * ldc + c;
-      *o = beta == 0.0 ? v : __builtin_fma(beta, *o, v);
+  for (int x = 0; x < MB; ++x)
+#pragma unroll
+    for (int y = 0; y < MB; ++y)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int e = (16 * x + 4 * v + g) * T + 16 * y + i;
+        red[w * E + e] = hi[x][y][v];
+        if (COMP) red[(W + w) * E + e] = lo[x][y][v];
+      }
+  __syncthreads();
+  for (int e = tid; e < E; e += 64 * W) {
+    double s = red[e], l = COMP ? red[W * E + e] : 0.0;
+    for (int q = 1; q < W; ++q) {
+      const double v = red[q * E + e];
+      if (COMP) {
+        const double u = s + v, bb = u - s;
+        l += (s - (u - bb)) + (v - bb) + red[(W + q) * E + e];
+        s = u;
+      } else {
+        s += v;
+      }
     }
+    const int64_t r = r0 + e / T, c = c0 + e % T;
+    if (r >= M || c >= N || (sym && c > r)) continue;
+    if (COMP && r == c && shift != 0.0) {
+      const double u = s + shift, bb = u - s;
+      l += (s - (u - bb)) + (shift - bb);
+      s = u;
+    }
+    const double v = alpha * (s + l);
+    TO* o = Cm + r * ldc + c;
+    const double out = beta == 0.0 ? v : __builtin_fma(beta, (double)*o, v);
+    *o = (TO)out;
+    if (sym && c < r) Cm[c * ldc + r] = (TO)out;
   }
 }
 
-template <typename TA, typename TB, bool TA_T, bool COMP>
-static int dn_gemm_t(const TA* A, int64_t lda, const TB* B, int64_t ldb, double* C, int64_t ldc, int64_t M,
-                     int64_t N, int64_t K, double alpha, double beta, hipStream_t s) {
+// Tile by size: 32 x 32 (half the operand traffic) where that still gives a
+// tile to every CU, else 16 x 16 with up to 16 waves on a long sum.
+template <typename TA, typename TB, typename TO, bool A_T, bool B_T, bool COMP>
+static int dn_gemm_t(const TA* A, int64_t lda, const TB* B, int64_t ldb, TO* C, int64_t ldc, int64_t M, int64_t N,
+                     int64_t K, double alpha, double beta, hipStream_t s, double shift = 0.0, bool sym = false,
+                     int* info = nullptr) {
   if (M <= 0 || N <= 0) return 0;
-  const dim3 grid((unsigned)((N + DN_T - 1) / DN_T), (unsigned)((M + DN_T - 1) / DN_T));
-  hipLaunchKernelGGL((dn_gemm_kernel<TA, TB, TA_T, COMP>), grid, dim3(256), 0, s, A, lda, B, ldb, C, ldc, M, N, K,
-                     alpha, beta);
+  const int64_t m32 = (M + 31) / 32, n32 = (N + 31) / 32, m16 = (M + 15) / 16, n16 = (N + 15) / 16;
+  const int sy = sym ? 1 : 0;
+  const bool big = N > 16 && (sym ? m32 * (m32 + 1) / 2 : m32 * n32) >= 256;
+  const unsigned nt = (unsigned)(big ? n32 : n16);
+  const dim3 grid((unsigned)((big ? m32 : m16) * nt));
+  if (big)
+    hipLaunchKernelGGL((dn_gemm_kernel<TA, TB, TO, A_T, B_T, COMP, 2, 4>), grid, dim3(256), 0, s, A, lda, B, ldb, C, ldc,
+                       M, N, K, alpha, beta, shift, sy, info, nt);
+  else if (K > 256)
+    hipLaunchKernelGGL((dn_gemm_kernel<TA, TB, TO, A_T, B_T, COMP, 1, 16>), grid, dim3(1024), 0, s, A, lda, B, ldb, C,
+                       ldc, M, N, K, alpha, beta, shift, sy, info, nt);
+  else
+    hipLaunchKernelGGL((dn_gemm_kernel<TA, TB, TO, A_T, B_T, COMP, 1, 4>), grid, dim3(256), 0, s, A, lda, B, ldb, C, ldc,
+                       M, N, K, alpha, beta, shift, sy, info, nt);
   return hipGetLastError() == hipSuccess ? 0 : -3;
 }
 
 int dn_gemm_ff(const float* A, int64_t lda, bool a_t, const float* B, int64_t ldb, double* C, int64_t ldc, int64_t M,
                int64_t N, int64_t K, double alpha, double beta, bool comp, hipStream_t s) {
-  if (a_t) return comp ? dn_gemm_t<float, float, true, true>(A, lda, B, ldb, C, ldc, M, N, K, alpha, beta, s)
-                       : dn_gemm_t<float, float, true, false>(A, lda, B, ldb, C, ldc, M, N, K, alpha, beta, s);
-  return comp ? dn_gemm_t<float, float, false, true>(A, lda, B, ldb, C, ldc, M, N, K, alpha, beta, s)
-              : dn_gemm_t<float, float, false, false>(A, lda, B, ldb, C, ldc, M, N, K, alpha, beta, s);
+  if (!a_t || !comp) return -1;  // (only the compensated A^T B is used)
+  const bool sym = A == B && lda == ldb && M == N && beta == 0.0;
+  return dn_gemm_t<float, float, double, true, false, true>(A, lda, B, ldb, C, ldc, M, N, K, alpha, beta, s, 0.0, sym);
 }
 
 int dn_gemm_fd(const float* A, int64_t lda, bool a_t, const double* B, int64_t ldb, double* C, int64_t ldc,
                int64_t M, int64_t N, int64_t K, double alpha, double beta, bool comp, hipStream_t s) {
-  if (a_t) return comp ? dn_gemm_t<float, double, true, true>(A, lda, B, ldb, C, ldc, M, N, K, alpha, beta, s)
-                       : dn_gemm_t<float, double, true, false>(A, lda, B, ldb, C, ldc, M, N, K, alpha, beta, s);
-  return comp ? dn_gemm_t<float, double, false, true>(A, lda, B, ldb, C, ldc, M, N, K, alpha, beta, s)
-              : dn_gemm_t<float, double, false, false>(A, lda, B, ldb, C, ldc, M, N, K, alpha, beta, s);
+  if (a_t) {
+    if (comp) return -1;
+    return dn_gemm_t<float, double, double, true, false, false>(A, lda, B, ldb, C, ldc, M, N, K, alpha, beta, s);
+  }
+  return comp ? dn_gemm_t<float, double, double, false, false, true>(A, lda, B, ldb, C, ldc, M, N, K, alpha, beta, s)
+              : dn_gemm_t<float, double, double, false, false, false>(A, lda, B, ldb, C, ldc, M, N, K, alpha, beta, s);
 }
 
-int dn_gemm_dd(const double* A, int64_t lda, bool a_t, const double* B, int64_t ldb, double* C, int64_t ldc,
-               int64_t M, int64_t N, int64_t K, double alpha, double beta, bool comp, hipStream_t s) {
-  if (a_t) return comp ? dn_gemm_t<double, double, true, true>(A, lda, B, ldb, C, ldc, M, N, K, alpha, beta, s)
-                       : dn_gemm_t<double, double, true, false>(A, lda, B, ldb, C, ldc, M, N, K, alpha, beta, s);
-  return comp ? dn_gemm_t<double, double, false, true>(A, lda, B, ldb, C, ldc, M, N, K, alpha, beta, s)
-              : dn_gemm_t<double, double, false, false>(A, lda, B, ldb, C, ldc, M, N, K, alpha, beta, s);
+int dn_gemm_dd(const double* A, int64_t lda, const double* B, int64_t ldb, double* C, int64_t ldc, int64_t M,
+               int64_t N, int64_t K, double alpha, double beta, hipStream_t s) {
+  return dn_gemm_t<double, double, double, false, false, false>(A, lda, B, ldb, C, ldc, M, N, K, alpha, beta, s);
+}
+
+int dn_gemm_fdf(const float* A, int64_t lda, const double* B, int64_t ldb, float* C, int64_t ldc, int64_t M,
+                int64_t N, int64_t K, hipStream_t s) {
+  return dn_gemm_t<float, double, float, false, false, false>(A, lda, B, ldb, C, ldc, M, N, K, 1.0, 0.0, s);
+}
+
+int dn_ltl(const double* L, int64_t n, int64_t r, double lam, double* M, int* info, hipStream_t s) {
+  return dn_gemm_t<double, double, double, false, true, true>(L, n, L, n, M, r, r, r, n, 1.0, 0.0, s, lam, true, info);
 }
 
 // D (n x n, double, dense) = S (float, lds) + shift I; clears info[0] when given.

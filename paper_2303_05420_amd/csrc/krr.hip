@@ -5,11 +5,11 @@
 //   lambda = ridge_rel mean(diag K_train),  A = K_train + lambda I = L L^T,
 //   alpha = L^{-T} L^{-1} Y,  pred = K_test alpha.
 //
-// Blocked right-looking Cholesky (block NB): factor the diagonal block in LDS,
-// solve the panel below it, update the trailing lower triangle; then copy L^T
-// into the strict upper triangle.  Substitutions are blocked the same way:
-// panel triangles one thread per right-hand side, the rest by float64 GEMM.
-#include "nk_kernels.h"
+// Blocked right-looking Cholesky in panels of 64 columns, two launches each:
+// the panel (its diagonal block and the rows below it) and the trailing
+// update on the float64 matrix cores.  Right-hand sides ride along in the
+// same launches (forward substitution); the backward one is a launch per panel.
+#include "mfma64.h"
 
 namespace nk {
 
@@ -42,129 +42,373 @@ __global__ __launch_bounds__(256) void krr_build_kernel(const float* __restrict_
   A[e] = v;
 }
 
-// Cholesky of the nb x nb diagonal block at (k, k), in LDS.
-__global__ __launch_bounds__(256) void chol_diag_kernel(double* __restrict__ A, int64_t n, int64_t k, int nb,
-                                                        int* __restrict__ info) {
-  __shared__ double L[CH_NB][CH_NB + 1];
-  const int tid = threadIdx.x;
-  for (int e = tid; e < nb * nb; e += 256) {
-    const int i = e / nb, j = e - i * nb;
-    L[i][j] = A[(k + i) * n + k + j];
-  }
-  __syncthreads();
-  for (int j = 0; j < nb; ++j) {
-    if (tid == 0) {
-      const double d = L[j][j];
-      if (!(d > 0.0)) {
-        info[0] = 1;
-        L[j][j] = 1.0;
-      } else {
-        L[j][j] = sqrt(d);
+// The factored 64 x 64 diagonal block of a panel in the matrix: L in its
+// lower triangle, and in the strict upper triangle of each 16 x 16 block on
+// its diagonal the strictly lower part of that block's inverse, transposed.
+// With the inverses a triangular solve is a chain of 16 x 16 products for the
+// matrix cores; 16 x 16 is small enough that the inverse adds no error that
+// shows beside the substitution's own.  In LDS: L in T, the whole inverses
+// in V.
+constexpr int CH_LD = CH_NB + 1, CH_LV = 17;
+
+struct CholLds {
+  double T[CH_NB * CH_LD];
+  double V[4 * 16 * CH_LV];
+};
+
+// X_b of one 16-column strip for the four 16-row blocks of a panel: X = L^{-1} Y
+// (BACK: L^{-T} Y), y[b] in the matrix cores' result layout, in place.
+template <bool BACK>
+__device__ __forceinline__ void chol_chain(const CholLds& m, d4 (&y)[4]) {
+  const int i = threadIdx.x & 15, g = (threadIdx.x >> 4) & 3;
+#pragma unroll
+  for (int s = 0; s < 4; ++s) {
+    const int b = BACK ? 3 - s : s;
+    d4 v = y[b];
+#pragma unroll
+    for (int u = 0; u < s; ++u) {
+      const int a = BACK ? 3 - u : u;
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        const int k = 4 * t + g;
+        v = mfma64(BACK ? -m.T[(16 * a + k) * CH_LD + 16 * b + i] : -m.T[(16 * b + i) * CH_LD + 16 * a + k], y[a][t],
+                   v);
       }
     }
-    __syncthreads();
-    const double djj = L[j][j];
-    for (int i = j + 1 + tid; i < nb; i += 256) L[i][j] /= djj;
-    __syncthreads();
-    // trailing update of the block (lower part)
-    for (int e = tid; e < (nb - j - 1) * (nb - j - 1); e += 256) {
-      const int i = j + 1 + e / (nb - j - 1), c = j + 1 + e % (nb - j - 1);
-      if (c <= i) L[i][c] -= L[i][j] * L[c][j];
+    d4 x = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      const int k = 4 * t + g;
+      x = mfma64(m.V[16 * b * CH_LV + (BACK ? k * CH_LV + i : i * CH_LV + k)], v[t], x);
     }
-    __syncthreads();
-  }
-  for (int e = tid; e < nb * nb; e += 256) {
-    const int i = e / nb, j = e - i * nb;
-    if (j <= i) A[(k + i) * n + k + j] = L[i][j];
+    y[b] = x;
   }
 }
 
-// Panel: rows i >= k + nb: A[i, k:k+nb] <- A[i, k:k+nb] L_kk^{-T}; one thread per row.
-__global__ __launch_bounds__(256) void chol_trsm_kernel(double* __restrict__ A, int64_t n, int64_t k, int nb) {
-  __shared__ double L[CH_NB][CH_NB + 1];
-  for (int e = threadIdx.x; e < nb * nb; e += 256) {
-    const int i = e / nb, j = e - i * nb;
-    L[i][j] = j <= i ? A[(k + i) * n + k + j] : 0.0;
+// A panel's strip of right-hand sides: rows k + 16 b + 4 t + g, column col.
+__device__ __forceinline__ void chol_load_strip(const double* Z, int64_t n, int64_t k, int64_t c, int64_t col, int g,
+                                                d4 (&y)[4]) {
+#pragma unroll
+  for (int b = 0; b < 4; ++b)
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      const int64_t r = k + 16 * b + 4 * t + g;
+      y[b][t] = r < n ? Z[r * c + col] : 0.0;
+    }
+}
+__device__ __forceinline__ void chol_store_strip(double* Z, int64_t n, int64_t k, int64_t c, int64_t col, int g,
+                                                 const d4 (&y)[4]) {
+  if (col >= c) return;
+#pragma unroll
+  for (int b = 0; b < 4; ++b)
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      const int64_t r = k + 16 * b + 4 * t + g;
+      if (r < n) Z[r * c + col] = y[b][t];
+    }
+}
+
+// Panel [k, k + nb): every workgroup factors the diagonal block for itself
+// (a launch of its own for it would add to the chain that bounds the solve:
+// n columns, one after the other).  The first nrow workgroups solve 64 of the
+// rows below each, 16 per wave: A[i, panel] <- A[i, panel] L^{-T}; the others
+// 64 right-hand sides each: Z[panel] <- L^{-1} Z[panel].  Workgroup 0 stores
+// the factor: into place if it is the only one, else beside it, at columns
+// k + 64 .. k + 127 of the unused upper triangle, since the others may still
+// be reading the block (chol_update_kernel moves it).
+// The columns are factored 16 at a time by one wave, a lane per row of the
+// block, pivots and multipliers by lane reads: no barrier inside.  With a
+// barrier per column (block in LDS, one workgroup, its own launch) and a
+// thread per row below: 82 + 43 us a panel at n = 2500, 23 us for
+// both.
+__global__ __launch_bounds__(256) void chol_panel_kernel(double* __restrict__ A, int64_t n, int64_t k, int nb,
+                                                         int* __restrict__ info, unsigned nrow,
+                                                         double* __restrict__ Z, int64_t c) {
+  __shared__ CholLds m;
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, i = lane & 15, g = lane >> 4;
+  const int64_t rest = n - k - nb;
+  const bool rhs = blockIdx.x >= nrow;
+  // this wave's 16 rows below or right-hand sides, and the diagonal block
+  // (all requested before the first is used)
+  const int64_t row = k + nb + (int64_t)blockIdx.x * CH_NB + 16 * w + i;
+  const int64_t col = (int64_t)(blockIdx.x - nrow) * 64 + 16 * w + i;
+  double* prow = A + (row < n ? row : n - 1) * n + k;
+  d4 y[4];
+  if (rhs) {
+    chol_load_strip(Z, n, k, c, col < c ? col : c - 1, g, y);
+  } else if (rest > 0) {
+#pragma unroll
+    for (int b = 0; b < 4; ++b)
+#pragma unroll
+      for (int t = 0; t < 4; ++t) y[b][t] = prow[16 * b + 4 * t + g];
+  }
+  {
+    double v[16];
+#pragma unroll
+    for (int q = 0; q < 16; ++q) {
+      const int r = 4 * q + w;
+      v[q] = (r < nb && lane <= r) ? A[(k + r) * n + k + lane] : (r == lane ? 1.0 : 0.0);
+    }
+#pragma unroll
+    for (int q = 0; q < 16; ++q) m.T[(4 * q + w) * CH_LD + lane] = v[q];
   }
   __syncthreads();
-  const int64_t i = k + nb + (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= n) return;
-  // (loops fully unrolled so that x stays in registers)
-  double x[CH_NB];
-  double* row = A + i * n + k;
+#pragma unroll 1
+  for (int jb = 0; jb < 4; ++jb) {
+    if (w == 0) {
+      double a[16];
 #pragma unroll
-  for (int j = 0; j < CH_NB; ++j) x[j] = j < nb ? row[j] : 0.0;
+      for (int j = 0; j < 16; ++j) a[j] = m.T[lane * CH_LD + 16 * jb + j];
+      bool bad = false;
 #pragma unroll
-  for (int j = 0; j < CH_NB; ++j) {
-    if (j < nb) {
-      double v = x[j];
+      for (int j = 0; j < 16; ++j) {
+        double d = lane_value(a[j], 16 * jb + j);
+        if (!(d > 0.0)) {
+          bad = true;
+          d = 1.0;
+        }
+        // 1 / sqrt(d) by two Newton steps, sqrt(d) with its residual
+        double r = __builtin_amdgcn_rsq(d);
+        r = fma(0.5 * r, fma(-d * r, r, 1.0), r);
+        r = fma(0.5 * r, fma(-d * r, r, 1.0), r);
+        double q = d * r;
+        q = fma(fma(-q, q, d), 0.5 * r, q);
+        const double l = lane == 16 * jb + j ? q : a[j] * r;
 #pragma unroll
-      for (int t = 0; t < j; ++t) v = fma(-x[t], L[j][t], v);
-      x[j] = v / L[j][j];
+        for (int e = j + 1; e < 16; ++e) a[e] = fma(-l, lane_value(l, 16 * jb + e), a[e]);
+        a[j] = l;
+      }
+      if (bad && lane == 0) info[0] = 1;
+#pragma unroll
+      for (int j = 0; j < 16; ++j) m.T[lane * CH_LD + 16 * jb + j] = a[j];
+    }
+    __syncthreads();
+    // the blocks right of it: T[rb][cb] -= L[rb][jb] L[cb][jb]^T, jb < cb <= rb
+    int tile = 0;
+    for (int rb = jb + 1; rb < 4; ++rb)
+      for (int cb = jb + 1; cb <= rb; ++cb, ++tile) {
+        if ((tile & 3) != w) continue;
+        d4 acc;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) acc[v] = m.T[(16 * rb + 4 * v + g) * CH_LD + 16 * cb + i];
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+          acc = mfma64(-m.T[(16 * rb + i) * CH_LD + 16 * jb + 4 * t + g],
+                       m.T[(16 * cb + i) * CH_LD + 16 * jb + 4 * t + g], acc);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) m.T[(16 * rb + 4 * v + g) * CH_LD + 16 * cb + i] = acc[v];
+      }
+    __syncthreads();
+  }
+  // inverse of the diagonal block of wave w: lane i forms its column i
+  if (g == 0) {
+    const double* L = m.T + 16 * w * CH_LD + 16 * w;
+    const double ri = 1.0 / L[i * CH_LD + i];
+    double x[16];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      double v = r == i ? 1.0 : 0.0;
+#pragma unroll
+      for (int e = 0; e < r; ++e) v = fma(-L[r * CH_LD + e], x[e], v);
+      x[r] = v * lane_value(ri, r);
+    }
+#pragma unroll
+    for (int r = 0; r < 16; ++r) m.V[(16 * w + r) * CH_LV + i] = x[r];  // (0 above the diagonal)
+  }
+  __syncthreads();
+  if (blockIdx.x == 0) {
+    const int64_t off = rest > CH_NB ? CH_NB : 0;
+#pragma unroll
+    for (int q = 0; q < 16; ++q) {
+      const int r = 4 * q + w;
+      const bool inv = lane > r && (lane >> 4) == (r >> 4);
+      const double v = inv ? m.V[lane * CH_LV + (r & 15)] : m.T[r * CH_LD + lane];
+      if (r < nb && lane < nb) A[(k + r) * n + k + off + lane] = v;
+    }
+  }
+  if (rhs || rest > 0) {
+    chol_chain<false>(m, y);
+    if (rhs) {
+      chol_store_strip(Z, n, k, c, col, g, y);
+    } else if (row < n) {
+#pragma unroll
+      for (int b = 0; b < 4; ++b)
+#pragma unroll
+        for (int t = 0; t < 4; ++t) prow[16 * b + 4 * t + g] = y[b][t];
+    }
+  }
+}
+
+// Trailing update for the 64-column panel at k (base = k + 64): of the matrix,
+// A[i][j] -= sum_t A[i][k + t] A[j][k + t], base <= j <= i < n, one 64 x 64 tile
+// of the lower triangle per workgroup and a 32 x 32 quadrant per wave
+// (blocks [0, ntiles)); of the right-hand sides, Z[i] -= sum_t A[i][k + t]
+// Z[k + t], 64 rows of one strip per workgroup (the last nrhs blocks); and one
+// block moves the panel's factor into place (move).  All operands of a tile
+// are requested at once, straight from the caches: at the sizes solved here a
+// launch is a few tiles per CU, bound by one round of latency (45 -> 12 us
+// a panel at n = 2500 against dot products on the vector unit from LDS), and by
+// HBM traffic of the tile itself beyond.
+__global__ __launch_bounds__(256) void chol_update_kernel(double* __restrict__ A, int64_t n, int64_t k,
+                                                          unsigned ntiles, int move, double* __restrict__ Z,
+                                                          int64_t c, unsigned nbk) {
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, i = lane & 15, g = lane >> 4;
+  const int64_t base = k + CH_NB;
+  if (blockIdx.x >= ntiles) {
+    if (move && blockIdx.x == ntiles) {
+      double v[16];
+#pragma unroll
+      for (int q = 0; q < 16; ++q) v[q] = A[(k + 4 * q + w) * n + base + lane];
+#pragma unroll
+      for (int q = 0; q < 16; ++q) A[(k + 4 * q + w) * n + k + lane] = v[q];
+      return;
+    }
+    const unsigned e = blockIdx.x - ntiles - move;
+    const int64_t j0 = (int64_t)(e / nbk) * 16, r0 = base + (int64_t)(e % nbk) * 64 + 16 * w;
+    const int64_t col = j0 + i < c ? j0 + i : c - 1;
+    const double* pa = A + (r0 + i < n ? r0 + i : n - 1) * n + k + 4 * g;
+    double a[4][4], b[4][4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      load4(pa + 16 * q, a[q]);
+#pragma unroll
+      for (int t = 0; t < 4; ++t) b[q][t] = Z[(k + 16 * q + 4 * g + t) * c + col];
+    }
+    d4 acc;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) acc[v] = Z[(r0 + 4 * v + g < n ? r0 + 4 * v + g : n - 1) * c + col];
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int t = 0; t < 4; ++t) acc = mfma64(-a[q][t], b[q][t], acc);
+    if (j0 + i < c) {
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+        if (r0 + 4 * v + g < n) Z[(r0 + 4 * v + g) * c + col] = acc[v];
+    }
+    return;
+  }
+  int64_t bi = (int64_t)((sqrtf(8.0f * (float)blockIdx.x + 1.0f) - 1.0f) * 0.5f);
+  while (bi * (bi + 1) / 2 > (int64_t)blockIdx.x) --bi;
+  while ((bi + 1) * (bi + 2) / 2 <= (int64_t)blockIdx.x) ++bi;
+  const int64_t bj = (int64_t)blockIdx.x - bi * (bi + 1) / 2;
+  const int64_t r0 = base + 64 * bi + 32 * (w >> 1), c0 = base + 64 * bj + 32 * (w & 1);
+  if (c0 > r0 || r0 >= n) return;  // the quadrant above the diagonal, or past the end
+  double av[2][4][4], bv[2][4][4];
+  d4 acc[2][2];
+#pragma unroll
+  for (int x = 0; x < 2; ++x) {
+    const int64_t ra = r0 + 16 * x + i, rb = c0 + 16 * x + i;
+    const double* pa = A + (ra < n ? ra : n - 1) * n + k + 4 * g;
+    const double* pb = A + (rb < n ? rb : n - 1) * n + k + 4 * g;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      load4(pa + 16 * q, av[x][q]);
+      load4(pb + 16 * q, bv[x][q]);
     }
   }
 #pragma unroll
-  for (int j = 0; j < CH_NB; ++j)
-    if (j < nb) row[j] = x[j];
+  for (int x = 0; x < 2; ++x)
+#pragma unroll
+    for (int y = 0; y < 2; ++y) {
+      const int64_t cc = c0 + 16 * y + i;
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int64_t r = r0 + 16 * x + 4 * v + g;
+        acc[x][y][v] = A[(r < n ? r : n - 1) * n + (cc < n ? cc : n - 1)];
+      }
+    }
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+#pragma unroll
+      for (int x = 0; x < 2; ++x)
+#pragma unroll
+        for (int y = 0; y < 2; ++y) acc[x][y] = mfma64(-av[x][q][t], bv[y][q][t], acc[x][y]);
+#pragma unroll
+  for (int x = 0; x < 2; ++x)
+#pragma unroll
+    for (int y = 0; y < 2; ++y) {
+      const int64_t cc = c0 + 16 * y + i;
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int64_t r = r0 + 16 * x + 4 * v + g;
+        if (r < n && cc <= r) A[r * n + cc] = acc[x][y][v];
+      }
+    }
 }
 
-// Trailing update: A[i][j] -= sum_t A[i][k+t] A[j][k+t] for k+nb <= j <= i < n.
-__global__ __launch_bounds__(256) void chol_update_kernel(double* __restrict__ A, int64_t n, int64_t k, int nb) {
-  const int64_t base = k + nb;
-  const int64_t bi = blockIdx.y, bj = blockIdx.x;
-  if (bj > bi) return;
-  __shared__ double Pi[CH_NB][CH_NB + 1], Pj[CH_NB][CH_NB + 1];
-  const int tid = threadIdx.x;
-  for (int e = tid; e < 64 * nb; e += 256) {
-    const int r = e / nb, t = e - r * nb;
-    const int64_t gi = base + bi * 64 + r, gj = base + bj * 64 + r;
-    Pi[r][t] = gi < n ? A[gi * n + k + t] : 0.0;
-    Pj[r][t] = gj < n ? A[gj * n + k + t] : 0.0;
+// One panel of a substitution with the factor in A: X[panel] = L_pp^{-1}
+// Z[panel] (BACK: L_pp^{-T}) and the products with it taken off the rows not
+// yet solved, 64 of them (tile) for one strip of 16 columns per workgroup;
+// every wave solves the panel's strip for itself (a chain of 40 products,
+// about a microsecond) so that a panel is one launch.  X is another array
+// than Z when there are tiles: the others may still be reading Z's panel.
+template <bool BACK>
+__global__ __launch_bounds__(256) void chol_solve_kernel(const double* __restrict__ A, int64_t n, int64_t k,
+                                                         double* Z, int64_t c, double* X, unsigned ntiles) {
+  __shared__ CholLds m;
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, i = lane & 15, g = lane >> 4;
+  const unsigned per = ntiles > 0 ? ntiles : 1, strip = blockIdx.x / per, tile = blockIdx.x - strip * per;
+  const int64_t j0 = (int64_t)strip * 16, col = j0 + i < c ? j0 + i : c - 1;
+  const int64_t r0 = (BACK ? 0 : k + CH_NB) + (int64_t)tile * 64 + 16 * w;
+  double f[16], a[4][4];
+  d4 y[4], acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+  for (int q = 0; q < 16; ++q) {
+    const int r = 4 * q + w;
+    f[q] = (k + r < n && k + lane < n) ? A[(k + r) * n + k + lane] : (r == lane ? 1.0 : 0.0);
+  }
+  chol_load_strip(Z, n, k, c, col, g, y);
+  if (ntiles > 0) {
+#pragma unroll
+    for (int b = 0; b < 4; ++b)
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        const int64_t kk = k + 16 * b + 4 * t + g, r = r0 + i;
+        // (backward: rows of the panel, past the end in the last one; forward: rows below)
+        if (BACK)
+          a[b][t] = kk < n ? A[kk * n + r] : 0.0;
+        else
+          a[b][t] = A[(r < n ? r : n - 1) * n + kk];
+      }
+#pragma unroll
+    for (int v = 0; v < 4; ++v) acc[v] = Z[(r0 + 4 * v + g < n ? r0 + 4 * v + g : n - 1) * c + col];
+  }
+#pragma unroll
+  for (int q = 0; q < 16; ++q) {
+    const int r = 4 * q + w, rb = r & 15, lb = lane & 15;
+    m.T[r * CH_LD + lane] = f[q];
+    if ((lane >> 4) == (r >> 4)) {
+      // upper triangle: the inverse, transposed; it is 0 above its diagonal
+      if (lane >= r) m.V[lane * CH_LV + rb] = lane == r ? 1.0 / f[q] : f[q];
+      if (lane > r) m.V[r * CH_LV + lb] = 0.0;
+    }
   }
   __syncthreads();
-  for (int e = tid; e < 64 * 64; e += 256) {
-    const int r = e / 64, c = e % 64;
-    const int64_t gi = base + bi * 64 + r, gj = base + bj * 64 + c;
-    if (gi >= n || gj >= n || gj > gi) continue;
-    double s = 0.0;
-    for (int t = 0; t < nb; ++t) s += Pi[r][t] * Pj[c][t];
-    A[gi * n + gj] -= s;
+  chol_chain<BACK>(m, y);
+  if (tile == 0 && w == 0) chol_store_strip(X, n, k, c, j0 + i, g, y);
+  if (ntiles > 0) {
+#pragma unroll
+    for (int b = 0; b < 4; ++b)
+#pragma unroll
+      for (int t = 0; t < 4; ++t) acc = mfma64(-a[b][t], y[b][t], acc);
+    if (j0 + i < c) {
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+        if (r0 + 4 * v + g < n) Z[(r0 + 4 * v + g) * c + col] = acc[v];
+    }
   }
 }
 
-// strict upper triangle <- L^T
-__global__ __launch_bounds__(256) void chol_mirror_kernel(double* __restrict__ A, int64_t n) {
+// resid = G - Y_t with G = K_ts alpha (m x c) on entry; G = 2 resid / (m c); sq = resid^2
+__global__ __launch_bounds__(256) void krr_resid_kernel(int64_t mc, const float* __restrict__ Yt,
+                                                        double* __restrict__ G, double* __restrict__ sq) {
   const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (e >= n * n) return;
-  const int64_t i = e / n, j = e - i * n;
-  if (j > i) A[i * n + j] = A[j * n + i];
-}
-
-// out (m x c, float) = K (m x n, float, leading dim ld) X (n x c, double)
-__global__ __launch_bounds__(256) void krr_matmul_kernel(const float* __restrict__ K, int64_t m, int64_t n,
-                                                         int64_t ld, const double* __restrict__ X, int64_t c,
-                                                         float* __restrict__ out) {
-  const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (e >= m * c) return;
-  const int64_t i = e / c, j = e - i * c;
-  double s = 0.0;
-  const float* row = K + i * ld;
-  for (int64_t t = 0; t < n; ++t) s += (double)row[t] * X[t * c + j];
-  out[e] = (float)s;
-}
-
-// pred = K_ts alpha (m x c); resid = pred - Y_t; G = 2 resid / (m c); sq = resid^2
-__global__ __launch_bounds__(256) void krr_resid_kernel(const float* __restrict__ Kts, int64_t m, int64_t n,
-                                                        const double* __restrict__ alpha, int64_t c,
-                                                        const float* __restrict__ Yt, double* __restrict__ G,
-                                                        double* __restrict__ sq) {
-  const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (e >= m * c) return;
-  const int64_t i = e / c, k = e - i * c;
-  double p = 0.0;
-  for (int64_t t = 0; t < n; ++t) p += (double)Kts[i * n + t] * alpha[t * c + k];
-  const double r = p - (double)Yt[e];
-  G[e] = 2.0 * r / (double)(m * c);
+  if (e >= mc) return;
+  const double r = G[e] - (double)Yt[e];
+  G[e] = 2.0 * r / (double)mc;
   sq[e] = r * r;
 }
 
@@ -183,18 +427,6 @@ __global__ __launch_bounds__(256) void krr_loss_kernel(const double* __restrict_
   if (threadIdx.x == 0) loss[0] = red[0] / (double)cnt;
 }
 
-// B (n x c) = K_ts^T G
-__global__ __launch_bounds__(256) void krr_ktg_kernel(const float* __restrict__ Kts, int64_t m, int64_t n,
-                                                      const double* __restrict__ G, int64_t c,
-                                                      double* __restrict__ B) {
-  const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (e >= n * c) return;
-  const int64_t t = e / c, k = e - t * c;
-  double s = 0.0;
-  for (int64_t i = 0; i < m; ++i) s += (double)Kts[i * n + t] * G[i * c + k];
-  B[e] = s;
-}
-
 // out (rows x cols, float) = scale * U V^T with U (rows x c), V (cols x c) double
 __global__ __launch_bounds__(256) void krr_outer_kernel(const double* __restrict__ U, int64_t rows,
                                                         const double* __restrict__ V, int64_t cols, int64_t c,
@@ -209,11 +441,10 @@ __global__ __launch_bounds__(256) void krr_outer_kernel(const double* __restrict
 
 int launch_krr_mse_bwd(const float* Kts, int64_t m, int64_t n, const double* alpha, int64_t c, const float* Yt,
                        double* G, double* sq, double* loss, double* B, hipStream_t s) {
-  const unsigned g1 = (unsigned)((m * c + 255) / 256), g2 = (unsigned)((n * c + 255) / 256);
-  hipLaunchKernelGGL(krr_resid_kernel, dim3(g1), dim3(256), 0, s, Kts, m, n, alpha, c, Yt, G, sq);
+  if (dn_gemm_fd(Kts, n, false, alpha, c, G, c, m, c, n, 1.0, 0.0, false, s)) return -3;
+  hipLaunchKernelGGL(krr_resid_kernel, dim3((unsigned)((m * c + 255) / 256)), dim3(256), 0, s, m * c, Yt, G, sq);
   hipLaunchKernelGGL(krr_loss_kernel, dim3(1), dim3(256), 0, s, sq, m * c, loss);
-  hipLaunchKernelGGL(krr_ktg_kernel, dim3(g2), dim3(256), 0, s, Kts, m, n, G, c, B);
-  return hipGetLastError() == hipSuccess ? 0 : -3;
+  return dn_gemm_fd(Kts, n, true, G, c, B, c, n, c, m, 1.0, 0.0, false, s);
 }
 
 int launch_krr_outer(const double* U, int64_t rows, const double* V, int64_t cols, int64_t c, double scale,
@@ -223,108 +454,46 @@ int launch_krr_outer(const double* U, int64_t rows, const double* V, int64_t col
   return hipGetLastError() == hipSuccess ? 0 : -3;
 }
 
-int launch_cholesky(double* A, int64_t n, int* info, hipStream_t s) {
+template <bool BACK>
+static void chol_solve_launch(const double* A, int64_t n, int64_t k, double* Z, int64_t c, double* X, int64_t ntiles,
+                              hipStream_t s) {
+  const int64_t strips = (c + 15) / 16;
+  hipLaunchKernelGGL(chol_solve_kernel<BACK>, dim3((unsigned)(strips * (ntiles > 0 ? ntiles : 1))), dim3(256), 0, s, A,
+                     n, k, Z, c, X, (unsigned)ntiles);
+}
+
+int launch_cholesky(double* A, int64_t n, int* info, double* Z, int64_t c, hipStream_t s) {
+  if (!Z) c = 0;
   for (int64_t k = 0; k < n; k += CH_NB) {
     const int nb = (int)((n - k) < CH_NB ? (n - k) : CH_NB);
-    hipLaunchKernelGGL(chol_diag_kernel, dim3(1), dim3(256), 0, s, A, n, k, nb, info);
-    const int64_t rest = n - k - nb;
+    const int64_t rest = n - k - nb, nbk = (rest + CH_NB - 1) / CH_NB;
+    // (with at most one workgroup of rows the factor goes straight into place,
+    // and the right-hand sides follow in a launch of their own)
+    const bool ride = c > 0 && rest > CH_NB;
+    const unsigned nrow = (unsigned)(nbk > 0 ? nbk : 1);
+    hipLaunchKernelGGL(chol_panel_kernel, dim3(nrow + (ride ? (unsigned)((c + 63) / 64) : 0)), dim3(256), 0, s, A, n, k,
+                       nb, info, nrow, Z, c);
+    if (c > 0 && !ride) chol_solve_launch<false>(A, n, k, Z, c, Z, 0, s);
     if (rest > 0) {
-      hipLaunchKernelGGL(chol_trsm_kernel, dim3((unsigned)((rest + 255) / 256)), dim3(256), 0, s, A, n, k, nb);
-      const unsigned nbk = (unsigned)((rest + 63) / 64);
-      hipLaunchKernelGGL(chol_update_kernel, dim3(nbk, nbk), dim3(256), 0, s, A, n, k, nb);
-    }
-  }
-  hipLaunchKernelGGL(chol_mirror_kernel, dim3((unsigned)((n * n + 255) / 256)), dim3(256), 0, s, A, n);
-  return hipGetLastError() == hipSuccess ? 0 : -3;
-}
-
-// ---- blocked substitution for many right-hand sides ----------------------
-//
-// X = A^{-1} B with A = L L^T factored in place (L in the lower triangle):
-// forward L Z = B and backward L^T X = Z in panels of CH_NB rows.  Each
-// panel's triangle is solved with one thread per right-hand side (the
-// triangle in LDS, the panel's unknowns in registers), and the rows not yet
-// solved are updated with the float64 GEMM (X_rest -= L_rest,panel X_panel).
-
-// X (n x c double) = B (float or double, n x c)
-__global__ __launch_bounds__(256) void chol_rhs_copy_kernel(const float* __restrict__ Bf,
-                                                            const double* __restrict__ Bd, int64_t nc,
-                                                            double* __restrict__ X) {
-  const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (e < nc) X[e] = Bf ? (double)Bf[e] : Bd[e];
-}
-
-// Triangle of panel [k, k + nb) for every column: forward (L) or backward (L^T).
-template <bool BACK>
-__global__ __launch_bounds__(256) void chol_panel_kernel(const double* __restrict__ A, int64_t n, int64_t k, int nb,
-                                                         double* __restrict__ X, int64_t c) {
-  __shared__ double T[CH_NB][CH_NB + 1];
-  for (int e = threadIdx.x; e < nb * nb; e += 256) {
-    const int i = e / nb, j = e - i * nb;
-    T[i][j] = j <= i ? A[(k + i) * n + k + j] : 0.0;  // L of the panel
-  }
-  __syncthreads();
-  const int64_t col = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (col >= c) return;
-  double x[CH_NB];
-#pragma unroll
-  for (int i = 0; i < CH_NB; ++i) x[i] = i < nb ? X[(k + i) * c + col] : 0.0;
-  if (!BACK) {
-#pragma unroll
-    for (int i = 0; i < CH_NB; ++i) {
-      if (i < nb) {
-        double v = x[i];
-#pragma unroll
-        for (int j = 0; j < i; ++j) v = fma(-T[i][j], x[j], v);
-        x[i] = v / T[i][i];
-      }
-    }
-  } else {
-#pragma unroll
-    for (int i = CH_NB - 1; i >= 0; --i) {
-      if (i < nb) {
-        double v = x[i];
-#pragma unroll
-        for (int j = i + 1; j < CH_NB; ++j)
-          if (j < nb) v = fma(-T[j][i], x[j], v);
-        x[i] = v / T[i][i];
-      }
-    }
-  }
-#pragma unroll
-  for (int i = 0; i < CH_NB; ++i)
-    if (i < nb) X[(k + i) * c + col] = x[i];
-}
-
-int launch_tri_solve(const double* A, int64_t n, double* X, int64_t c, bool upper, hipStream_t s) {
-  if (n <= 0 || c <= 0) return 0;
-  const unsigned gc = (unsigned)((c + 255) / 256);
-  if (!upper) {
-    for (int64_t k = 0; k < n; k += CH_NB) {
-      const int nb = (int)((n - k) < CH_NB ? (n - k) : CH_NB);
-      hipLaunchKernelGGL(chol_panel_kernel<false>, dim3(gc), dim3(256), 0, s, A, n, k, nb, X, c);
-      const int64_t rest = n - k - nb;
-      if (rest > 0 && dn_gemm_dd(A + (k + nb) * n + k, n, false, X + k * c, c, X + (k + nb) * c, c, rest, c, nb,
-                                 -1.0, 1.0, false, s))
-        return -3;
-    }
-  } else {
-    const int64_t last = ((n - 1) / CH_NB) * CH_NB;
-    for (int64_t k = last; k >= 0; k -= CH_NB) {
-      const int nb = (int)((n - k) < CH_NB ? (n - k) : CH_NB);
-      hipLaunchKernelGGL(chol_panel_kernel<true>, dim3(gc), dim3(256), 0, s, A, n, k, nb, X, c);
-      // rows [0, k): X -= (L[k:k+nb, 0:k])^T X_panel
-      if (k > 0 && dn_gemm_dd(A + k * n, n, true, X + k * c, c, X, c, k, c, nb, -1.0, 1.0, false, s)) return -3;
+      const int64_t ntiles = nbk * (nbk + 1) / 2;
+      const int move = rest > CH_NB ? 1 : 0;
+      hipLaunchKernelGGL(chol_update_kernel, dim3((unsigned)(ntiles + move + (c + 15) / 16 * nbk)), dim3(256), 0, s, A,
+                         n, k, (unsigned)ntiles, move, Z, c, (unsigned)nbk);
     }
   }
   return hipGetLastError() == hipSuccess ? 0 : -3;
 }
 
-int launch_chol_solve(const double* A, int64_t n, const float* Bf, const double* Bd, int64_t c, double* X,
-                      hipStream_t s) {
+int launch_chol_forward(const double* A, int64_t n, double* Z, int64_t c, double* X, hipStream_t s) {
   if (n <= 0 || c <= 0) return 0;
-  hipLaunchKernelGGL(chol_rhs_copy_kernel, dim3((unsigned)((n * c + 255) / 256)), dim3(256), 0, s, Bf, Bd, n * c, X);
-  if (launch_tri_solve(A, n, X, c, false, s) || launch_tri_solve(A, n, X, c, true, s)) return -3;
+  for (int64_t k = 0; k < n; k += CH_NB)
+    chol_solve_launch<false>(A, n, k, Z, c, X, n - k > CH_NB ? (n - k - 1) / CH_NB : 0, s);
+  return hipGetLastError() == hipSuccess ? 0 : -3;
+}
+
+int launch_chol_backward(const double* A, int64_t n, double* Z, int64_t c, double* X, hipStream_t s) {
+  if (n <= 0 || c <= 0) return 0;
+  for (int64_t k = (n - 1) / CH_NB * CH_NB; k >= 0; k -= CH_NB) chol_solve_launch<true>(A, n, k, Z, c, X, k / CH_NB, s);
   return hipGetLastError() == hipSuccess ? 0 : -3;
 }
 
@@ -333,13 +502,6 @@ int launch_krr_build(const float* K, int64_t n, double ridge_rel, double lam_abs
   if (ridge_rel >= 0.0) hipLaunchKernelGGL(krr_diag_mean_kernel, dim3(1), dim3(256), 0, s, K, n, n, mean);
   hipLaunchKernelGGL(krr_build_kernel, dim3((unsigned)((n * n + 255) / 256)), dim3(256), 0, s, K, n, mean,
                      ridge_rel, lam_abs, A, info);
-  return hipGetLastError() == hipSuccess ? 0 : -3;
-}
-
-int launch_krr_matmul(const float* K, int64_t m, int64_t n, int64_t ld, const double* X, int64_t c, float* out,
-                      hipStream_t s) {
-  hipLaunchKernelGGL(krr_matmul_kernel, dim3((unsigned)((m * c + 255) / 256)), dim3(256), 0, s, K, m, n, ld, X, c,
-                     out);
   return hipGetLastError() == hipSuccess ? 0 : -3;
 }
 

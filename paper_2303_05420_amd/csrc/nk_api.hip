@@ -869,8 +869,7 @@ int approx_low_rank_v(const float* K_nr, int64_t n, int64_t r, int64_t ld_nr, co
   if (nk::dn_gemm_ff(K_nr, ld_nr, true, K_nr, ld_nr, A, r, r, r, n, 1.0, 0.0, true, s) ||
       nk::dn_load_shift(K_rr, ld_rr, r, jitter, D, info, s) || nk::dn_axpby(A, D, r * r, 1.0, lam, s) ||
       nk::dn_gemm_ff(K_nr, ld_nr, true, Y, c, bb, c, r, c, n, 1.0, 0.0, true, s) ||
-      nk::launch_cholesky(A, r, info, s) ||
-      nk::launch_chol_solve(A, r, nullptr, bb, c, at<double>(ws, ap.v), s))
+      nk::launch_cholesky(A, r, info, bb, c, s) || nk::launch_chol_backward(A, r, bb, c, at<double>(ws, ap.v), s))
     return -3;
   return 0;
 }
@@ -1327,9 +1326,10 @@ int nk_krr_predict(const float* K_train, int64_t n, const float* K_test, int64_t
   double* X = at<double>(ws, kp.X);
   hipStream_t s = (hipStream_t)stream;
   if (nk::launch_krr_build(K_train, n, ridge_rel, 0.0, mean, A, info, s)) return hip_fail("krr build");
-  if (nk::launch_cholesky(A, n, info, s)) return hip_fail("cholesky");
-  if (nk::launch_chol_solve(A, n, Y, nullptr, c, X, s)) return hip_fail("cholesky solve");
-  if (m > 0 && nk::launch_krr_matmul(K_test, m, n, n, X, c, pred, s)) return hip_fail("krr predict");
+  double* Z = at<double>(ws, kp.Z);
+  if (nk::dn_copy_f(Y, c, n, c, false, Z, c, s) || nk::launch_cholesky(A, n, info, Z, c, s)) return hip_fail("cholesky");
+  if (nk::launch_chol_backward(A, n, Z, c, X, s)) return hip_fail("cholesky solve");
+  if (m > 0 && nk::dn_gemm_fdf(K_test, n, X, c, pred, c, m, c, n, s)) return hip_fail("krr predict");
   int h_info = 0;
   if (hipMemcpyAsync(&h_info, info, sizeof(int), hipMemcpyDeviceToHost, s) != hipSuccess) return hip_fail("krr");
   if (hipStreamSynchronize(s) != hipSuccess) return hip_fail("krr sync");
@@ -1359,12 +1359,15 @@ int nk_krr_mse_backward(const float* K_ss, int64_t n, const float* K_ts, int64_t
   ProfScope ps("krr_mse_backward", s);
   if (nk::launch_krr_build(K_ss, n, ridge_is_relative ? ridge : -1.0, ridge, mean, A, info, s))
     return hip_fail("krr build");
-  if (nk::launch_cholesky(A, n, info, s)) return hip_fail("cholesky");
-  if (nk::launch_chol_solve(A, n, Y_s, nullptr, c, X, s)) return hip_fail("cholesky solve");
+  if (nk::dn_copy_f(Y_s, c, n, c, false, Z, c, s) || nk::launch_cholesky(A, n, info, Z, c, s))
+    return hip_fail("cholesky");
+  if (nk::launch_chol_backward(A, n, Z, c, X, s)) return hip_fail("cholesky solve");
   if (nk::launch_krr_mse_bwd(K_ts, m, n, X, c, Y_t, G, sq, dloss, B, s)) return hip_fail("krr cotangent");
-  if (nk::launch_chol_solve(A, n, nullptr, B, c, Z, s)) return hip_fail("cholesky solve");
+  // A^{-1} B through Z, back into B
+  if (nk::launch_chol_forward(A, n, B, c, Z, s) || nk::launch_chol_backward(A, n, Z, c, B, s))
+    return hip_fail("cholesky solve");
   if (nk::launch_krr_outer(G, m, X, n, c, 1.0, dK_ts, s)) return hip_fail("krr outer");
-  if (nk::launch_krr_outer(Z, n, X, n, c, -1.0, dK_ss, s)) return hip_fail("krr outer");
+  if (nk::launch_krr_outer(B, n, X, n, c, -1.0, dK_ss, s)) return hip_fail("krr outer");
   int h_info = 0;
   if (hipMemcpyAsync(&h_info, info, sizeof(int), hipMemcpyDeviceToHost, s) != hipSuccess) return hip_fail("krr");
   double h_mean = 0.0;
@@ -1528,12 +1531,10 @@ int nk_krr_nystrom(const float* K_nr, int64_t n, int64_t r, int64_t ld_nr, const
   hipStream_t s = (hipStream_t)stream;
   ProfScope ps("krr_nystrom", s);
   double* alpha = at<double>(ws, ap.alpha);
-  double* P = at<double>(ws, ap.P);
   if (approx_low_rank_v(K_nr, n, r, ld_nr, K_rr, ld_rr, Y, c, lambda, jitter, ws, ap, s) ||
       nk::dn_gemm_fd(K_nr, ld_nr, false, at<double>(ws, ap.v), c, alpha, c, n, c, r, 1.0, 0.0, true, s) ||
       nk::dn_residual_scale(Y, c, n, c, 1.0 / lambda, alpha, s) ||
-      nk::dn_gemm_fd(K_mn, ld_mn, false, alpha, c, P, c, m, c, n, 1.0, 0.0, false, s) ||
-      nk::dn_cast(P, m, c, pred, c, s))
+      nk::dn_gemm_fdf(K_mn, ld_mn, alpha, c, pred, c, m, c, n, s))
     return hip_fail("nystrom");
   return approx_finish(s, at<int>(ws, ap.info), "nystrom");
 }
@@ -1551,10 +1552,8 @@ int nk_krr_sor(const float* K_nr, int64_t n, int64_t r, int64_t ld_nr, const flo
   if (!ws || ws_bytes < ap.total) return fail(NK_EINVAL, "workspace too small (need %zu bytes)", ap.total);
   hipStream_t s = (hipStream_t)stream;
   ProfScope ps("krr_sor", s);
-  double* P = at<double>(ws, ap.P);
   if (approx_low_rank_v(K_nr, n, r, ld_nr, K_rr, ld_rr, Y, c, lambda, jitter, ws, ap, s) ||
-      nk::dn_gemm_fd(K_mr, ld_mr, false, at<double>(ws, ap.v), c, P, c, m, c, r, 1.0, 0.0, false, s) ||
-      nk::dn_cast(P, m, c, pred, c, s))
+      nk::dn_gemm_fdf(K_mr, ld_mr, at<double>(ws, ap.v), c, pred, c, m, c, r, s))
     return hip_fail("sor");
   return approx_finish(s, at<int>(ws, ap.info), "sor");
 }
@@ -1574,21 +1573,19 @@ int nk_krr_block_diag(int32_t p, const float* const* K_blocks, const int64_t* si
   hipStream_t s = (hipStream_t)stream;
   ProfScope ps("krr_block_diag", s);
   double* D = at<double>(ws, ap.D);
+  double* RHS = at<double>(ws, ap.rhs2);
   double* alpha = at<double>(ws, ap.alpha);
-  double* P = at<double>(ws, ap.P);
   int* info = at<int>(ws, ap.info);
   int64_t off = 0;
   for (int32_t i = 0; i < p; ++i) {
     const int64_t b = sizes[i];
     if (nk::dn_load_shift(K_blocks[i], b, b, lambda, D, i == 0 ? info : nullptr, s) ||
-        nk::launch_cholesky(D, b, info, s) ||
-        nk::launch_chol_solve(D, b, Y + off * c, nullptr, c, alpha + off * c, s))
+        nk::dn_copy_f(Y + off * c, c, b, c, false, RHS, c, s) || nk::launch_cholesky(D, b, info, RHS, c, s) ||
+        nk::launch_chol_backward(D, b, RHS, c, alpha + off * c, s))
       return hip_fail("block diagonal");
     off += b;
   }
-  if (nk::dn_gemm_fd(K_mn, ld_mn, false, alpha, c, P, c, m, c, n, 1.0, 0.0, false, s) ||
-      nk::dn_cast(P, m, c, pred, c, s))
-    return hip_fail("block diagonal");
+  if (nk::dn_gemm_fdf(K_mn, ld_mn, alpha, c, pred, c, m, c, n, s)) return hip_fail("block diagonal");
   return approx_finish(s, info, "block diagonal");
 }
 
@@ -1622,28 +1619,28 @@ int nk_krr_bcm(int32_t p, const float* const* K_blocks, const int64_t* sizes, co
   const int64_t w = c + m;
   // prior precision of the test values: (K_mm + jitter I)^{-1}; prec = -(p - 1) of it
   if (nk::dn_identity(I, m, s) || nk::dn_load_shift(K_mm, ld_mm, m, jitter, S, info, s) ||
-      nk::launch_cholesky(S, m, info, s) || nk::launch_chol_solve(S, m, nullptr, I, m, Kinv, s) ||
+      nk::launch_cholesky(S, m, info, I, m, s) || nk::launch_chol_backward(S, m, I, m, Kinv, s) ||
       nk::dn_axpby(prec, Kinv, m * m, 0.0, -(double)(p - 1), s) || nk::launch_zero_f64(acc, m * c, s))
     return hip_fail("bcm");
   int64_t off = 0;
   for (int32_t i = 0; i < p; ++i) {
     const int64_t b = sizes[i];
     const float* kmi = K_mn + off;  // columns off .. off + b of K_mn
-    if (nk::dn_load_shift(K_blocks[i], b, b, lambda, D, nullptr, s) || nk::launch_cholesky(D, b, info, s) ||
+    if (nk::dn_load_shift(K_blocks[i], b, b, lambda, D, nullptr, s) ||
         nk::dn_copy_f(Y + off * c, c, b, c, false, RHS, w, s) ||
-        nk::dn_copy_f(kmi, ld_mn, b, m, true, RHS + c, w, s) ||
-        nk::launch_chol_solve(D, b, nullptr, RHS, w, Z, s) ||
+        nk::dn_copy_f(kmi, ld_mn, b, m, true, RHS + c, w, s) || nk::launch_cholesky(D, b, info, RHS, w, s) ||
+        nk::launch_chol_backward(D, b, RHS, w, Z, s) ||
         // mu_i = K_mi Z[:, :c];  S_i = K_mm - K_mi Z[:, c:] (a difference of nearly equal terms: compensated)
         nk::dn_gemm_fd(kmi, ld_mn, false, Z, w, mu, c, m, c, b, 1.0, 0.0, false, s) ||
         nk::dn_copy_f(K_mm, ld_mm, m, m, false, S, m, s) ||
         nk::dn_gemm_fd(kmi, ld_mn, false, Z + c, w, S, m, m, m, b, -1.0, 1.0, true, s) ||
-        nk::dn_shift(S, m, jitter, nullptr, s) || nk::launch_cholesky(S, m, info, s) ||
-        nk::launch_chol_solve(S, m, nullptr, I, m, Sinv, s) || nk::dn_axpby(prec, Sinv, m * m, 1.0, 1.0, s) ||
-        nk::dn_gemm_dd(Sinv, m, false, mu, c, acc, c, m, c, m, 1.0, 1.0, false, s))
+        nk::dn_shift(S, m, jitter, nullptr, s) || nk::dn_identity(I, m, s) ||
+        nk::launch_cholesky(S, m, info, I, m, s) || nk::launch_chol_backward(S, m, I, m, Sinv, s) || nk::dn_axpby(prec, Sinv, m * m, 1.0, 1.0, s) ||
+        nk::dn_gemm_dd(Sinv, m, mu, c, acc, c, m, c, m, 1.0, 1.0, s))
       return hip_fail("bcm");
     off += b;
   }
-  if (nk::launch_cholesky(prec, m, info, s) || nk::launch_chol_solve(prec, m, nullptr, acc, c, P, s) ||
+  if (nk::launch_cholesky(prec, m, info, acc, c, s) || nk::launch_chol_backward(prec, m, acc, c, P, s) ||
       nk::dn_cast(P, m, c, pred, c, s))
     return hip_fail("bcm");
   return approx_finish(s, info, "bcm");

@@ -177,20 +177,19 @@ int launch_finish_sigma(const double* sums, double sw2, float* dsigma, hipStream
 // out (cols x rows) = in^T (rows x cols), both dense; rows <= 65535 * 32.
 int launch_transpose_f32(const float* in, int64_t rows, int64_t cols, float* out, hipStream_t s);
 int launch_zero_f64(double* p, int64_t n, hipStream_t s);
-int launch_cholesky(double* A, int64_t n, int* info, hipStream_t s);
-// In place X (n x c, row-major) <- L^{-1} X (upper = false) or L^{-T} X
-// (upper = true), L the factor launch_cholesky left in A.
-int launch_tri_solve(const double* A, int64_t n, double* X, int64_t c, bool upper, hipStream_t s);
-int launch_chol_solve(const double* A, int64_t n, const float* Bf, const double* Bd, int64_t c, double* X,
-                      hipStream_t s);
+// Cholesky factor of A (n x n, lower triangle) in place; info[0] = 1 at a
+// pivot that is not positive.  Z (n x c, row-major; NULL: none) <- L^{-1} Z.
+int launch_cholesky(double* A, int64_t n, int* info, double* Z, int64_t c, hipStream_t s);
+// X = L^{-1} Z and X = L^{-T} Z (n x c each) for the factor that
+// launch_cholesky left in A; X is another array than Z, which is used up.
+int launch_chol_forward(const double* A, int64_t n, double* Z, int64_t c, double* X, hipStream_t s);
+int launch_chol_backward(const double* A, int64_t n, double* Z, int64_t c, double* X, hipStream_t s);
 int launch_krr_build(const float* K, int64_t n, double ridge_rel, double lam_abs, double* mean, double* A,
                      int* info, hipStream_t s);
 int launch_krr_mse_bwd(const float* Kts, int64_t m, int64_t n, const double* alpha, int64_t c, const float* Yt,
                        double* G, double* sq, double* loss, double* B, hipStream_t s);
 int launch_krr_outer(const double* U, int64_t rows, const double* V, int64_t cols, int64_t c, double scale,
                      float* out, hipStream_t s);
-int launch_krr_matmul(const float* K, int64_t m, int64_t n, int64_t ld, const double* X, int64_t c, float* out,
-                      hipStream_t s);
 
 // Event bracket around one launch (the host API times the product that
 // dominates a conjugate-gradient iteration through it).
@@ -236,15 +235,20 @@ int launch_kmv(const float* K, int64_t n, int64_t ldk, const double* P, int C, d
                double* pq_part, hipStream_t s, ProfHook* hook);
 int launch_diag_mean(const float* K, int64_t n, int64_t ldk, double* out, hipStream_t s);
 
-// Dense float64 helpers of the approximate solvers (dense.hip).  GEMM:
-// C (M x N, ldc) = beta C + alpha op(A) B, op(A) = A (M x K) or A^T (A is
-// K x M); comp carries each sum's rounding error (compensated).
+// Dense float64 helpers of the solvers (dense.hip).  GEMM: C (M x N, ldc) =
+// beta C + alpha op(A) B, op(A) = A (M x K) or A^T (A is K x M); comp carries
+// the sums' rounding errors (compensated).  -1: a form that is not compiled.
 int dn_gemm_ff(const float* A, int64_t lda, bool a_t, const float* B, int64_t ldb, double* C, int64_t ldc, int64_t M,
                int64_t N, int64_t K, double alpha, double beta, bool comp, hipStream_t s);
 int dn_gemm_fd(const float* A, int64_t lda, bool a_t, const double* B, int64_t ldb, double* C, int64_t ldc,
                int64_t M, int64_t N, int64_t K, double alpha, double beta, bool comp, hipStream_t s);
-int dn_gemm_dd(const double* A, int64_t lda, bool a_t, const double* B, int64_t ldb, double* C, int64_t ldc,
-               int64_t M, int64_t N, int64_t K, double alpha, double beta, bool comp, hipStream_t s);
+int dn_gemm_dd(const double* A, int64_t lda, const double* B, int64_t ldb, double* C, int64_t ldc, int64_t M,
+               int64_t N, int64_t K, double alpha, double beta, hipStream_t s);
+// C (float) = A B
+int dn_gemm_fdf(const float* A, int64_t lda, const double* B, int64_t ldb, float* C, int64_t ldc, int64_t M,
+                int64_t N, int64_t K, hipStream_t s);
+// M (r x r) = lam I + L^T L, compensated, L n x r column-major; clears info[0]
+int dn_ltl(const double* L, int64_t n, int64_t r, double lam, double* M, int* info, hipStream_t s);
 int dn_load_shift(const float* S, int64_t lds, int64_t n, double shift, double* D, int* info, hipStream_t s);
 int dn_shift(double* D, int64_t n, double shift, int* info, hipStream_t s);
 int dn_identity(double* I, int64_t n, hipStream_t s);

@@ -254,71 +254,19 @@ __global__ __launch_bounds__(PC_TPB) void pc_transpose_kernel(const double* __re
   }
 }
 
-// M = lam I + L^T L (r x r, row major), 32 x 32 output tiles; also clears the
-// factorisation flag.  The Woodbury form subtracts L M^{-1} L^T from the
-// identity, which along the leading directions of K leaves only about
-// lam / sigma^2 (sigma^2 up to the largest eigenvalue of K): so M has to
-// match L^T L to about one rounding of its entries, or the preconditioner
-// loses definiteness there and CG stalls.  A plain running sum over n rows
-// is off by up to n roundings; the sums here carry their error terms
-// (exact product errors by FMA, TwoSum for the additions) and round once.
-__global__ __launch_bounds__(PC_TPB) void pc_ltl_kernel(const double* __restrict__ L, int64_t n, int r, double lam,
-                                                        double* __restrict__ M, int* __restrict__ info) {
-#pragma clang fp contract(off)
-  __shared__ double A[32][33], B[32][33];
-  const int a0 = blockIdx.y * 32, b0 = blockIdx.x * 32;
-  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;  // 8 rows of threads, 4 outputs each
-  double hi[4] = {0.0, 0.0, 0.0, 0.0}, lo[4] = {0.0, 0.0, 0.0, 0.0};
-  for (int64_t i0 = 0; i0 < n; i0 += 32) {
-    for (int y = ty; y < 32; y += 8) {
-      const int64_t i = i0 + tx;
-      A[y][tx] = (a0 + y < r && i < n) ? L[(int64_t)(a0 + y) * n + i] : 0.0;
-      B[y][tx] = (b0 + y < r && i < n) ? L[(int64_t)(b0 + y) * n + i] : 0.0;
-    }
-    __syncthreads();
-    for (int k = 0; k < 32; ++k) {
-      const double bv = B[tx][k];
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const double av = A[ty + 8 * q][k];
-        const double p = av * bv;
-        const double pe = __builtin_fma(av, bv, -p);  // av bv - p exactly
-        const double s = hi[q] + p;
-        const double bb = s - hi[q];
-        const double se = (hi[q] - (s - bb)) + (p - bb);  // hi + p - s exactly
-        hi[q] = s;
-        lo[q] += se + pe;
-      }
-    }
-    __syncthreads();
-  }
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int a = a0 + ty + 8 * q, b = b0 + tx;
-    if (a < r && b < r) {
-      double v = hi[q];
-      double e = lo[q];
-      if (a == b) {
-        const double s = v + lam;
-        const double bb = s - v;
-        e += (v - (s - bb)) + (lam - bb);
-        v = s;
-      }
-      M[(int64_t)a * r + b] = v + e;
-    }
-  }
-  if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) info[0] = 0;
-}
-
 int launch_pc_setup(double* LU, int64_t n, int r, double lam, double* Ur, double* M, int* info, hipStream_t s) {
   if (r == 0) return 0;
-  const unsigned g = (unsigned)((r + 31) / 32);
-  hipLaunchKernelGGL(pc_ltl_kernel, dim3(g, g), dim3(PC_TPB), 0, s, LU, n, r, lam, M, info);
-  if (launch_cholesky(M, r, info, s)) return -3;
+  // M = lam I + L^T L.  The Woodbury form subtracts L M^{-1} L^T from the
+  // identity, which along the leading directions of K leaves only about
+  // lam / sigma^2 (sigma^2 up to the largest eigenvalue of K): so M has to
+  // match L^T L to about one rounding of its entries, or the preconditioner
+  // loses definiteness there and CG stalls.  A plain running sum over n rows
+  // is off by up to n roundings; the product is compensated.
+  if (dn_ltl(LU, n, r, lam, M, info, s)) return -3;
   // U = L R^{-T} in place: with L stored column major (an r x n row-major
   // array), U^T = R^{-1} L^T is a forward substitution with n right-hand
-  // sides, run blocked (panel triangles and float64 GEMM updates)
-  if (launch_tri_solve(M, r, LU, n, false, s)) return -3;
+  // sides, which ride along in the factorisation of M
+  if (launch_cholesky(M, r, info, LU, n, s)) return -3;
   hipLaunchKernelGGL(pc_transpose_kernel, dim3((unsigned)((n + 31) / 32), (unsigned)((r + 31) / 32)), dim3(PC_TPB),
                      0, s, LU, n, r, Ur);
   return hipGetLastError() == hipSuccess ? 0 : -3;
