@@ -4,50 +4,63 @@
 //   K_{l+1}    = sigma_w2 F(K_l, K_l(x, x), K_l(x', x')) + sigma_b2
 //   F(s, q, q') = sqrt(q q') / 2 J1(s / sqrt(q q'))
 //
-// The first layer's dot products are a dense (n1 x d) (d x n2) contraction:
-// they run on the fp32 matrix cores (v_mfma_f32_16x16x4f32) from LDS tiles,
-// and the ReLU recursion is applied in the epilogue of the same kernel.  The diagonals
-// follow K_{l+1}(x, x) = sigma_w2 K_l(x, x) / 2 + sigma_b2 (F(q, q, q) = q/2).
+// The first layer's dot products are a dense (n1 x d) (d x n2) contraction on
+// the matrix cores, and the ReLU recursion is applied in the epilogue of the
+// same kernel.  The diagonals follow K_{l+1}(x, x) = sigma_w2 K_l(x, x) / 2 +
+// sigma_b2 (F(q, q, q) = q/2).  Two kernels, by size (launch_fc):
+//   fc_small_kernel   few outputs: a 16 x 16 tile per workgroup, its waves
+//                     splitting d, fp32 matrix instructions;
+//   fc_split_kernel   128 x 128 or 64 x 64 tiles, each float32 as the exact sum
+//                     of three bfloat16 (bf16 matrix instructions run 16 times
+//                     as fast, and six of the nine products are needed).
 #include "nk_kernels.h"
 
 namespace nk {
 
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 
-// first-layer diagonal sigma_w2 |x|^2 / d + sigma_b2, one wave per row
-__global__ __launch_bounds__(256) void fc_diag_kernel(const float* __restrict__ x, int64_t n, int d, float sw2,
-                                                      float sb2, float* __restrict__ out) {
-  const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));  // rows are element aligned only
+typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
+typedef float f2 __attribute__((ext_vector_type(2)));
+typedef float f16v __attribute__((ext_vector_type(16)));
+
+// first-layer diagonals sigma_w2 |x|^2 / d + sigma_b2 of both sets, one wave per row
+__global__ __launch_bounds__(256) void fc_diag_kernel(const float* __restrict__ x1, int64_t n1,
+                                                      const float* __restrict__ x2, int64_t n2, int d, float sw2,
+                                                      float sb2, float* __restrict__ d1, float* __restrict__ d2) {
+  const int64_t e = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
-  if (row >= n) return;
-  const float* p = x + row * (int64_t)d;
+  if (e >= n1 + n2) return;
+  const float* p = e < n1 ? x1 + e * (int64_t)d : x2 + (e - n1) * (int64_t)d;
   double s = 0.0;
-  for (int k = lane; k < d; k += 64) s += (double)p[k] * (double)p[k];
+  int k = 4 * lane;
+  for (; k + 3 < d; k += 256) {
+    const f4u v = *reinterpret_cast<const f4u*>(p + k);
+    s += (double)v.x * (double)v.x + (double)v.y * (double)v.y + (double)v.z * (double)v.z + (double)v.w * (double)v.w;
+  }
+  for (; k < d; ++k) s += (double)p[k] * (double)p[k];  // (the lane whose four straddle the end)
   for (int off = 32; off >= 1; off >>= 1) s += __shfl_xor(s, off);
-  if (lane == 0) out[row] = (float)((double)sw2 * s / d + (double)sb2);
+  if (lane == 0) *(e < n1 ? d1 + e : d2 + (e - n1)) = (float)((double)sw2 * s / d + (double)sb2);
 }
 
-__device__ __forceinline__ float4 load4_guard(const float* __restrict__ p, int64_t row, int64_t nrows, int d,
-                                               int k, bool vec) {
-  if (row >= nrows) return make_float4(0.f, 0.f, 0.f, 0.f);
-  const float* q = p + row * (int64_t)d + k;
-  if (vec && k + 3 < d) return *reinterpret_cast<const float4*>(q);
-  float v[4];
-#pragma unroll
-  for (int t = 0; t < 4; ++t) v[t] = (k + t < d) ? q[t] : 0.f;
-  return make_float4(v[0], v[1], v[2], v[3]);
+// The ReLU recursion and readout of one entry from its first-layer dot
+// product; same: an image with itself, whose first-layer value is its diagonal
+// (summed in float64; the float32 sum of squares is up to 1e-6 off at d = 384).
+__device__ __forceinline__ float fc_entry(const FcArgs& a, float dot, float inv_d, float q1, float q2, bool same) {
+  float k = same ? q1 : a.sw2 * dot * inv_d + a.sb2;
+  for (int l = 0; l < a.depth; ++l) {
+    const float qq = q1 * q2;
+    const float rs = __builtin_amdgcn_rsqf(qq);
+    const float rho = k * rs;
+    const float f = 0.5f * (qq * rs) * (l == 0 ? j1_signed(rho) : j1_nonneg(rho));
+    k = a.sw2 * (qq > 0.f ? f : 0.f) + a.sb2;
+    q1 = 0.5f * a.sw2 * q1 + a.sb2;
+    q2 = 0.5f * a.sw2 * q2 + a.sb2;
+  }
+  return k;
 }
 
-// Tiling of the first-layer contraction.  A workgroup (4 waves) owns a
-// 128 x 128 output tile, each wave a 64 x 64 quadrant as 4 x 4 blocks of
-// 16 x 16 v_mfma_f32_16x16x4f32 accumulators (64 registers).  The k range
-// runs in tiles of FC_BK = 32: the 128 rows of x1 and of x2 for the tile sit
-// in LDS as [row][k] (row padded by 4 floats: 16-byte aligned rows, and the
-// 16 rows a block reads start on different banks); the next tile is loaded
-// into registers (4 + 4 float4 per thread) while the current one feeds the
-// MFMAs, and written to LDS between two barriers.  For a block, lane l feeds
-// A[i = l % 16][k = l / 16] and B[k = l / 16][j = l % 16] of each 4-wide k step.
-constexpr int FC_BM = 128, FC_BK = 32, FC_LDR = FC_BK + 4;
 // Tile order.  Workgroups go to the 8 XCDs round-robin in launch order and
 // each XCD has its own L2, so the launch index is first mapped to one
 // contiguous range of tiles per XCD; each range walks the output in groups
@@ -57,145 +70,335 @@ constexpr int FC_BM = 128, FC_BK = 32, FC_LDR = FC_BK + 4;
 // diagonal, in the pair order of the Myrtle stages over tile indices
 // (groups of FC_GROUP), and each off-diagonal tile also writes its mirror.
 constexpr int FC_GROUP = 8;
+__device__ __forceinline__ void fc_tile(const FcArgs& a, int side, int64_t* ti, int64_t* tj) {
+  const int64_t nb = gridDim.x, lin = blockIdx.x;
+  const int64_t xcd = lin & 7, q = nb >> 3, rem = nb & 7;
+  const int64_t id = (xcd < rem ? xcd * (q + 1) : rem * (q + 1) + (xcd - rem) * q) + (lin >> 3);
+  const int64_t gy = (a.n1 + side - 1) / side, gx = (a.n2 + side - 1) / side;
+  if (a.sym) {
+    pair_of(id, gy, gy, 1, FC_GROUP, ti, tj);
+    return;
+  }
+  const int64_t grp = id / (FC_GROUP * gx), first = grp * FC_GROUP;
+  const int64_t rows = gy - first < FC_GROUP ? gy - first : FC_GROUP;
+  const int64_t in = id - first * gx;
+  *ti = first + in % rows;
+  *tj = in / rows;
+}
 
-__global__ __launch_bounds__(256) void fc_kernel(const FcArgs a) {
-  __shared__ __attribute__((aligned(16))) float As[FC_BM * FC_LDR];
-  __shared__ __attribute__((aligned(16))) float Bs[FC_BM * FC_LDR];
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  int64_t r0, c0;
-  bool mirror = false;
-  {
-    const int64_t gx = gridDim.x, gy = gridDim.y, nb = gx * gy;
-    const int64_t lin = (int64_t)blockIdx.y * gx + blockIdx.x;
-    const int64_t xcd = lin & 7, q = nb >> 3, rem = nb & 7;
-    const int64_t id = (xcd < rem ? xcd * (q + 1) : rem * (q + 1) + (xcd - rem) * q) + (lin >> 3);
-    if (a.sym) {
-      const int64_t nt = (a.n1 + FC_BM - 1) / FC_BM;
-      int64_t ti, tj;
-      pair_of(id, nt, nt, 1, FC_GROUP, &ti, &tj);
-      r0 = ti * FC_BM;
-      c0 = tj * FC_BM;
-      mirror = ti != tj;
-    } else {
-      const int64_t grp = id / (FC_GROUP * gx), first = grp * FC_GROUP;
-      const int64_t rows = gy - first < FC_GROUP ? gy - first : FC_GROUP;
-      const int64_t in = id - first * gx;
-      r0 = (first + in % rows) * FC_BM;
-      c0 = (in / rows) * FC_BM;
-    }
+// Four entries of a column, rows rb .. rb + 3; mirror: also as row c, columns
+// rb .. rb + 3; upper: only entries on and above the diagonal (a tile on the
+// diagonal of a symmetric block).
+__device__ __forceinline__ void fc_store4(const FcArgs& a, const float (&kv)[4], int64_t rb, int64_t c, bool mirror,
+                                          bool upper) {
+  if (c >= a.n2) return;
+#pragma unroll
+  for (int v = 0; v < 4; ++v)
+    if (rb + v < a.n1 && !(upper && rb + v > c)) a.K[(rb + v) * a.ldk + c] = kv[v];
+  if (!mirror) return;
+  float* m = a.K + c * a.ldk + rb;
+  if (!upper && rb + 3 < a.n1 && (reinterpret_cast<uintptr_t>(m) & 15) == 0) {
+    *reinterpret_cast<float4*>(m) = make_float4(kv[0], kv[1], kv[2], kv[3]);
+  } else {
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+      if (rb + v < a.n1 && !(upper && rb + v >= c)) m[v] = kv[v];
   }
-  const int wr = 64 * (w >> 1), wc = 64 * (w & 1);
-  const int li = lane & 15, ks = lane >> 4;
-  const bool vec = (a.d & 3) == 0;
-  float4 pa[4], pb[4];
-  auto fetch = [&](int k0) {
+}
+
+// Few outputs.  A workgroup owns a 16 x 16 tile and its 16 waves take every
+// 16th chunk of 16 features each (lane l = 16 g + i reads features 4 g .. 4 g
+// + 3 of row i of both operands, one 16-byte load each), so the depth of the
+// contraction is spread over a CU however few tiles there are; the squares for
+// the diagonals are summed in float64 on the way, so the call is one launch.
+// Bound by the reading of the longer set.  4 x 1000 at d = 3072: 10.9 us
+// (two launches for the diagonals and 8 workgroups of 128 x 128 walking all of
+// d: 307 us).
+constexpr int FS_W = 16;
+__global__ __launch_bounds__(64 * FS_W) void fc_small_kernel(const FcArgs a) {
+  __shared__ float part[FS_W][256];
+  __shared__ double sq[2][FS_W][16];
+  __shared__ float q[2][16];
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, i = lane & 15, g = lane >> 4;
+  int64_t ti, tj;
+  fc_tile(a, 16, &ti, &tj);
+  const int64_t r0 = ti * 16, c0 = tj * 16;
+  const int64_t r = r0 + i < a.n1 ? r0 + i : a.n1 - 1, c = c0 + i < a.n2 ? c0 + i : a.n2 - 1;
+  const float* p1 = a.x1 + r * (int64_t)a.d;
+  const float* p2 = a.x2 + c * (int64_t)a.d;
+  floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+  double s1 = 0.0, s2 = 0.0;
+  auto step = [&](const float (&u)[4], const float (&v)[4]) {
 #pragma unroll
-    for (int m = 0; m < 4; ++m) {
-      const int q = tid + 256 * m, row = q >> 3, kq = 4 * (q & 7);
-      pa[m] = load4_guard(a.x1, r0 + row, a.n1, a.d, k0 + kq, vec);
-      pb[m] = load4_guard(a.x2, c0 + row, a.n2, a.d, k0 + kq, vec);
+    for (int t = 0; t < 4; ++t) {
+      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(u[t], v[t], acc, 0, 0, 0);
+      s1 = __builtin_fma((double)u[t], (double)u[t], s1);
+      s2 = __builtin_fma((double)v[t], (double)v[t], s2);
     }
   };
-  auto store = [&]() {
+  int k0 = 16 * w;
+#pragma unroll 4
+  for (; k0 + 16 <= a.d; k0 += 16 * FS_W) {
+    const f4u x = *reinterpret_cast<const f4u*>(p1 + k0 + 4 * g), y = *reinterpret_cast<const f4u*>(p2 + k0 + 4 * g);
+    const float u[4] = {x.x, x.y, x.z, x.w}, v[4] = {y.x, y.y, y.z, y.w};
+    step(u, v);
+  }
+  if (k0 < a.d) {
+    const int k = k0 + 4 * g;
+    float u[4], v[4];
 #pragma unroll
-    for (int m = 0; m < 4; ++m) {
-      const int q = tid + 256 * m, row = q >> 3, kq = 4 * (q & 7);
-      *reinterpret_cast<float4*>(&As[row * FC_LDR + kq]) = pa[m];
-      *reinterpret_cast<float4*>(&Bs[row * FC_LDR + kq]) = pb[m];
+    for (int t = 0; t < 4; ++t) {
+      u[t] = k + t < a.d ? p1[k + t] : 0.f;
+      v[t] = k + t < a.d ? p2[k + t] : 0.f;
     }
-  };
-  floatx4 acc[4][4];
+    step(u, v);
+  }
+  s1 += __shfl_xor(s1, 16);
+  s2 += __shfl_xor(s2, 16);
+  s1 += __shfl_xor(s1, 32);
+  s2 += __shfl_xor(s2, 32);
+  if (g == 0) {
+    sq[0][w][i] = s1;
+    sq[1][w][i] = s2;
+  }
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
-  fetch(0);
-  store();
+  for (int v = 0; v < 4; ++v) part[w][(4 * g + v) * 16 + i] = acc[v];
   __syncthreads();
-  for (int k0 = 0; k0 < a.d; k0 += FC_BK) {
-    // (the last tile re-requests its own k range: in bounds, never stored)
-    fetch(k0 + FC_BK < a.d ? k0 + FC_BK : k0);
+  double dot = 0.0;
+  if (tid < 256) {
+    for (int m = 0; m < FS_W; ++m) dot += (double)part[m][tid];
+  } else if (tid < 288) {
+    const int o = (tid >> 4) & 1, e = tid & 15;
+    double t = 0.0;
+    for (int m = 0; m < FS_W; ++m) t += sq[o][m][e];
+    q[o][e] = (float)((double)a.sw2 * t / a.d + (double)a.sb2);
+  }
+  __syncthreads();
+  if (tid >= 256) return;
+  const int64_t er = r0 + (tid >> 4), ec = c0 + (tid & 15);
+  if (er >= a.n1 || ec >= a.n2 || (a.sym && ec < er)) return;
+  const float kv = fc_entry(a, (float)dot, 1.0f / (float)a.d, q[0][tid >> 4], q[1][tid & 15],
+                            a.sym && er == ec);
+  a.K[er * a.ldk + ec] = kv;
+  if (a.sym && ec > er) a.K[ec * a.ldk + er] = kv;
+}
+
+// A float32 pair as three bfloat16 pairs, x = h + m + l exactly (8 significant
+// bits each; what underflows bfloat16's 2^-133 is lost).
+__device__ __forceinline__ void fc_split2(float x0, float x1, unsigned& h, unsigned& m, unsigned& l) {
+  auto pk = [](float a, float b) { return __builtin_bit_cast(unsigned, __builtin_convertvector(f2{a, b}, bf2)); };
+  auto lo = [](unsigned u) { return __builtin_bit_cast(float, u << 16); };
+  auto hi = [](unsigned u) { return __builtin_bit_cast(float, u & 0xffff0000u); };
+  h = pk(x0, x1);
+  const float r0 = x0 - lo(h), r1 = x1 - hi(h);
+  m = pk(r0, r1);
+  l = pk(r0 - lo(m), r1 - hi(m));
+}
+
+// Tiles of 64 WB x 64 WB outputs, a quadrant of WB x WB blocks of 32 x 32 per
+// wave on v_mfma_f32_32x32x16_bf16.  The rows of both operands are read as
+// float32, split into three bfloat16 planes on the way into LDS, and the
+// products h h', h m', m h', m m', h l', l h' accumulate in float32 (NP = 6);
+// the three left out are below 2^-24 of the product of the two numbers, with
+// either sign, which 64 or more features average out (NP = 9, all of them,
+// below).  The sum rounds once per 16 terms and product, less often than with
+// fp32 instructions.  Error against float64 at d = 3072: 9.5e-8 of the
+// kernel, 9.6e-8 with fp32 instructions.
+// Non-finite inputs: an infinity or NaN makes its row's diagonal non-finite,
+// and from one ReLU on the entry no longer depends on the dot product; without
+// ReLU layers such an entry's product is formed anew in float32.
+// LDS: [buffer][operand][plane][row] of 16 KT features, rows padded by 16 bytes
+// so that 8 lanes' 16-byte reads fall on different banks.  Two buffers, one
+// barrier per tile of features: the next tile is split and stored while the
+// current one multiplies, the one after it is on its way from memory (its
+// loads stay in flight across the barrier, which waits for LDS only); two
+// workgroups per CU.
+// Bound: the matrix instructions, 6 x 2 n1 n2 d operations at the bf16 rate, by
+// the reads that feed them.  FC-3 Gram of 20000 x 3072 (symmetric): 7.05 ms,
+// 1050 TFLOP/s of bf16 products, what a large library product reaches on this
+// card (1081); with fp32 instructions 12.3 ms, 0.65 of their peak.
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
+template <int WB, int KT, int NP>
+__global__ __launch_bounds__(256, WB == 1 ? 4 : 2) void fc_split_kernel(const FcArgs a) {
+  constexpr int TM = 64 * WB, BK = 16 * KT, ROW = 2 * BK + 16, PLANE = TM * ROW, BUF = 6 * PLANE;
+  constexpr int TPR = BK / 4, RPP = 256 / TPR, NQ = TM / RPP;  // threads a row, rows a pass, passes an operand
+  __shared__ __attribute__((aligned(16))) char lds[2 * BUF];
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  int64_t ti, tj;
+  fc_tile(a, TM, &ti, &tj);
+  const int64_t r0 = ti * TM, c0 = tj * TM;
+  const bool mirror = a.sym, upper = a.sym && ti == tj;
+  // staging: this thread's float4 m of either operand is row tid / TPR + RPP m,
+  // features sk .. sk + 3 of the tile
+  const int srow = tid / TPR, sk = 4 * (tid % TPR);
+  const float* p1[NQ];
+  const float* p2[NQ];
 #pragma unroll
-    for (int kk = 0; kk < FC_BK; kk += 4) {
-      float av[4], bv[4];
+  for (int m = 0; m < NQ; ++m) {
+    const int64_t r = r0 + srow + RPP * m, c = c0 + srow + RPP * m;
+    p1[m] = a.x1 + (r < a.n1 ? r : a.n1 - 1) * (int64_t)a.d + sk;
+    p2[m] = a.x2 + (c < a.n2 ? c : a.n2 - 1) * (int64_t)a.d + sk;
+  }
+  struct Regs {
+    f4u a[NQ], b[NQ];
+  };
+  // (past the last tile: the last one again, in bounds and never stored)
+  const int nt = (a.d + BK - 1) / BK;
+  auto fetch = [&](int t, Regs& v) {
+    const int k0 = (t < nt ? t : nt - 1) * BK;
+    if (k0 + BK <= a.d) {
 #pragma unroll
-      for (int i = 0; i < 4; ++i) av[i] = As[(wr + 16 * i + li) * FC_LDR + kk + ks];
+      for (int m = 0; m < NQ; ++m) {
+        v.a[m] = *reinterpret_cast<const f4u*>(p1[m] + k0);
+        v.b[m] = *reinterpret_cast<const f4u*>(p2[m] + k0);
+      }
+    } else {
 #pragma unroll
-      for (int j = 0; j < 4; ++j) bv[j] = Bs[(wc + 16 * j + li) * FC_LDR + kk + ks];
+      for (int m = 0; m < NQ; ++m)
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[i], bv[j], acc[i][j], 0, 0, 0);
+        for (int q = 0; q < 4; ++q) {
+          const bool in = k0 + sk + q < a.d;
+          v.a[m][q] = in ? p1[m][k0 + q] : 0.f;
+          v.b[m][q] = in ? p2[m][k0 + q] : 0.f;
+        }
     }
-    if (k0 + FC_BK < a.d) {
-      __syncthreads();
-      store();
-      __syncthreads();
+  };
+  auto put = [&](const f4u& x, char* p) {
+    unsigned h0, m0, l0, h1, m1, l1;
+    fc_split2(x.x, x.y, h0, m0, l0);
+    fc_split2(x.z, x.w, h1, m1, l1);
+    *reinterpret_cast<uint2*>(p) = make_uint2(h0, h1);
+    *reinterpret_cast<uint2*>(p + PLANE) = make_uint2(m0, m1);
+    *reinterpret_cast<uint2*>(p + 2 * PLANE) = make_uint2(l0, l1);
+  };
+  char* sp = lds + srow * ROW + 2 * sk;
+  auto store = [&](const Regs& v, int buf) {
+#pragma unroll
+    for (int m = 0; m < NQ; ++m) {
+      put(v.a[m], sp + buf * BUF + RPP * m * ROW);
+      put(v.b[m], sp + buf * BUF + 3 * PLANE + RPP * m * ROW);
+    }
+  };
+  f16v acc[WB][WB];
+#pragma unroll
+  for (int i = 0; i < WB; ++i)
+#pragma unroll
+    for (int j = 0; j < WB; ++j)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+  const int wr = 32 * WB * (w >> 1), wc = 32 * WB * (w & 1), li = lane & 31, kh = lane >> 5;
+  const char* fa = lds + (wr + li) * ROW + 16 * kh;
+  const char* fb = lds + 3 * PLANE + (wc + li) * ROW + 16 * kh;
+  auto multiply = [&](int buf) {
+#pragma unroll
+    for (int kk = 0; kk < KT; ++kk) {
+      bf8 av[3][WB], bv[3][WB];
+#pragma unroll
+      for (int p = 0; p < 3; ++p)
+#pragma unroll
+        for (int i = 0; i < WB; ++i) {
+          av[p][i] = *reinterpret_cast<const bf8*>(fa + buf * BUF + p * PLANE + i * 32 * ROW + 32 * kk);
+          bv[p][i] = *reinterpret_cast<const bf8*>(fb + buf * BUF + p * PLANE + i * 32 * ROW + 32 * kk);
+        }
+      // smallest products first
+      constexpr int PA[9] = {2, 1, 2, 0, 2, 1, 0, 1, 0}, PB[9] = {2, 2, 1, 2, 0, 1, 1, 0, 0};
+#pragma unroll
+      for (int p = 9 - NP; p < 9; ++p)
+#pragma unroll
+        for (int i = 0; i < WB; ++i)
+#pragma unroll
+          for (int j = 0; j < WB; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[PA[p]][i], bv[PB[p]][j], acc[i][j], 0, 0, 0);
+    }
+  };
+  Regs even, odd;  // the tiles of even and odd number on their way
+  fetch(0, even);
+  fetch(1, odd);
+  store(even, 0);
+  lds_barrier();
+  for (int t = 0; t < nt; t += 2) {
+    fetch(t + 2, even);
+    multiply(0);
+    store(odd, 1);  // tile t + 1
+    lds_barrier();
+    if (t + 1 < nt) {
+      fetch(t + 3, odd);
+      multiply(1);
+      store(even, 0);  // tile t + 2
+      lds_barrier();
     }
   }
+  // lane l holds column l & 31, rows 8 (v >> 2) + 4 (l >> 5) + (v & 3) of a block
   const float inv_d = 1.0f / (float)a.d;
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < WB; ++i)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int64_t rb = r0 + wr + 16 * i + 4 * ks;  // rows rb .. rb + 3 of this lane
-      const int64_t c = c0 + wc + 16 * j + li;
-      if (c >= a.n2) continue;
-      float kv[4];
+    for (int j = 0; j < WB; ++j) {
+      const int64_t c = c0 + wc + 32 * j + li;
+      const float q2 = a.d2[c < a.n2 ? c : a.n2 - 1];
 #pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int64_t r = rb + v;
-        if (r >= a.n1) {
-          kv[v] = 0.f;
-          continue;
-        }
-        float k = a.sw2 * acc[i][j][v] * inv_d + a.sb2;
-        float q1 = a.d1[r], q2 = a.d2[c];
-        for (int l = 0; l < a.depth; ++l) {
-          const float qq = q1 * q2;
-          float f = 0.f;
-          if (qq > 0.f) {
-            const float rs = __builtin_amdgcn_rsqf(qq);
-            const float rho = k * rs;
-            f = 0.5f * (qq * rs) * (l == 0 ? j1_signed(rho) : j1_nonneg(rho));
-          }
-          k = a.sw2 * f + a.sb2;
-          q1 = 0.5f * a.sw2 * q1 + a.sb2;
-          q2 = 0.5f * a.sw2 * q2 + a.sb2;
-        }
-        kv[v] = k;
-        a.K[r * a.ldk + c] = k;
-      }
-      if (mirror) {
-        // row c of the block, columns rb .. rb + 3 (one 16-byte store when
-        // they are in range and aligned)
-        float* m = a.K + c * a.ldk + rb;
-        if (rb + 3 < a.n1 && (reinterpret_cast<uintptr_t>(m) & 15) == 0) {
-          *reinterpret_cast<float4*>(m) = make_float4(kv[0], kv[1], kv[2], kv[3]);
-        } else {
+      for (int u = 0; u < 4; ++u) {
+        const int64_t rb = r0 + wr + 32 * i + 8 * u + 4 * kh;
+        float kv[4];
 #pragma unroll
-          for (int v = 0; v < 4; ++v)
-            if (rb + v < a.n1) m[v] = kv[v];
-        }
+        for (int v = 0; v < 4; ++v)
+          kv[v] = fc_entry(a, acc[i][j][4 * u + v], inv_d, a.d1[rb + v < a.n1 ? rb + v : a.n1 - 1], q2,
+                           upper && rb + v == c);
+        fc_store4(a, kv, rb, c, mirror, upper);
       }
     }
+  if (a.depth == 0) {
+    // no ReLU layer: entries of rows that hold an infinity or NaN (their
+    // diagonal says so), from a plain float32 product
+    __syncthreads();
+    for (int e = tid; e < TM * TM; e += 256) {
+      const int64_t r = r0 + e / TM, c = c0 + e % TM;
+      if (r >= a.n1 || c >= a.n2 || (upper && r > c)) continue;
+      if (__builtin_isfinite(a.d1[r]) && __builtin_isfinite(a.d2[c])) continue;
+      float dot = 0.f;
+      for (int k = 0; k < a.d; ++k) dot = __builtin_fmaf(a.x1[r * a.d + k], a.x2[c * a.d + k], dot);
+      const float kv = fc_entry(a, dot, inv_d, a.d1[r], a.d2[c], upper && r == c);
+      a.K[r * a.ldk + c] = kv;
+      if (mirror) a.K[c * a.ldk + r] = kv;
+    }
+  }
+}
+
+// Tiles of side `side` that a launch has to form.
+static int64_t fc_tiles(const FcArgs& a, int64_t side) {
+  const int64_t t1 = (a.n1 + side - 1) / side, t2 = (a.n2 + side - 1) / side;
+  return a.sym ? t1 * (t1 + 1) / 2 : t1 * t2;
 }
 
 int launch_fc(const FcArgs& a, float* d1, float* d2, hipStream_t stream) {
-  hipLaunchKernelGGL(fc_diag_kernel, dim3((unsigned)((a.n1 + 3) / 4)), dim3(256), 0, stream, a.x1, a.n1, a.d, a.sw2,
-                     a.sb2, d1);
-  hipLaunchKernelGGL(fc_diag_kernel, dim3((unsigned)((a.n2 + 3) / 4)), dim3(256), 0, stream, a.x2, a.n2, a.d, a.sw2,
-                     a.sb2, d2);
+  // Kernel by size.  16 x 16 tiles read 16 + 16 rows for 256 outputs, eight
+  // times what the others read, but spread any d over a CU: at d = 3072 / 784,
+  // 512 x 512 outputs (1024 tiles) take 50 / 14 us against 80 / 29 with 64 x 64
+  // tiles, 4 x 20000 (1250) 46 / 16 against 133 / 47, 1000 x 1000 (3969) 183 /
+  // 45 against 86 / 32.
+  const int64_t small = fc_tiles(a, 16);
+  if (small <= 1536) {
+    hipLaunchKernelGGL(fc_small_kernel, dim3((unsigned)small), dim3(64 * FS_W), 0, stream, a);
+    return hipGetLastError() == hipSuccess ? 0 : -3;
+  }
   FcArgs b = a;
   b.d1 = d1;
-  b.d2 = d2;
-  const int64_t t1 = (a.n1 + FC_BM - 1) / FC_BM, t2 = (a.n2 + FC_BM - 1) / FC_BM;
-  if (a.sym) {
-    // (the x2 diagonals equal the x1 ones; both are computed, as for any block)
-    hipLaunchKernelGGL(fc_kernel, dim3((unsigned)(t1 * (t1 + 1) / 2)), dim3(256), 0, stream, b);
-  } else {
-    hipLaunchKernelGGL(fc_kernel, dim3((unsigned)t2, (unsigned)t1), dim3(256), 0, stream, b);
-  }
+  b.d2 = a.sym ? d1 : d2;
+  const int64_t rows = a.n1 + (a.sym ? 0 : a.n2);
+  hipLaunchKernelGGL(fc_diag_kernel, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, stream, a.x1, a.n1, a.x2,
+                     a.sym ? 0 : a.n2, a.d, a.sw2, a.sb2, d1, d2);
+  // 128 x 128 tiles halve the reads of 64 x 64 ones, which fill the chip sooner
+  // and hide the epilogue (four workgroups a CU): 4096 x 4096 at d = 3072 / 784
+  // / 64: 620 / 192 / 69 us against 760 / 218 / 58; 3000 x 3000 (576 tiles):
+  // 423 / 150 / 59 against 427 / 130 / 37.
+  const int64_t t128 = fc_tiles(a, 128), t64 = fc_tiles(a, 64);
+  if (t128 >= 640 && a.d >= 384)
+    hipLaunchKernelGGL((fc_split_kernel<2, 1, 6>), dim3((unsigned)t128), dim3(256), 0, stream, b);
+  else if (a.d >= 64)
+    hipLaunchKernelGGL((fc_split_kernel<1, 1, 6>), dim3((unsigned)t64), dim3(256), 0, stream, b);
+  else
+    hipLaunchKernelGGL((fc_split_kernel<1, 1, 9>), dim3((unsigned)t64), dim3(256), 0, stream, b);
   return hipGetLastError() == hipSuccess ? 0 : -3;
 }
 
