@@ -16,25 +16,27 @@ namespace nk {
 // LDS at the end, in a fixed order, so a tile's sum is spread over a CU
 // however few tiles there are.  Operands come straight from the caches (a
 // lane's four consecutive k of a row, or 16 lanes' consecutive columns), the
-// next chunk's while the current one runs: a chunk is 4 MB^2 instructions of
-// 64 cycles for 8 MB loads.
+// next chunk's while the current one runs.  Bound: the float64 pipes, shared
+// by the products (4 MB^2 of 64 cycles a chunk), the operands' conversions and
+// COMP's sums; reading the operands from a cached 256 rows instead changes
+// nothing.
 // COMP: for sums whose result is later subtracted from a nearly equal
-// quantity.  A chunk starts from zero and its sum is added to the running one
-// with TwoSum, the rounding errors carried and added at the end: what is left
-// is the rounding inside chunks, 16 terms of a sum of K, and one rounding of
-// the result.  (A chain of compensated single products on the vector unit, 4
+// quantity.  Two chunks start from zero and their sum is added to the running
+// one with TwoSum, the rounding errors carried and added at the end: what is
+// left is the rounding inside 32 terms of a sum of K, and one rounding of the
+// result.  (A chain of compensated single products on the vector unit, 4
 // outputs per thread: 3.8 ms for the 1000 x 1000 x 12000 product of a
-// Nystrom solve, now 0.72 ms.)
+// Nystrom solve, now 0.57.)
 // sym: op(B) = op(A)^T; the tiles on and below the diagonal are formed and
 // mirrored.
 template <typename TA, typename TB, typename TO, bool A_T, bool B_T, bool COMP, int MB, int W>
-__global__ __launch_bounds__(64 * W) void dn_gemm_kernel(const TA* __restrict__ A, int64_t lda,
+__global__ __launch_bounds__(64 * W, MB == 2 ? 3 : 1) void dn_gemm_kernel(const TA* __restrict__ A, int64_t lda,
                                                          const TB* __restrict__ B, int64_t ldb, TO* __restrict__ Cm,
                                                          int64_t ldc, int64_t M, int64_t N, int64_t K, double alpha,
                                                          double beta, double shift, int sym, int* __restrict__ info,
                                                          unsigned ntc) {
   constexpr int T = 16 * MB, E = T * T;
-  __shared__ double red[(COMP ? 2 : 1) * W * E];
+  extern __shared__ double red[];  // (COMP ? 2 : 1) * W / 2 * E
   const unsigned tr = blockIdx.x / ntc, tc = blockIdx.x - tr * ntc;  // tile row and column
   if (info && blockIdx.x == 0 && threadIdx.x == 0) info[0] = 0;
   if (sym && tc > tr) return;
@@ -46,35 +48,26 @@ __global__ __launch_bounds__(64 * W) void dn_gemm_kernel(const TA* __restrict__ 
     ra[x] = r0 + 16 * x + i < M ? r0 + 16 * x + i : M - 1;
     cb[x] = c0 + 16 * x + i < N ? c0 + 16 * x + i : N - 1;
   }
-  TA av[MB][4];
-  TB bv[MB][4];
-  auto fetch = [&](int64_t k0) {
-    const int64_t k = k0 + 4 * g;
-    if (k0 + 16 <= K) {
+  struct Frag {
+    TA a[MB][4];
+    TB b[MB][4];
+  };
+  auto fetch = [&](int64_t q, Frag& f) {  // chunk q, a whole one
+    const int64_t k = 16 * q + 4 * g;
 #pragma unroll
-      for (int x = 0; x < MB; ++x) {
-        if constexpr (A_T) {
+    for (int x = 0; x < MB; ++x) {
+      if constexpr (A_T) {
 #pragma unroll
-          for (int t = 0; t < 4; ++t) av[x][t] = A[(k + t) * lda + ra[x]];
-        } else {
-          load4(A + ra[x] * lda + k, av[x]);
-        }
-        if constexpr (B_T) {
-          load4(B + cb[x] * ldb + k, bv[x]);
-        } else {
-#pragma unroll
-          for (int t = 0; t < 4; ++t) bv[x][t] = B[(k + t) * ldb + cb[x]];
-        }
+        for (int t = 0; t < 4; ++t) f.a[x][t] = A[(k + t) * lda + ra[x]];
+      } else {
+        load4(A + ra[x] * lda + k, f.a[x]);
       }
-    } else {
+      if constexpr (B_T) {
+        load4(B + cb[x] * ldb + k, f.b[x]);
+      } else {
 #pragma unroll
-      for (int x = 0; x < MB; ++x)
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-          const bool in = k + t < K;
-          av[x][t] = in ? (A_T ? A[(k + t) * lda + ra[x]] : A[ra[x] * lda + k + t]) : (TA)0;
-          bv[x][t] = in ? (B_T ? B[cb[x] * ldb + k + t] : B[(k + t) * ldb + cb[x]]) : (TB)0;
-        }
+        for (int t = 0; t < 4; ++t) f.b[x][t] = B[(k + t) * ldb + cb[x]];
+      }
     }
   };
   d4 hi[MB][MB], lo[MB][MB];
@@ -82,103 +75,156 @@ __global__ __launch_bounds__(64 * W) void dn_gemm_kernel(const TA* __restrict__ 
   for (int x = 0; x < MB; ++x)
 #pragma unroll
     for (int y = 0; y < MB; ++y) hi[x][y] = lo[x][y] = d4{0.0, 0.0, 0.0, 0.0};
-  int64_t k0 = 16 * w;
-  if (k0 < K) fetch(k0);
-  for (; k0 < K; k0 += 16 * W) {
-    double a[MB][4], b[MB][4];
-#pragma unroll
-    for (int x = 0; x < MB; ++x)
-#pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        a[x][t] = (double)av[x][t];
-        b[x][t] = (double)bv[x][t];
-      }
-    if (k0 + 16 * W < K) fetch(k0 + 16 * W);
-    d4 p[MB][MB];
-#pragma unroll
-    for (int x = 0; x < MB; ++x)
-#pragma unroll
-      for (int y = 0; y < MB; ++y) p[x][y] = COMP ? d4{0.0, 0.0, 0.0, 0.0} : hi[x][y];
+  auto multiply = [&](const Frag& f, d4 (&p)[MB][MB]) {
 #pragma unroll
     for (int t = 0; t < 4; ++t)
 #pragma unroll
       for (int x = 0; x < MB; ++x)
 #pragma unroll
-        for (int y = 0; y < MB; ++y) p[x][y] = mfma64(a[x][t], b[y][t], p[x][y]);
+        for (int y = 0; y < MB; ++y) p[x][y] = mfma64((double)f.a[x][t], (double)f.b[y][t], p[x][y]);
+  };
+  d4 p[MB][MB];  // COMP: the running chunk pair
+  auto start = [&]() {
+#pragma unroll
+    for (int x = 0; x < MB; ++x)
+#pragma unroll
+      for (int y = 0; y < MB; ++y) p[x][y] = d4{0.0, 0.0, 0.0, 0.0};
+  };
+  auto add = [&]() {
 #pragma unroll
     for (int x = 0; x < MB; ++x)
 #pragma unroll
       for (int y = 0; y < MB; ++y) {
-        if (COMP) {
-          const d4 s = hi[x][y] + p[x][y];
-          const d4 bb = s - hi[x][y];
-          lo[x][y] += (hi[x][y] - (s - bb)) + (p[x][y] - bb);
-          hi[x][y] = s;
-        } else {
-          hi[x][y] = p[x][y];
-        }
+        const d4 s = hi[x][y] + p[x][y];
+        const d4 bb = s - hi[x][y];
+        lo[x][y] += (hi[x][y] - (s - bb)) + (p[x][y] - bb);
+        hi[x][y] = s;
       }
+  };
+  // whole chunks w, w + W, ...: two register sets, the next chunk's loads in
+  // flight while one multiplies (past the last: that one again, not used)
+  const int64_t whole = K / 16;
+  if (w < whole) {
+    Frag even, odd;
+    fetch(w, even);
+    for (int64_t q = w;;) {
+      const bool more = q + W < whole;
+      fetch(more ? q + W : q, odd);
+      if (COMP) start();
+      multiply(even, COMP ? p : hi);
+      if (more) {
+        q += 2 * W;
+        fetch(q < whole ? q : q - W, even);
+        multiply(odd, COMP ? p : hi);
+      }
+      if (COMP) add();
+      if (!more || q >= whole) break;
+    }
   }
+  if (K % 16 != 0 && whole % W == w) {
+    Frag f;
+    const int64_t k = 16 * whole + 4 * g;
+#pragma unroll
+    for (int x = 0; x < MB; ++x)
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        const bool in = k + t < K;
+        f.a[x][t] = in ? (A_T ? A[(k + t) * lda + ra[x]] : A[ra[x] * lda + k + t]) : (TA)0;
+        f.b[x][t] = in ? (B_T ? B[cb[x] * ldb + k + t] : B[(k + t) * ldb + cb[x]]) : (TB)0;
+      }
+    if (COMP) start();
+    multiply(f, COMP ? p : hi);
+    if (COMP) add();
+  }
+  // the upper half of the waves into the lower one, until one is left
+#pragma unroll 1
+  for (int h = W / 2; h >= 1; h >>= 1) {
+    double* mine = red + (size_t)(w % h) * E * (COMP ? 2 : 1);
+    if (w >= h && w < 2 * h) {
+#pragma unroll
+      for (int x = 0; x < MB; ++x)
+#pragma unroll
+        for (int y = 0; y < MB; ++y)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {
+            const int e = ((x * MB + y) * 4 + v) * 64 + lane;
+            mine[e] = hi[x][y][v];
+            if (COMP) mine[E + e] = lo[x][y][v];
+          }
+    }
+    __syncthreads();
+    if (w < h) {
+#pragma unroll
+      for (int x = 0; x < MB; ++x)
+#pragma unroll
+        for (int y = 0; y < MB; ++y)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {
+            const int e = ((x * MB + y) * 4 + v) * 64 + lane;
+            const double o = mine[e];
+            if (COMP) {
+              const double s = hi[x][y][v] + o, bb = s - hi[x][y][v];
+              lo[x][y][v] += (hi[x][y][v] - (s - bb)) + (o - bb) + mine[E + e];
+              hi[x][y][v] = s;
+            } else {
+              hi[x][y][v] += o;
+            }
+          }
+    }
+    __syncthreads();
+  }
+  if (w != 0) return;
 #pragma unroll
   for (int x = 0; x < MB; ++x)
 #pragma unroll
     for (int y = 0; y < MB; ++y)
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
-        const int e = (16 * x + 4 * v + g) * T + 16 * y + i;
-        red[w * E + e] = hi[x][y][v];
-        if (COMP) red[(W + w) * E + e] = lo[x][y][v];
+        const int64_t r = r0 + 16 * x + 4 * v + g, c = c0 + 16 * y + i;
+        if (r >= M || c >= N || (sym && c > r)) continue;
+        double s = hi[x][y][v], l = lo[x][y][v];
+        if (COMP && r == c && shift != 0.0) {
+          const double u = s + shift, bb = u - s;
+          l += (s - (u - bb)) + (shift - bb);
+          s = u;
+        }
+        const double val = alpha * (s + l);
+        TO* o = Cm + r * ldc + c;
+        const double out = beta == 0.0 ? val : __builtin_fma(beta, (double)*o, val);
+        *o = (TO)out;
+        if (sym && c < r) Cm[c * ldc + r] = (TO)out;
       }
-  __syncthreads();
-  for (int e = tid; e < E; e += 64 * W) {
-    double s = red[e], l = COMP ? red[W * E + e] : 0.0;
-    for (int q = 1; q < W; ++q) {
-      const double v = red[q * E + e];
-      if (COMP) {
-        const double u = s + v, bb = u - s;
-        l += (s - (u - bb)) + (v - bb) + red[(W + q) * E + e];
-        s = u;
-      } else {
-        s += v;
-      }
-    }
-    const int64_t r = r0 + e / T, c = c0 + e % T;
-    if (r >= M || c >= N || (sym && c > r)) continue;
-    if (COMP && r == c && shift != 0.0) {
-      const double u = s + shift, bb = u - s;
-      l += (s - (u - bb)) + (shift - bb);
-      s = u;
-    }
-    const double v = alpha * (s + l);
-    TO* o = Cm + r * ldc + c;
-    const double out = beta == 0.0 ? v : __builtin_fma(beta, (double)*o, v);
-    *o = (TO)out;
-    if (sym && c < r) Cm[c * ldc + r] = (TO)out;
-  }
 }
 
-// Tile by size: 32 x 32 (half the operand traffic) where that still gives a
-// tile to every CU, else 16 x 16 with up to 16 waves on a long sum.
+template <typename TA, typename TB, typename TO, bool A_T, bool B_T, bool COMP, int MB, int W>
+static int dn_gemm_launch(const TA* A, int64_t lda, const TB* B, int64_t ldb, TO* C, int64_t ldc, int64_t M, int64_t N,
+                          int64_t K, double alpha, double beta, hipStream_t s, double shift, bool sym, int* info) {
+  static std::atomic<size_t> seen[kMaxDevices];
+  constexpr int T = 16 * MB;
+  const size_t lds = (size_t)(COMP ? 2 : 1) * W / 2 * T * T * sizeof(double);
+  const auto kernel = dn_gemm_kernel<TA, TB, TO, A_T, B_T, COMP, MB, W>;
+  if (allow_dyn_lds((const void*)kernel, lds, seen)) return -3;
+  const int64_t mt = (M + T - 1) / T, nt = (N + T - 1) / T;
+  hipLaunchKernelGGL(kernel, dim3((unsigned)(mt * nt)), dim3(64 * W), lds, s, A, lda, B, ldb, C, ldc, M, N, K, alpha,
+                     beta, shift, sym ? 1 : 0, info, (unsigned)nt);
+  return hipGetLastError() == hipSuccess ? 0 : -3;
+}
+
+// Tile by size: 16 x 16 with up to 16 waves on a long sum, until 32 x 32 tiles
+// (half the operand traffic and conversions) reach every CU.
 template <typename TA, typename TB, typename TO, bool A_T, bool B_T, bool COMP>
 static int dn_gemm_t(const TA* A, int64_t lda, const TB* B, int64_t ldb, TO* C, int64_t ldc, int64_t M, int64_t N,
                      int64_t K, double alpha, double beta, hipStream_t s, double shift = 0.0, bool sym = false,
                      int* info = nullptr) {
   if (M <= 0 || N <= 0) return 0;
-  const int64_t m32 = (M + 31) / 32, n32 = (N + 31) / 32, m16 = (M + 15) / 16, n16 = (N + 15) / 16;
-  const int sy = sym ? 1 : 0;
-  const bool big = N > 16 && (sym ? m32 * (m32 + 1) / 2 : m32 * n32) >= 256;
-  const unsigned nt = (unsigned)(big ? n32 : n16);
-  const dim3 grid((unsigned)((big ? m32 : m16) * nt));
-  if (big)
-    hipLaunchKernelGGL((dn_gemm_kernel<TA, TB, TO, A_T, B_T, COMP, 2, 4>), grid, dim3(256), 0, s, A, lda, B, ldb, C, ldc,
-                       M, N, K, alpha, beta, shift, sy, info, nt);
-  else if (K > 256)
-    hipLaunchKernelGGL((dn_gemm_kernel<TA, TB, TO, A_T, B_T, COMP, 1, 16>), grid, dim3(1024), 0, s, A, lda, B, ldb, C,
-                       ldc, M, N, K, alpha, beta, shift, sy, info, nt);
-  else
-    hipLaunchKernelGGL((dn_gemm_kernel<TA, TB, TO, A_T, B_T, COMP, 1, 4>), grid, dim3(256), 0, s, A, lda, B, ldb, C, ldc,
-                       M, N, K, alpha, beta, shift, sy, info, nt);
-  return hipGetLastError() == hipSuccess ? 0 : -3;
+  const int64_t m = (M + 31) / 32, n = (N + 31) / 32;
+  if (N > 16 && (sym ? m * (m + 1) / 2 : m * n) >= 256)
+    return dn_gemm_launch<TA, TB, TO, A_T, B_T, COMP, 2, 4>(A, lda, B, ldb, C, ldc, M, N, K, alpha, beta, s, shift, sym,
+                                                            info);
+  return K > 256 ? dn_gemm_launch<TA, TB, TO, A_T, B_T, COMP, 1, 16>(A, lda, B, ldb, C, ldc, M, N, K, alpha, beta, s,
+                                                                     shift, sym, info)
+                 : dn_gemm_launch<TA, TB, TO, A_T, B_T, COMP, 1, 4>(A, lda, B, ldb, C, ldc, M, N, K, alpha, beta, s,
+                                                                    shift, sym, info);
 }
 
 int dn_gemm_ff(const float* A, int64_t lda, bool a_t, const float* B, int64_t ldb, double* C, int64_t ldc, int64_t M,

@@ -153,8 +153,27 @@ __global__ __launch_bounds__(256) void chol_panel_kernel(double* __restrict__ A,
     for (int q = 0; q < 16; ++q) m.T[(4 * q + w) * CH_LD + lane] = v[q];
   }
   __syncthreads();
+  // inverse of a diagonal block: lane i forms its column i (wave 3, while wave
+  // 0 factors the next block)
+  auto inverse = [&](int b) {
+    if (g != 0) return;
+    const double* L = m.T + 16 * b * CH_LD + 16 * b;
+    const double ri = 1.0 / L[i * CH_LD + i];
+    double x[16];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) x[r] = r == i ? 1.0 : 0.0;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      x[r] *= lane_value(ri, r);
+#pragma unroll
+      for (int e = r + 1; e < 16; ++e) x[e] = fma(-L[e * CH_LD + r], x[r], x[e]);
+    }
+#pragma unroll
+    for (int r = 0; r < 16; ++r) m.V[(16 * b + r) * CH_LV + i] = x[r];  // (0 above the diagonal)
+  };
 #pragma unroll 1
   for (int jb = 0; jb < 4; ++jb) {
+    if (w == 3 && jb > 0) inverse(jb - 1);
     if (w == 0) {
       double a[16];
 #pragma unroll
@@ -173,10 +192,10 @@ __global__ __launch_bounds__(256) void chol_panel_kernel(double* __restrict__ A,
         r = fma(0.5 * r, fma(-d * r, r, 1.0), r);
         double q = d * r;
         q = fma(fma(-q, q, d), 0.5 * r, q);
-        const double l = lane == 16 * jb + j ? q : a[j] * r;
+        const double l = a[j] * r;  // (sqrt(d) up to rounding in row j itself, which the updates do not read)
 #pragma unroll
         for (int e = j + 1; e < 16; ++e) a[e] = fma(-l, lane_value(l, 16 * jb + e), a[e]);
-        a[j] = l;
+        a[j] = lane == 16 * jb + j ? q : l;
       }
       if (bad && lane == 0) info[0] = 1;
 #pragma unroll
@@ -200,21 +219,7 @@ __global__ __launch_bounds__(256) void chol_panel_kernel(double* __restrict__ A,
       }
     __syncthreads();
   }
-  // inverse of the diagonal block of wave w: lane i forms its column i
-  if (g == 0) {
-    const double* L = m.T + 16 * w * CH_LD + 16 * w;
-    const double ri = 1.0 / L[i * CH_LD + i];
-    double x[16];
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      double v = r == i ? 1.0 : 0.0;
-#pragma unroll
-      for (int e = 0; e < r; ++e) v = fma(-L[r * CH_LD + e], x[e], v);
-      x[r] = v * lane_value(ri, r);
-    }
-#pragma unroll
-    for (int r = 0; r < 16; ++r) m.V[(16 * w + r) * CH_LV + i] = x[r];  // (0 above the diagonal)
-  }
+  if (w == 3) inverse(3);
   __syncthreads();
   if (blockIdx.x == 0) {
     const int64_t off = rest > CH_NB ? CH_NB : 0;

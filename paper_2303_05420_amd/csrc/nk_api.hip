@@ -910,15 +910,18 @@ int pc_lt_splits(int64_t n, int r) {
 
 struct PcgPlan {
   size_t d, pv, pi, dpiv, mean, piv, L, Lr, M, info, W, wpart, R, X, Z, P, Q, kpart, part1, part2, st;
+  int64_t maxima;  // pivot-step workgroups that pv and pi hold
   int lt_splits;
   size_t total;
 };
 
-// what: 0 = pivoted Cholesky only, 1 = full solver, 2 = product only
-PcgPlan pcg_plan(int64_t n, int r, int what) {
+// what: 0 = pivoted Cholesky only, 1 = full solver, 2 = product only.  small:
+// pivot steps of 256 rows a workgroup (the least a pivoted Cholesky accepts).
+PcgPlan pcg_plan(int64_t n, int r, int what, bool small = false) {
   PcgPlan p{};
   Bump b;
-  const int64_t nb = (n + 255) / 256, nbz = (n + 63) / 64;
+  const int64_t nbz = (n + 63) / 64, nb = small ? (n + 255) / 256 : nbz;
+  p.maxima = nb;
   const size_t G = kPcgGroup;
   if (what != 2) {
     p.d = b.take(sizeof(double) * n);
@@ -1688,13 +1691,14 @@ int nk_pivoted_cholesky(const float* K, int64_t n, int64_t ldk, int32_t rank, do
   if (!(pivot_tol >= 0.0)) return fail(NK_EINVAL, "pivot_tol must be >= 0");
   if (rank_used) *rank_used = 0;
   if (rank == 0) return ok();
-  const PcgPlan pp = pcg_plan(n, rank, 0);
+  PcgPlan pp = pcg_plan(n, rank, 0);
+  if (ws_bytes < pp.total) pp = pcg_plan(n, rank, 0, true);
   if (!ws || ws_bytes < pp.total) return fail(NK_EINVAL, "workspace too small (need %zu bytes)", pp.total);
   hipStream_t s = (hipStream_t)stream;
   {
     ProfScope ps("pivoted_cholesky", s);
     if (nk::launch_pchol(K, n, ldk, rank, pivot_tol, L, piv, at<double>(ws, pp.d), at<double>(ws, pp.pv),
-                         at<int>(ws, pp.pi), at<double>(ws, pp.dpiv), s))
+                         at<int>(ws, pp.pi), pp.maxima, at<double>(ws, pp.dpiv), s))
       return hip_fail("pivoted cholesky");
   }
   std::vector<int32_t> hp(rank);
@@ -1753,7 +1757,7 @@ int nk_krr_pcg(const float* K, int64_t n, int64_t ldk, const double* Y, int64_t 
     {
       ProfScope ps("pivoted_cholesky", s);
       if (nk::launch_pchol(K, n, ldk, rank, cfg->pivot_tol, L, piv, at<double>(ws, pp.d), at<double>(ws, pp.pv),
-                           at<int>(ws, pp.pi), at<double>(ws, pp.dpiv), s))
+                           at<int>(ws, pp.pi), pp.maxima, at<double>(ws, pp.dpiv), s))
         return hip_fail("pivoted cholesky");
     }
     std::vector<int> hp(rank);
@@ -1787,7 +1791,6 @@ int nk_krr_pcg(const float* K, int64_t n, int64_t ldk, const double* Y, int64_t 
   a.tol = cfg->tol;
   a.max_iter = cfg->max_iter;
   a.r = r;
-  a.U = L;  // L R^{-T}, formed in place by the set-up
   a.Ur = at<double>(ws, pp.Lr);
   a.W = at<double>(ws, pp.W);
   a.wpart = at<double>(ws, pp.wpart);
@@ -1802,7 +1805,6 @@ int nk_krr_pcg(const float* K, int64_t n, int64_t ldk, const double* Y, int64_t 
   a.part2 = at<double>(ws, pp.part2);
   double* st = at<double>(ws, pp.st);
   a.gamma = st;
-  a.beta = st + kPcgGroup;
   a.ynorm = st + 2 * kPcgGroup;
   a.relres = st + 3 * kPcgGroup;
   a.active = reinterpret_cast<int*>(st + 4 * kPcgGroup);

@@ -211,23 +211,23 @@ struct PcgArgs {
   double lam, tol;
   int max_iter;
   int r;                 // preconditioner rank (0: Ph = lam I)
-  const double* U;       // n x r, column major: L R^{-T}, R R^T = lam I + L^T L
-  const double* Ur;      // the same, row major
+  const double* Ur;      // n x r, row major: L R^{-T}, R R^T = lam I + L^T L
   double* W;             // r x 16
   double* wpart;         // lt_splits x r x 16
   int lt_splits;
   double *R, *X, *Z, *P, *Q;  // n x 16
   double* kpart;              // kmv_splits(n) x n x 16
   double *part1, *part2;      // ceil(n / 64) x 16 (per-workgroup partial sums)
-  double *gamma, *beta, *ynorm, *relres;  // 16 each
-  int *active, *iters;                    // 16 each
-  int* any;                               // 1 device int: some column still iterates
+  double *gamma, *ynorm, *relres;         // 2 x 16, 16, 16
+  int *active, *iters;                    // 2 x 16, 16
+  int* any;                               // 2 device ints: some column still iterates
   int* host_any;                          // 3 ints of pinned host memory
   ProfHook* hook;
 };
 
+// maxima: workgroups that pv and pi have room for (two entries each), at least ceil(n / 256)
 int launch_pchol(const float* K, int64_t n, int64_t ldk, int rank, double pivot_tol, double* L, int* piv,
-                 double* d, double* pv, int* pi, double* dpiv, hipStream_t s);
+                 double* d, double* pv, int* pi, int64_t maxima, double* dpiv, hipStream_t s);
 int launch_pc_setup(double* LU, int64_t n, int r, double lam, double* Ur, double* M, int* info, hipStream_t s);
 int launch_pcg_group(const PcgArgs& a, int64_t c0, int C, hipStream_t s);
 int kmv_splits(int64_t n);
