@@ -798,7 +798,7 @@ int check_cv(const nk_cv_cfg* c) {
 }
 
 struct CvPlan {
-  size_t tab1, tab2, d1, d2, total;
+  size_t tab1, tab2, total;
 };
 
 CvPlan cv_plan(const nk_cv_cfg* c, int64_t n1, int64_t n2, bool sym) {
@@ -806,11 +806,7 @@ CvPlan cv_plan(const nk_cv_cfg* c, int64_t n1, int64_t n2, bool sym) {
   Bump b;
   const size_t per = (size_t)c->depth * c->H * c->W * sizeof(float2);
   p.tab1 = b.take(per * (size_t)std::max<int64_t>(n1, 1));
-  p.d1 = b.take(sizeof(float) * (size_t)std::max<int64_t>(n1, 1));
-  if (!sym) {
-    p.tab2 = b.take(per * (size_t)std::max<int64_t>(n2, 1));
-    p.d2 = b.take(sizeof(float) * (size_t)std::max<int64_t>(n2, 1));
-  }
+  if (!sym) p.tab2 = b.take(per * (size_t)std::max<int64_t>(n2, 1));
   p.total = b.off + 256;
   return p;
 }
@@ -1665,11 +1661,8 @@ int nk_cv_nngp(const float* x1, int64_t n1, const float* x2, int64_t n2, const n
   float2* t2 = sym ? t1 : at<float2>(ws, cp.tab2);
   {
     ProfScope ps("cv_prepare", s);
-    if (nk::launch_cv_prepare(x1, n1, N, cfg->C, cfg->depth, cfg->sigma_w2, cfg->sigma_b2, t1,
-                              at<float>(ws, cp.d1), s))
-      return hip_fail("cv prepare");
-    if (!sym && nk::launch_cv_prepare(x2, n2, N, cfg->C, cfg->depth, cfg->sigma_w2, cfg->sigma_b2, t2,
-                                      at<float>(ws, cp.d2), s))
+    if (nk::launch_cv_prepare(x1, n1, t1, sym ? nullptr : x2, n2, t2, N, cfg->C, cfg->depth, cfg->sigma_w2,
+                              cfg->sigma_b2, s))
       return hip_fail("cv prepare");
   }
   const float seed_scale = (float)((double)cfg->sigma_w2 / (9.0 * cfg->C));

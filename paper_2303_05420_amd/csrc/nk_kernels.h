@@ -258,10 +258,10 @@ int dn_residual_scale(const float* Y, int64_t ldy, int64_t n, int64_t c, double 
 int dn_cast(const double* in, int64_t rows, int64_t cols, float* out, int64_t ldo, hipStream_t s);
 int dn_axpby(double* D, const double* E, int64_t n, double alpha, double beta, hipStream_t s);
 
-// CNN-VEC NNGP (cv.hip): per-image tables [img][layer][pixel] float2 and
-// K(x, x), then one N-lane segment per pair.
-int launch_cv_prepare(const float* x, int64_t n, int N, int C, int D, double sw2, double sb2, float2* tab,
-                      float* kdiag, hipStream_t s);
+// CNN-VEC NNGP (cv.hip): per-image tables [img][layer][pixel] float2 of both
+// sets (x2 NULL: one set), then one N-lane segment per pair.
+int launch_cv_prepare(const float* x1, int64_t n1, float2* tab1, const float* x2, int64_t n2, float2* tab2, int N, int C,
+                      int D, double sw2, double sb2, hipStream_t s);
 int launch_cv_pairs(int N, const float* x1, const float* x2, int64_t n1, int64_t n2, int sym, int T, int C, int D,
                     const float2* tab1, const float2* tab2, float* K, int64_t ldk, float sb2, float seed_scale,
                     hipStream_t s);
