@@ -61,6 +61,7 @@ struct StageArgs {
   const TileDesc* tiles;  // batched pass: tile table (NULL: one block given by n1, n2, x1, x2, K)
   int ntiles;
   int persist;     // > 0: grid of `persist` workgroups looping over the chunk
+  int parts;       // workgroups that share a pair's sweep (32x32 pooling stage, set by its launcher)
   const float* x1;
   const float* x2;
   const float2* tab1;

@@ -298,10 +298,13 @@ __device__ __forceinline__ void s32_consume(const StageArgs& args, const S32Ctx&
 // One ky step: the tile's layers, the y part of the pool, and on the steps
 // that complete a coarse row (E: that emit's number, counted over the
 // workgroup's life from 1) the x part and the write of that row.
-template <int PAR, bool SEED, bool BIAS, bool C4>
+// SPLIT: a part of a sweep shared by several workgroups.  The odd step that
+// begins it (`begins`) only carries its odd rows on; the same step at the sweep's end (ky =
+// 33 mod 32 = 1) completes coarse row 0 with its even rows.
+template <int PAR, bool SEED, bool BIAS, bool C4, bool SPLIT>
 __device__ __forceinline__ void s32_step(const StageArgs& args, const S32Ctx& c, int ky, int E, float (&acc0)[kH],
                                          float (&acc1)[kH], float (&wrap0)[kH], float (&wrap1)[kH], bool valid,
-                                         int64_t pl) {
+                                         int64_t pl, bool begins) {
   const int seam = ky == 0 ? -1 : kN - ky;
   const int kx = c.seg;
   float A0[kN], A1[kN];
@@ -356,6 +359,30 @@ __device__ __forceinline__ void s32_step(const StageArgs& args, const S32Ctx& c,
 
   // y part of the pool (coarse row I gets fine rows 2I, 2I + 1 of the tiles
   // ky = 2K and the even rows of ky = 2K + 1, odd rows of ky = 2K - 1)
+  if constexpr (SPLIT) {
+    if constexpr (PAR == 0) {
+#pragma unroll
+      for (int I = 0; I < kH; ++I) {
+        acc0[I] = acc0[I] + (A0[2 * I] + A0[2 * I + 1]);
+        acc1[I] = acc1[I] + (A1[2 * I] + A1[2 * I + 1]);
+      }
+    } else {
+      if (!begins) {
+#pragma unroll
+        for (int I = 0; I < kH; ++I) {
+          acc0[I] = acc0[I] + A0[2 * I];
+          acc1[I] = acc1[I] + A1[2 * I];
+        }
+        s32_emit(args, c, acc0, acc1, A0, A1, ((ky - 1) & (kN - 1)) >> 1, E, valid, pl);
+      }
+#pragma unroll
+      for (int I = 0; I < kH; ++I) {
+        acc0[I] = A0[2 * I + 1];
+        acc1[I] = A1[2 * I + 1];
+      }
+    }
+    return;
+  }
   const bool emit = ky != 1 && (ky == 0 || (ky & 1));
   if (ky == 1) {
 #pragma unroll
@@ -395,7 +422,7 @@ __device__ __forceinline__ void s32_step(const StageArgs& args, const S32Ctx& c,
   }
 }
 
-template <bool SEED, bool BIAS, bool C4>
+template <bool SEED, bool BIAS, bool C4, bool SPLIT>
 __global__ __launch_bounds__(kThreads) void stage32_kernel(const StageArgs args) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
   __shared__ int64_t s_t1, s_t2, s_off, s_offm;
@@ -438,13 +465,16 @@ __global__ __launch_bounds__(kThreads) void stage32_kernel(const StageArgs args)
   float4* i1w = const_cast<float4*>(c.img1);
   float4* i2w = const_cast<float4*>(c.img2);
 
-  const int64_t nunits = args.np;
+  // SPLIT: `parts` workgroups share the sweep of a pair (s32_parts)
+  const int parts = SPLIT ? args.parts : 1;
+  const int64_t nunits = args.np * parts;
   int E0 = 0;  // emits of the units before this one
   int64_t unit, ustep, uend;
   unit_range(nunits, args.persist, &unit, &ustep, &uend);
   for (; unit < uend; unit += ustep) {
     if (tid == 0) {
-      int64_t pl = unit < args.np ? unit : args.np - 1;
+      int64_t pl = SPLIT ? unit / parts : unit;
+      if (pl >= args.np) pl = args.np - 1;
       resolve_pair(args, args.p0 + pl, args.img_floats, &s_t1, &s_t2, &s_x1, &s_x2, &s_k, &s_off, &s_offm, &s_same,
                    false);
     }
@@ -491,22 +521,41 @@ __global__ __launch_bounds__(kThreads) void stage32_kernel(const StageArgs args)
     }
     __syncthreads();
 
-    const int64_t pl = unit;
+    const int64_t pl = SPLIT ? unit / parts : unit;
     const bool valid = pl < args.np;
     const int64_t plc = valid ? pl : args.np - 1;
     c.inp = SEED ? nullptr : args.in + plc * (int64_t)kN * kN * kN * kN;
     float acc0[kH], acc1[kH], wrap0[kH], wrap1[kH];
 #pragma unroll
     for (int I = 0; I < kH; ++I) acc0[I] = acc1[I] = wrap0[I] = wrap1[I] = 0.f;
+    if constexpr (SPLIT) {
+      // Coarse rows t0 + 1 .. t1 (16: row 0): the odd rows of ky = 2 t0 + 1,
+      // then per row t the tiles ky = 2t and 2t + 1 (mod 32), summed in the
+      // order of the whole sweep, so a row does not depend on the split.
+      const int part = (int)(unit - pl * parts);
+      const int t0 = part * kH / parts, t1 = (part + 1) * kH / parts;
+#pragma unroll 1
+      for (int t = t0; t <= t1; ++t) {
+        s32_step<1, SEED, BIAS, C4, true>(args, c, (2 * t + 1) & (kN - 1), t - t0, acc0, acc1, wrap0, wrap1, valid, pl,
+                                          t == t0);
+        if (t > t0 + 1) s32_consume(args, c, t - 1, t - 1 - t0, valid, pl);
+        if (t < t1)
+          s32_step<0, SEED, BIAS, C4, true>(args, c, (2 * t + 2) & (kN - 1), 0, acc0, acc1, wrap0, wrap1, valid, pl,
+                                            false);
+      }
+      s32_consume(args, c, t1 & (kH - 1), t1 - t0, valid, pl);
+      return;  // (one unit per workgroup)
+    }
     // ky = 1, 2, ..., 31, 0 in pairs (odd ky: seam row 32 - ky odd; even ky:
     // even or none).  Emits: ky = 2t + 1 (t >= 1) is emit E0 + t of coarse
     // row t, ky = 0 emit E0 + 16 of coarse row 0; each is completed after
     // the next one.
 #pragma unroll 1
     for (int t = 0; t < kN / 2; ++t) {
-      s32_step<1, SEED, BIAS, C4>(args, c, 2 * t + 1, E0 + t, acc0, acc1, wrap0, wrap1, valid, pl);
+      s32_step<1, SEED, BIAS, C4, false>(args, c, 2 * t + 1, E0 + t, acc0, acc1, wrap0, wrap1, valid, pl, false);
       if (t >= 2) s32_consume(args, c, t - 1, E0 + t - 1, valid, pl);
-      s32_step<0, SEED, BIAS, C4>(args, c, (2 * t + 2) & (kN - 1), E0 + kH, acc0, acc1, wrap0, wrap1, valid, pl);
+      s32_step<0, SEED, BIAS, C4, false>(args, c, (2 * t + 2) & (kN - 1), E0 + kH, acc0, acc1, wrap0, wrap1, valid, pl,
+                                         false);
     }
     s32_consume(args, c, kH - 1, E0 + kH - 1, valid, pl);
     s32_consume(args, c, 0, E0 + kH, valid, pl);
@@ -515,29 +564,67 @@ __global__ __launch_bounds__(kThreads) void stage32_kernel(const StageArgs args)
   }
 }
 
-template <bool SEED, bool BIAS, bool C4>
-int s32_attr(size_t lds) {
-  static std::atomic<size_t> seen[kMaxDevices];
-  return allow_dyn_lds((const void*)stage32_kernel<SEED, BIAS, C4>, lds, seen);
+// Workgroups that share the sweep of a pair.  A workgroup takes one CU (or half
+// of one) for the sweep's 32 tiles, so a chunk of fewer pairs than the chip
+// holds leaves CUs idle; a part of 16 / P coarse rows costs 32 / P tiles, one
+// more to begin with, and about two tiles' time to fill LDS.  P is the power of
+// two with the fewest rounds x tiles (from four rounds on the last one no longer
+// matters).  Myrtle-10 at 32x32x3, 2 x 60 pairs, whole call: 548 us with a
+// workgroup a pair, 387 us with two.
+inline int s32_parts(int64_t np, int64_t resident) {
+  int best = 1;
+  int64_t least = 0;
+  for (int P = 1; P <= kH; P *= 2) {
+    const int64_t cost = (np * P + resident - 1) / resident * (kN / P + (P > 1 ? 3 : 2));
+    if (P == 1 || cost < least) {
+      least = cost;
+      best = P;
+    }
+  }
+  return best;
 }
 
+template <bool SEED, bool BIAS, bool C4, bool SPLIT>
+int s32_attr(size_t lds) {
+  static std::atomic<size_t> seen[kMaxDevices];
+  return allow_dyn_lds((const void*)stage32_kernel<SEED, BIAS, C4, SPLIT>, lds, seen);
+}
+
+// Workgroups a CU holds (by LDS, but for the smallest depths by waves).
 template <bool SEED, bool BIAS, bool C4>
-int s32_launch(const StageArgs& a, hipStream_t stream) {
+int s32_occ(int D) {
+  const size_t lds = s32_lds_bytes(D, SEED);
+  if (s32_attr<SEED, BIAS, C4, false>(lds)) return -3;
+  int nb = 0;
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, stage32_kernel<SEED, BIAS, C4, false>, kThreads, lds) !=
+      hipSuccess)
+    return -3;
+  return nb;
+}
+
+template <bool SEED, bool BIAS, bool C4, bool SPLIT>
+int s32_go(const StageArgs& a, int64_t grid, hipStream_t stream) {
   const size_t lds = s32_lds_bytes(a.D, SEED);
-  if (s32_attr<SEED, BIAS, C4>(lds)) return -3;
-  const int64_t grid = a.persist > 0 ? a.persist : a.np;
-  hipLaunchKernelGGL((stage32_kernel<SEED, BIAS, C4>), dim3((unsigned)grid), dim3(kThreads), lds, stream, a);
+  if (s32_attr<SEED, BIAS, C4, SPLIT>(lds)) return -3;
+  hipLaunchKernelGGL((stage32_kernel<SEED, BIAS, C4, SPLIT>), dim3((unsigned)grid), dim3(kThreads), lds, stream, a);
   return hipGetLastError() == hipSuccess ? 0 : -3;
 }
 
 template <bool SEED, bool BIAS, bool C4>
-int s32_occ(int D) {
-  const size_t lds = s32_lds_bytes(D, SEED);
-  if (s32_attr<SEED, BIAS, C4>(lds)) return -3;
-  int nb = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, stage32_kernel<SEED, BIAS, C4>, kThreads, lds) != hipSuccess)
-    return -3;
-  return nb;
+int s32_launch(const StageArgs& a, hipStream_t stream) {
+  int dev = 0, cus = 0;
+  if (a.np <= 1024 && hipGetDevice(&dev) == hipSuccess &&
+      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && cus > 0) {
+    const int occ = s32_occ<SEED, BIAS, C4>(a.D);
+    const int parts = occ > 0 ? s32_parts(a.np, (int64_t)cus * occ) : 1;
+    if (parts > 1) {
+      StageArgs p = a;
+      p.parts = parts;
+      p.persist = 0;
+      return s32_go<SEED, BIAS, C4, true>(p, a.np * parts, stream);
+    }
+  }
+  return s32_go<SEED, BIAS, C4, false>(a, a.persist > 0 ? a.persist : a.np, stream);
 }
 
 }  // namespace
