@@ -16,6 +16,14 @@
 // tiles for the x part of the pool.  The images are read from global memory
 // (L1/L2) once per tile.
 //
+// What bounds it: one workgroup per CU (LDS), two waves per SIMD, so neither
+// LDS nor global latency hides by itself.  With the seed formed before the
+// layers (16 rows of pixels requested, waited for and used at a time) the
+// vector units were busy 63 % of the time; formed row by row inside the first
+// layer, eight rows after its request, with the outputs that are added to
+// requested together, 76 %.  Myrtle at 64x64x3, depth 2,2,2, 24 x 21 pairs, whole
+// call: 14.8 -> 12.2 ms.
+//
 // Pooling.  The y part runs in registers along the ky sweep as in the
 // smaller stages, except that coarse row 0 (its first part comes at ky = 1,
 // the rest at the end of the sweep, ky = 0) is emitted twice and summed in
@@ -36,43 +44,88 @@ namespace nk {
 constexpr int S64_THREADS = 512;  // 8 waves, one tile column each
 
 // Rows of the first image kept in LDS (channel-major per row, lane-contiguous
-// reads) for the first batch of seed rows: what fits beside the tables and
+// reads), the first of which a tile needs at once: what fits beside the tables and
 // the pooling row at depth 2 (12 KiB at 3 channels); none at 4 channels.
 __host__ __device__ constexpr int s64_x1_rows(int C) { return C <= 3 ? 16 : 0; }
 
-// [3x3 conv, ReLU] on one 64-row tile; as tile_layer, with the second
+// Seed rows whose pixels are on their way at any time.
+constexpr int S64_AHEAD = 8;
+
+// Where a tile's seed comes from: pixel rows of both images at this lane's
+// columns (global memory; uniform bases, so that a row's address is scalar),
+// and the first image's first rows in LDS.
+template <int C>
+struct S64Seed {
+  const float* x1;   // row 0 of the first image (uniform)
+  const float* x2;   // row 0 of the second image (uniform)
+  const float* x1l;  // [rows][C][64] at this lane's column
+  unsigned o1, o2;   // this lane's float offset in a row of each
+  float ss;
+};
+
+// One [3x3 conv, ReLU] layer on one 64-row tile; as tile_layer, with the second
 // image's table rows wrapping: row r of tile (ky, kx) reads pixel row
 // (r + ky) mod 64 of x2.  The map is the forward NNGP's degree-3 fit, and
 // each row's tables are requested two rows before its map (at two waves per
 // SIMD the LDS latency is not hidden by other waves alone; the compiler
 // barrier keeps each request ahead of the row it runs before).
-template <bool SIGNED, bool BIAS>
+// FIRST: the tile's seed is formed as the layer goes, one row ahead of the box
+// sum.  The pixels of a row are requested S64_AHEAD rows earlier (pre: those of
+// rows 0 .. S64_AHEAD - 1, requested before the previous tile's pooling), so
+// the latency of global memory passes under the map of the rows between.
+template <bool FIRST, bool BIAS, int C>
 __device__ __forceinline__ void s64_layer(float (&A)[64], const float2* __restrict__ c1,
                                           const float2* __restrict__ t2l, int ky, int jx, int seam, float mL,
-                                          float mR, float sb2) {
-  float2 ta[64], tb[64];  // (registers: three rows live at a time)
+                                          float mR, float sb2, const S64Seed<C>& sd, const float (&pre)[S64_AHEAD][C]) {
+  constexpr int XR = s64_x1_rows(C);
+  float2 ta[64], tb[64];            // (registers: three rows live at a time)
+  float u[64][C], v[64][C];         // (registers: S64_AHEAD rows live at a time)
   auto fetch = [&](int r) {
     ta[r] = c1[r * 64];
     tb[r] = t2l[((r + ky) & 63) * 64 + jx];
   };
+  auto request = [&](int r, bool both) {
+    const float* p1 = sd.x1 + r * 64 * C;
+    const float* p2 = sd.x2 + ((r + ky) & 63) * 64 * C;
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+      u[r][c] = r < XR ? sd.x1l[(r * C + c) * 64] : p1[sd.o1 + c];
+      v[r][c] = both ? p2[sd.o2 + c] : pre[r < S64_AHEAD ? r : 0][c];
+    }
+  };
+  auto seed = [&](int r) {
+    float d = 0.f;
+#pragma unroll
+    for (int c = 0; c < C; ++c) d = __builtin_fmaf(u[r][c], v[r][c], d);
+    A[r] = d * sd.ss;
+  };
+  if constexpr (FIRST) {
+#pragma unroll
+    for (int r = 0; r < S64_AHEAD; ++r) request(r, false);
+  }
   fetch(0);
   fetch(1);
+  if constexpr (FIRST) seed(0);
   float hm = 0.f;
   float h0 = hsum3(A[0], mL, mR);
 #pragma unroll
   for (int r = 0; r < 64; ++r) {
+    if (FIRST && r + S64_AHEAD < 64) request(r + S64_AHEAD, true);
     if (r + 2 < 64) fetch(r + 2);
     asm volatile("" ::: "memory");
     float hp = 0.f;
-    if (r + 1 < 64) hp = hsum3(A[r + 1], mL, mR);
-    float v = h0;
-    if (r > 0) v = __builtin_fmaf(uniform_mask(r == seam), hm, v);
-    if (r + 1 < 64) v = __builtin_fmaf(uniform_mask(r + 1 == seam), hp, v);
-    if (BIAS) v += sb2;
+    if (r + 1 < 64) {
+      if constexpr (FIRST) seed(r + 1);
+      hp = hsum3(A[r + 1], mL, mR);
+    }
+    float w = h0;
+    if (r > 0) w = __builtin_fmaf(uniform_mask(r == seam), hm, w);
+    if (r + 1 < 64) w = __builtin_fmaf(uniform_mask(r + 1 == seam), hp, w);
+    if (BIAS) w += sb2;
     const float2 a = ta[r];
     const float2 b = tb[r];
     const float rr = a.x * b.x;
-    const float J = SIGNED ? j1_signed_vr3(v, rr) : j1_nonneg3(v * rr);
+    const float J = FIRST ? j1_signed_vr3(w, rr) : j1_nonneg3(w * rr);
     A[r] = (a.y * b.y) * J;
     hm = h0;
     h0 = hp;
@@ -104,10 +157,7 @@ __global__ __launch_bounds__(S64_THREADS) void stage64_kernel(const StageArgs ar
     x1l[(row * C + c) * N + col] = args.x1[ia * NN * C + e];
   }
   __syncthreads();
-  const float* x1p = args.x1 + (ia * NN + ix) * C;
-  const float* x2p = args.x2 + ib * NN * C;
   float* out = args.out + pl * (int64_t)H * H3;
-  const float ss = args.seed_scale;
 
 #pragma unroll 1
   for (int g = 0; g < 8; ++g) {
@@ -115,7 +165,27 @@ __global__ __launch_bounds__(S64_THREADS) void stage64_kernel(const StageArgs ar
     const float mL = (ix >= 1 && ix != N - kx) ? 1.f : 0.f;
     const float mR = (ix + 1 < N && ix + 1 != N - kx) ? 1.f : 0.f;
     const int jx = (ix + kx) & (N - 1);
-    const float* x2c = x2p + jx * C;
+    S64Seed<C> sd;
+    sd.x1l = x1l + ix;
+    sd.o1 = ix * C;
+    sd.o2 = jx * C;
+    sd.ss = args.seed_scale;
+    // (an opaque offset keeps the row addresses from being hoisted out of the
+    // sweep: they would pin their registers)
+    auto bases = [&] {
+      const int z = opaque_zero();
+      sd.x1 = args.x1 + ia * NN * C + z;
+      sd.x2 = args.x2 + ib * NN * C + z;
+    };
+    float pre[S64_AHEAD][C];
+    auto begin = [&](int ky) {
+#pragma unroll
+      for (int r = 0; r < S64_AHEAD; ++r)
+#pragma unroll
+        for (int c = 0; c < C; ++c) pre[r][c] = sd.x2[((r + ky) & (N - 1)) * N * C + sd.o2 + c];
+    };
+    bases();
+    begin(1);
     float acc[H];
 #pragma unroll
     for (int I = 0; I < H; ++I) acc[I] = 0.f;
@@ -132,36 +202,11 @@ __global__ __launch_bounds__(S64_THREADS) void stage64_kernel(const StageArgs ar
       // to what the output already holds
       const bool add_all = ky == 0;
       float A[N];
-      constexpr int SR = 16;  // seed rows whose pixels are requested together
-      // (an opaque offset keeps the 64 row addresses of each image from being
-      // hoisted out of the sweep: they would pin 256 registers)
-      const int z = opaque_zero();
-      const float* x1s = x1p + z;
-      const float* x2s = x2c + z;
-#pragma unroll
-      for (int r0 = 0; r0 < N; r0 += SR) {
-        float u[SR][C], v[SR][C];
-#pragma unroll
-        for (int k = 0; k < SR; ++k) {
-          const float* p1 = x1s + (r0 + k) * N * C;
-          const float* p2 = x2s + ((r0 + k + ky) & (N - 1)) * N * C;
-#pragma unroll
-          for (int c = 0; c < C; ++c) {
-            u[k][c] = r0 + k < XR ? x1l[((r0 + k) * C + c) * N + ix] : p1[c];
-            v[k][c] = p2[c];
-          }
-        }
-#pragma unroll
-        for (int k = 0; k < SR; ++k) {
-          float sd = 0.f;
-#pragma unroll
-          for (int c = 0; c < C; ++c) sd = __builtin_fmaf(u[k][c], v[k][c], sd);
-          A[r0 + k] = sd * ss;
-        }
-      }
       const float2* c1 = t1 + ix;
-      s64_layer<true, BIAS>(A, c1, t2, ky, jx, seam, mL, mR, args.sb2);
-      if (D > 1) s64_layer<false, BIAS>(A, c1 + NN, t2 + NN, ky, jx, seam, mL, mR, args.sb2);
+      s64_layer<true, BIAS, C>(A, c1, t2, ky, jx, seam, mL, mR, args.sb2, sd, pre);
+      bases();
+      begin((ky + 1) & (N - 1));
+      if (D > 1) s64_layer<false, BIAS, C>(A, c1 + NN, t2 + NN, ky, jx, seam, mL, mR, args.sb2, sd, pre);
 
       // y part of the pool
       if (ky == 1) {
@@ -200,16 +245,32 @@ __global__ __launch_bounds__(S64_THREADS) void stage64_kernel(const StageArgs ar
             // part of row 0) or, for the last group, coarse column 0 (which
             // group 0 wrote: added)
             float* o = out + (int64_t)Ky * H3 + (int64_t)(((4 * g + 4) & (H - 1)) * H) * H + (ix >> 1);
-            const bool add = g == 7 || add_all;
+            if (g == 7 || add_all) {
+              float had[H];  // (requested together)
 #pragma unroll
-            for (int I = 0; I < H; ++I) o[I * H] = add ? o[I * H] + acc[I] : acc[I];
+              for (int I = 0; I < H; ++I) had[I] = o[I * H];
+#pragma unroll
+              for (int I = 0; I < H; ++I) o[I * H] = had[I] + acc[I];
+            } else {
+#pragma unroll
+              for (int I = 0; I < H; ++I) o[I * H] = acc[I];
+            }
           }
         }
         __syncthreads();
         {
           float* o = out + (int64_t)Ky * H3 + (int64_t)(4 * g) * H2;
-          for (int e = tid; e < 4 * H2; e += S64_THREADS)
-            o[e] = (add_all || (g > 0 && e < H2)) ? o[e] + red[e] : red[e];
+          float had[8];  // (requested together)
+#pragma unroll
+          for (int j = 0; j < 8; ++j) {
+            const int e = tid + j * S64_THREADS;
+            had[j] = add_all || (g > 0 && e < H2) ? o[e] : 0.f;
+          }
+#pragma unroll
+          for (int j = 0; j < 8; ++j) {
+            const int e = tid + j * S64_THREADS;
+            o[e] = add_all || (g > 0 && e < H2) ? had[j] + red[e] : red[e];
+          }
         }
         __syncthreads();
         if (ky != 0) {
