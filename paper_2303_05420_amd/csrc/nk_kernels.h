@@ -61,7 +61,7 @@ struct StageArgs {
   const TileDesc* tiles;  // batched pass: tile table (NULL: one block given by n1, n2, x1, x2, K)
   int ntiles;
   int persist;     // > 0: grid of `persist` workgroups looping over the chunk
-  int parts;       // workgroups that share a pair's sweep (32x32 pooling stage, set by its launcher)
+  int parts;       // workgroups that share a pair's sweep (32x32 pooling and 64x64 stages, set by their launchers)
   const float* x1;
   const float* x2;
   const float2* tab1;
@@ -131,6 +131,29 @@ struct FcArgs {
   int64_t ldk;
   int sym;  // x1 and x2 are the same images: upper-triangle tiles, mirrored
 };
+
+// Workgroups that share the sweep of a pair's N displacement rows (N = 32, 64).
+// A workgroup takes one CU (or half of one) for the N tiles of a tile column,
+// so a chunk of fewer pairs than the chip holds (`resident`) leaves CUs idle; a
+// part of N / 2P coarse rows costs N / P tiles, one more to begin with, and
+// about two tiles' time to fill LDS.  P is the power of two with the fewest
+// rounds x tiles (from four rounds on the last one no longer matters).  Whole
+// calls: Myrtle-10 at 32x32x3, 2 x 60 pairs, 548 us with a workgroup a pair,
+// 387 us with two; Myrtle at 64x64x3, depth 2,2,2, 1 x 20 pairs 5.85 -> 1.11 ms,
+// 2 x 60 pairs 6.13 -> 3.39 ms.
+inline int sweep_parts(int64_t np, int64_t resident, int N) {
+  int best = 1;
+  int64_t least = 0;
+  for (int P = 1; P <= N / 2; P *= 2) {
+    const int64_t cost = (np * P + resident - 1) / resident * (N / P + (P > 1 ? 3 : 2));
+    if (P == 1 || cost < least) {
+      least = cost;
+      best = P;
+    }
+  }
+  return best;
+}
+
 
 // Variance tables of both image sets (x2 NULL: one set).  Scratch: slots x
 // prep_scratch_doubles(net) doubles, slots = prep_slots(images) images at a time.

@@ -465,7 +465,7 @@ __global__ __launch_bounds__(kThreads) void stage32_kernel(const StageArgs args)
   float4* i1w = const_cast<float4*>(c.img1);
   float4* i2w = const_cast<float4*>(c.img2);
 
-  // SPLIT: `parts` workgroups share the sweep of a pair (s32_parts)
+  // SPLIT: `parts` workgroups share the sweep of a pair (sweep_parts)
   const int parts = SPLIT ? args.parts : 1;
   const int64_t nunits = args.np * parts;
   int E0 = 0;  // emits of the units before this one
@@ -564,26 +564,6 @@ __global__ __launch_bounds__(kThreads) void stage32_kernel(const StageArgs args)
   }
 }
 
-// Workgroups that share the sweep of a pair.  A workgroup takes one CU (or half
-// of one) for the sweep's 32 tiles, so a chunk of fewer pairs than the chip
-// holds leaves CUs idle; a part of 16 / P coarse rows costs 32 / P tiles, one
-// more to begin with, and about two tiles' time to fill LDS.  P is the power of
-// two with the fewest rounds x tiles (from four rounds on the last one no longer
-// matters).  Myrtle-10 at 32x32x3, 2 x 60 pairs, whole call: 548 us with a
-// workgroup a pair, 387 us with two.
-inline int s32_parts(int64_t np, int64_t resident) {
-  int best = 1;
-  int64_t least = 0;
-  for (int P = 1; P <= kH; P *= 2) {
-    const int64_t cost = (np * P + resident - 1) / resident * (kN / P + (P > 1 ? 3 : 2));
-    if (P == 1 || cost < least) {
-      least = cost;
-      best = P;
-    }
-  }
-  return best;
-}
-
 template <bool SEED, bool BIAS, bool C4, bool SPLIT>
 int s32_attr(size_t lds) {
   static std::atomic<size_t> seen[kMaxDevices];
@@ -616,7 +596,7 @@ int s32_launch(const StageArgs& a, hipStream_t stream) {
   if (a.np <= 1024 && hipGetDevice(&dev) == hipSuccess &&
       hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && cus > 0) {
     const int occ = s32_occ<SEED, BIAS, C4>(a.D);
-    const int parts = occ > 0 ? s32_parts(a.np, (int64_t)cus * occ) : 1;
+    const int parts = occ > 0 ? sweep_parts(a.np, (int64_t)cus * occ, kN) : 1;
     if (parts > 1) {
       StageArgs p = a;
       p.parts = parts;

@@ -144,8 +144,20 @@ __global__ __launch_bounds__(S64_THREADS) void stage64_kernel(const StageArgs ar
   float* x1l = red + 4 * H2;  // [XR][C][N]: the first XR rows of the first image
   const int tid = threadIdx.x, w = tid >> 6, ix = tid & 63;
 
-  const int64_t pl = xcd_logical_block();
+  // Part `part` of P of the sweep: coarse rows row0 + 1 .. row1 (32: row 0), each
+  // from the odd rows of ky = 2t - 1 and the tiles ky = 2t and 2t + 1, in the
+  // order of the whole sweep (ky = 1 .. 63, 0), which P = 1 is.  A part of
+  // several begins with a step that only carries its odd rows on; the last one
+  // first takes ky = 1 as well, for the first part of coarse row 0.
+  const int P = args.parts;
+  const int64_t unit = xcd_logical_block();
+  const int64_t pl = unit / P;
   if (pl >= args.np) return;  // whole workgroup, before any barrier
+  const int part = (int)(unit - pl * P);
+  const int row0 = part * H / P, row1 = (part + 1) * H / P;
+  const int pre1 = P > 1 && row1 == H ? 1 : 0;  // the last part's ky = 1
+  const int nsteps = P > 1 ? 2 * (row1 - row0) + 1 : N;
+  auto ky_of = [&](int step) { return step < pre1 ? 1 : (2 * row0 + 1 + step - pre1) & (N - 1); };
   int64_t ia, ib;
   pair_of(args.p0 + pl, args.n1, args.n2, args.sym, args.T, &ia, &ib);
   for (int e = tid; e < D * NN; e += S64_THREADS) {
@@ -185,18 +197,19 @@ __global__ __launch_bounds__(S64_THREADS) void stage64_kernel(const StageArgs ar
         for (int c = 0; c < C; ++c) pre[r][c] = sd.x2[((r + ky) & (N - 1)) * N * C + sd.o2 + c];
     };
     bases();
-    begin(1);
+    begin(ky_of(0));
     float acc[H];
 #pragma unroll
     for (int I = 0; I < H; ++I) acc[I] = 0.f;
 #pragma unroll 1
-    for (int step = 0; step < N; ++step) {
-      const int ky = (step + 1) & (N - 1);
+    for (int step = 0; step < nsteps; ++step) {
+      const int ky = ky_of(step);
       const int seam = ky == 0 ? -1 : N - ky;
       // coarse row completed (or, at ky = 1, begun) at this step: ky = 1
       // and ky = 0 emit coarse row 0 in two parts, every odd ky > 1 ends row
       // (ky - 1) / 2
-      const bool emit = ky == 0 || (ky & 1);
+      const bool carry = P > 1 && step == pre1;
+      const bool emit = (ky == 0 || (ky & 1)) && !carry;
       const int Ky = ky == 0 ? 0 : (ky - 1) >> 1;
       // the second part of coarse row 0 and the carried boundary columns add
       // to what the output already holds
@@ -205,11 +218,14 @@ __global__ __launch_bounds__(S64_THREADS) void stage64_kernel(const StageArgs ar
       const float2* c1 = t1 + ix;
       s64_layer<true, BIAS, C>(A, c1, t2, ky, jx, seam, mL, mR, args.sb2, sd, pre);
       bases();
-      begin((ky + 1) & (N - 1));
+      begin(ky_of(step + 1));
       if (D > 1) s64_layer<false, BIAS, C>(A, c1 + NN, t2 + NN, ky, jx, seam, mL, mR, args.sb2, sd, pre);
 
       // y part of the pool
-      if (ky == 1) {
+      if (carry) {
+#pragma unroll
+        for (int I = 0; I < H; ++I) acc[I] = A[2 * I + 1];
+      } else if (ky == 1) {
 #pragma unroll
         for (int I = 0; I < H; ++I) acc[I] = A[2 * I];
       } else if ((ky & 1) == 0) {
@@ -293,7 +309,13 @@ static int launch_s64_t(const StageArgs& a, hipStream_t s) {
   const size_t lds = stage64_lds_bytes(a.D, C);
   static std::atomic<size_t> seen[kMaxDevices];  // per instantiation
   if (allow_dyn_lds((const void*)fn, lds, seen)) return -3;
-  hipLaunchKernelGGL(fn, dim3((unsigned)a.np), dim3(S64_THREADS), lds, s, a);
+  StageArgs p = a;
+  p.parts = 1;
+  int dev = 0, cus = 0;
+  if (a.np <= 1024 && hipGetDevice(&dev) == hipSuccess &&
+      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && cus > 0)
+    p.parts = sweep_parts(a.np, cus, 64);  // (LDS: one workgroup per CU)
+  hipLaunchKernelGGL(fn, dim3((unsigned)(a.np * p.parts)), dim3(S64_THREADS), lds, s, p);
   return hipGetLastError() == hipSuccess ? 0 : -3;
 }
 
