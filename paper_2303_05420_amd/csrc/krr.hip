@@ -86,6 +86,9 @@ __device__ __forceinline__ void chol_chain(const CholLds& m, d4 (&y)[4]) {
 }
 
 // A panel's strip of right-hand sides: rows k + 16 b + 4 t + g, column col.
+// (Here as in the other kernels of the factorisation loads are clamped into
+// the matrix and what lies past its end is replaced afterwards: loads under a
+// condition went out one after another, 12000 of a panel's 52000 cycles.)
 __device__ __forceinline__ void chol_load_strip(const double* Z, int64_t n, int64_t k, int64_t c, int64_t col, int g,
                                                 d4 (&y)[4]) {
 #pragma unroll
@@ -93,8 +96,14 @@ __device__ __forceinline__ void chol_load_strip(const double* Z, int64_t n, int6
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
       const int64_t r = k + 16 * b + 4 * t + g;
-      y[b][t] = r < n ? Z[r * c + col] : 0.0;
+      y[b][t] = Z[(r < n ? r : n - 1) * c + col];
     }
+  if (k + CH_NB <= n) return;
+#pragma unroll
+  for (int b = 0; b < 4; ++b)
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+      if (k + 16 * b + 4 * t + g >= n) y[b][t] = 0.0;
 }
 __device__ __forceinline__ void chol_store_strip(double* Z, int64_t n, int64_t k, int64_t c, int64_t col, int g,
                                                  const d4 (&y)[4]) {
@@ -108,6 +117,12 @@ __device__ __forceinline__ void chol_store_strip(double* Z, int64_t n, int64_t k
     }
 }
 
+// 1 / d: the hardware's estimate (relative error about 2^-23) and a cubic step.
+__device__ __forceinline__ double chol_rcp(double d) {
+  const double r = __builtin_amdgcn_rcp(d), e = fma(-d, r, 1.0);
+  return fma(r, fma(e, e, e), r);
+}
+
 // Panel [k, k + nb): every workgroup factors the diagonal block for itself
 // (a launch of its own for it would add to the chain that bounds the solve:
 // n columns, one after the other).  The first nrow workgroups solve 64 of the
@@ -119,8 +134,10 @@ __device__ __forceinline__ void chol_store_strip(double* Z, int64_t n, int64_t k
 // The columns are factored 16 at a time by one wave, a lane per row of the
 // block, pivots and multipliers by lane reads: no barrier inside.  With a
 // barrier per column (block in LDS, one workgroup, its own launch) and a
-// thread per row below: 82 + 43 us a panel at n = 2500, 23 us for
-// both.
+// thread per row below: 82 + 43 us a panel at n = 2500; 23 us for
+// both with a square root between pivots and each broadcast read where it is
+// used (400 cycles a column) and loads under conditions; 17 us so, of which 2.7
+// load, 8.5 factor and update the block, 2.7 invert its last part and solve.
 __global__ __launch_bounds__(256) void chol_panel_kernel(double* __restrict__ A, int64_t n, int64_t k, int nb,
                                                          int* __restrict__ info, unsigned nrow,
                                                          double* __restrict__ Z, int64_t c) {
@@ -133,6 +150,12 @@ __global__ __launch_bounds__(256) void chol_panel_kernel(double* __restrict__ A,
   const int64_t row = k + nb + (int64_t)blockIdx.x * CH_NB + 16 * w + i;
   const int64_t col = (int64_t)(blockIdx.x - nrow) * 64 + 16 * w + i;
   double* prow = A + (row < n ? row : n - 1) * n + k;
+  double dv[16];
+#pragma unroll
+  for (int q = 0; q < 16; ++q) {
+    const int r = 4 * q + w;
+    dv[q] = A[(k + (r < nb ? r : nb - 1)) * n + k + (lane < nb ? lane : nb - 1)];
+  }
   d4 y[4];
   if (rhs) {
     chol_load_strip(Z, n, k, c, col < c ? col : c - 1, g, y);
@@ -142,15 +165,10 @@ __global__ __launch_bounds__(256) void chol_panel_kernel(double* __restrict__ A,
 #pragma unroll
       for (int t = 0; t < 4; ++t) y[b][t] = prow[16 * b + 4 * t + g];
   }
-  {
-    double v[16];
 #pragma unroll
-    for (int q = 0; q < 16; ++q) {
-      const int r = 4 * q + w;
-      v[q] = (r < nb && lane <= r) ? A[(k + r) * n + k + lane] : (r == lane ? 1.0 : 0.0);
-    }
-#pragma unroll
-    for (int q = 0; q < 16; ++q) m.T[(4 * q + w) * CH_LD + lane] = v[q];
+  for (int q = 0; q < 16; ++q) {
+    const int r = 4 * q + w;
+    m.T[r * CH_LD + lane] = (r < nb && lane <= r) ? dv[q] : (r == lane ? 1.0 : 0.0);
   }
   __syncthreads();
   // inverse of a diagonal block: lane i forms its column i (wave 3, while wave
@@ -175,31 +193,51 @@ __global__ __launch_bounds__(256) void chol_panel_kernel(double* __restrict__ A,
   for (int jb = 0; jb < 4; ++jb) {
     if (w == 3 && jb > 0) inverse(jb - 1);
     if (w == 0) {
-      double a[16];
+      // (rotated, so that the block's own rows are lanes 0 .. 15)
+      const int row = (lane + 16 * jb) & 63;
+      double a[16], b[16];
 #pragma unroll
-      for (int j = 0; j < 16; ++j) a[j] = m.T[lane * CH_LD + 16 * jb + j];
-      bool bad = false;
+      for (int j = 0; j < 16; ++j) a[j] = m.T[row * CH_LD + 16 * jb + j];
+      // Column j of the unscaled factor: a[e] -= (a[j] / d) a_e[j], d the
+      // pivot.  Between one pivot and the next stand 1 / d (a cubic step on the
+      // hardware's estimate), two products and a broadcast; the other columns'
+      // updates and the next column's broadcasts (b) pass under them, each
+      // kind in one go, since a broadcast read just before its use costs the
+      // wave its latency (schedule fixed by the barriers).  The square roots
+      // are taken for the 16 columns at once, when all pivots are known.
+      double r = chol_rcp(lane_value(a[0], 0));
 #pragma unroll
-      for (int j = 0; j < 16; ++j) {
-        double d = lane_value(a[j], 16 * jb + j);
-        if (!(d > 0.0)) {
-          bad = true;
-          d = 1.0;
-        }
-        // 1 / sqrt(d) by two Newton steps, sqrt(d) with its residual
-        double r = __builtin_amdgcn_rsq(d);
-        r = fma(0.5 * r, fma(-d * r, r, 1.0), r);
-        r = fma(0.5 * r, fma(-d * r, r, 1.0), r);
-        double q = d * r;
-        q = fma(fma(-q, q, d), 0.5 * r, q);
-        const double l = a[j] * r;  // (sqrt(d) up to rounding in row j itself, which the updates do not read)
+      for (int e = 1; e < 16; ++e) b[e] = lane_value(a[0], e);
 #pragma unroll
-        for (int e = j + 1; e < 16; ++e) a[e] = fma(-l, lane_value(l, 16 * jb + e), a[e]);
-        a[j] = lane == 16 * jb + j ? q : l;
+      for (int j = 0; j < 15; ++j) {
+        const double u = -a[j] * r;
+        a[j + 1] = fma(u, b[j + 1], a[j + 1]);
+        const double d = lane_value(a[j + 1], j + 1);
+        const double r0 = __builtin_amdgcn_rcp(d);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int e = j + 2; e < 16; ++e) a[e] = fma(u, b[e], a[e]);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int e = j + 2; e < 16; ++e) b[e] = lane_value(a[j + 1], e);
+        const double e1 = fma(-d, r0, 1.0);
+        r = fma(r0, fma(e1, e1, e1), r0);
+        __builtin_amdgcn_sched_barrier(0);
       }
-      if (bad && lane == 0) info[0] = 1;
+      double d = 1.0;  // lane j < 16: pivot j
 #pragma unroll
-      for (int j = 0; j < 16; ++j) m.T[lane * CH_LD + 16 * jb + j] = a[j];
+      for (int j = 0; j < 16; ++j) d = lane == j ? a[j] : d;
+      // (a pivot that is not positive spoils the columns after it; the caller
+      // reports the flag instead of a result)
+      if (!(d > 0.0)) info[0] = 1;
+      // 1 / sqrt(d) by two Newton steps, sqrt(d) with its residual
+      double rs = __builtin_amdgcn_rsq(d);
+      rs = fma(0.5 * rs, fma(-d * rs, rs, 1.0), rs);
+      rs = fma(0.5 * rs, fma(-d * rs, rs, 1.0), rs);
+      double sq = d * rs;
+      sq = fma(fma(-sq, sq, d), 0.5 * rs, sq);
+#pragma unroll
+      for (int j = 0; j < 16; ++j) m.T[row * CH_LD + 16 * jb + j] = lane == j ? sq : a[j] * lane_value(rs, j);
     }
     __syncthreads();
     // the blocks right of it: T[rb][cb] -= L[rb][jb] L[cb][jb]^T, jb < cb <= rb
@@ -363,7 +401,7 @@ __global__ __launch_bounds__(256) void chol_solve_kernel(const double* __restric
 #pragma unroll
   for (int q = 0; q < 16; ++q) {
     const int r = 4 * q + w;
-    f[q] = (k + r < n && k + lane < n) ? A[(k + r) * n + k + lane] : (r == lane ? 1.0 : 0.0);
+    f[q] = A[(k + r < n ? k + r : n - 1) * n + (k + lane < n ? k + lane : n - 1)];
   }
   chol_load_strip(Z, n, k, c, col, g, y);
   if (ntiles > 0) {
@@ -374,7 +412,7 @@ __global__ __launch_bounds__(256) void chol_solve_kernel(const double* __restric
         const int64_t kk = k + 16 * b + 4 * t + g, r = r0 + i;
         // (backward: rows of the panel, past the end in the last one; forward: rows below)
         if (BACK)
-          a[b][t] = kk < n ? A[kk * n + r] : 0.0;
+          a[b][t] = A[(kk < n ? kk : n - 1) * n + r];
         else
           a[b][t] = A[(r < n ? r : n - 1) * n + kk];
       }
@@ -384,6 +422,7 @@ __global__ __launch_bounds__(256) void chol_solve_kernel(const double* __restric
 #pragma unroll
   for (int q = 0; q < 16; ++q) {
     const int r = 4 * q + w, rb = r & 15, lb = lane & 15;
+    if (k + r >= n || k + lane >= n) f[q] = r == lane ? 1.0 : 0.0;
     m.T[r * CH_LD + lane] = f[q];
     if ((lane >> 4) == (r >> 4)) {
       // upper triangle: the inverse, transposed; it is 0 above its diagonal
