@@ -31,7 +31,7 @@
 // scratch (the first form) that chain was 49 x 3 layers long at Myrtle-10
 // 32x32: a call on 2 and 60 images spent 2.28 ms here (two sets, one after
 // the other), one on 8192 images 18.7 ms.  Now it is 3 x 3 layers long in 15
-// workgroups per image and both sets share a launch: 0.14 ms and 13.1 ms.
+// workgroups per image and both sets share a launch: 0.13 ms and 13.1 ms.
 #include "prep.h"
 
 namespace nk {
