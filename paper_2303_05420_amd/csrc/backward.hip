@@ -68,7 +68,10 @@ __device__ inline void rev_sums(double accw, double accb, double* __restrict__ s
 }
 
 // Reverse of one kept slice of a pooling stage s (maps of at most 32 x 32).
-__global__ __launch_bounds__(1024) void prep_rev_slice_kernel(const PrepRevArgs args, const int s, const int units) {
+// (THREADS as in prepare_stage_kernel: two workgroups per CU for the larger maps)
+template <int THREADS>
+__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(THREADS > 256 ? 8 : 4))) void
+prep_rev_slice_kernel(const PrepRevArgs args, const int s, const int units) {
   extern __shared__ double rev_sm[];
   const PrepArgs& fa = args.fwd;
   const NetDesc& net = fa.net;
@@ -308,9 +311,13 @@ int launch_prepare_bwd(const float* x1, int64_t n1, const double* W1, double* xb
       if (s + 1 < net.S) {
         const int units = prep_half(prep_R(net, s));
         const size_t lds = (size_t)(3 + 2 * D) * m * sizeof(double);
-        if (allow_dyn_lds((const void*)prep_rev_slice_kernel, lds, seen_s)) return -3;
-        hipLaunchKernelGGL(prep_rev_slice_kernel, dim3((unsigned)(cnt * units)), dim3((unsigned)prep_threads(m)), lds,
-                           stream, a, s, units);
+        const dim3 grid((unsigned)(cnt * units)), block((unsigned)prep_threads(m));
+        if (block.x > 256) {
+          if (allow_dyn_lds((const void*)prep_rev_slice_kernel<1024>, lds, seen_s)) return -3;
+          hipLaunchKernelGGL(prep_rev_slice_kernel<1024>, grid, block, lds, stream, a, s, units);
+        } else {
+          hipLaunchKernelGGL(prep_rev_slice_kernel<256>, grid, block, lds, stream, a, s, units);
+        }
       }
       const size_t lds = (size_t)(2 + D) * m * sizeof(double);
       if (allow_dyn_lds((const void*)prep_rev_chain_kernel, lds, seen_c)) return -3;

@@ -48,7 +48,27 @@ __device__ inline double relu_map64(double s, double q1, double q2) {
   return nrm * (sqrt(fmax(1.0 - rho * rho, 0.0)) + (M_PI - th) * rho) * (0.5 / M_PI);
 }
 
-// Partial derivatives of the map above.
+// sqrt of x in [0, 1], not denormal: two Newton steps on the hardware's 1 / sqrt
+// and the residual (correctly rounded but for the last bit, as sqrt() is; that
+// one also scales its argument for the ends of the range).
+__device__ inline double unit_sqrt64(double x) {
+  double r = __builtin_amdgcn_rsq(x);
+  r = fma(0.5 * r, fma(-x * r, r, 1.0), r);
+  r = fma(0.5 * r, fma(-x * r, r, 1.0), r);
+  const double q = x * r;
+  return x > 0.0 ? fma(fma(-q, q, x), 0.5 * r, q) : 0.0;
+}
+
+// The map above on r1 = sqrt(q1), r2 = sqrt(q2).
+__device__ inline double relu_map64_roots(double s, double r1, double r2) {
+  const double nrm = r1 * r2;
+  if (!(nrm > 0.0)) return 0.0;
+  double rho = s / nrm;
+  rho = rho > 1.0 ? 1.0 : (rho < -1.0 ? -1.0 : rho);
+  return nrm * (unit_sqrt64(fmax(1.0 - rho * rho, 0.0)) + (M_PI - acos(rho)) * rho) * (0.5 / M_PI);
+}
+
+// Partial derivatives of relu_map64.
 __device__ inline void relu_partials64(double s, double q1, double q2, double* ds, double* dq1, double* dq2) {
   const double qq = q1 * q2;
   if (!(qq > 0.0)) {

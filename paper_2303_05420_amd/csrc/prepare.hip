@@ -31,7 +31,7 @@
 // scratch (the first form) that chain was 49 x 3 layers long at Myrtle-10
 // 32x32: a call on 2 and 60 images spent 2.28 ms here (two sets, one after
 // the other), one on 8192 images 18.7 ms.  Now it is 3 x 3 layers long in 15
-// workgroups per image and both sets share a launch: 0.13 ms and 13.1 ms.
+// workgroups per image and both sets share a launch: 0.11 ms and 8.9 ms.
 #include "prep.h"
 
 namespace nk {
@@ -42,7 +42,13 @@ int64_t prep_slots(int64_t n) { return n < kPrepSlots ? n : kPrepSlots; }
 
 // Stage s of every image of the launch: `units` workgroups per image, each
 // one (coarse slice, part); the first of them also writes the stage's tables.
-__global__ __launch_bounds__(1024) void prepare_stage_kernel(const PrepArgs args, const int s, const int units) {
+// THREADS = 1024 (maps of more than 256 pixels): registers for two workgroups
+// per CU, which pass under each other's barriers and float64 chains (one per CU
+// at 68 registers: 125 us for the tables of 62 images of Myrtle-10 at 32x32,
+// two at 61: 111 us).  Smaller maps run in smaller workgroups and do not need it.
+template <int THREADS>
+__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(THREADS > 256 ? 8 : 4))) void
+prepare_stage_kernel(const PrepArgs args, const int s, const int units) {
   extern __shared__ double prep_sm[];
   const NetDesc& net = args.net;
   const int img = blockIdx.x / units, unit = blockIdx.x - img * units;
@@ -89,6 +95,9 @@ __global__ __launch_bounds__(1024) void prepare_stage_kernel(const PrepArgs args
   }
   if (s + 1 == net.S) return;
 
+  // the map below takes the roots (its own pixels, before the first barrier)
+  for (int i = tid; i < n2; i += nt)
+    for (int l = 0; l < D; ++l) q[l * n2 + i] = sqrt(q[l * n2 + i]);
   // the fine slices of this unit's coarse slice (DY, DX), pooled: coarse
   // pixel I of it gathers the fine pixels i = 2I + a with (i + delta) >> 1 ==
   // I + Delta in each dimension
@@ -113,7 +122,7 @@ __global__ __launch_bounds__(1024) void prepare_stage_kernel(const PrepArgs args
           const int y = i >> lg, xx = i & (n - 1), y2 = y + dyi, x2 = xx + dxi;
           double v = 0.0;
           if (y2 >= 0 && y2 < n && x2 >= 0 && x2 < n)
-            v = relu_map64(c * box9(w0, n, y, xx) + b, q[l * n2 + i], q[l * n2 + y2 * n + x2]);
+            v = relu_map64_roots(c * box9(w0, n, y, xx) + b, q[l * n2 + i], q[l * n2 + y2 * n + x2]);
           w1[i] = v;
         }
         __syncthreads();
@@ -140,9 +149,13 @@ int launch_prepare_stages(const PrepArgs& a, int64_t cnt, int stages, hipStream_
     const int m = stage_res(net, s) * stage_res(net, s);
     const int units = s + 1 < net.S ? prep_half(prep_R(net, s + 1)) * prep_parts(net) : 1;
     const size_t lds = (size_t)(2 + net.depth[s]) * m * sizeof(double);
-    if (allow_dyn_lds((const void*)prepare_stage_kernel, lds, seen)) return -3;
-    hipLaunchKernelGGL(prepare_stage_kernel, dim3((unsigned)(cnt * units)), dim3((unsigned)prep_threads(m)), lds,
-                       stream, a, s, units);
+    const dim3 grid((unsigned)(cnt * units)), block((unsigned)prep_threads(m));
+    if (block.x > 256) {
+      if (allow_dyn_lds((const void*)prepare_stage_kernel<1024>, lds, seen)) return -3;
+      hipLaunchKernelGGL(prepare_stage_kernel<1024>, grid, block, lds, stream, a, s, units);
+    } else {
+      hipLaunchKernelGGL(prepare_stage_kernel<256>, grid, block, lds, stream, a, s, units);
+    }
     if (hipGetLastError() != hipSuccess) return -3;
   }
   return 0;
