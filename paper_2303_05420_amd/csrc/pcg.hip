@@ -486,9 +486,13 @@ __global__ __launch_bounds__(PC_TPB) void kmv_reduce_kernel(const double* __rest
 // eight rows in flight), at least 64 rows each.  At n = 8192 that is 16 splits:
 // 57 us and 5 for their sum; with 1024 columns a workgroup there were 64, whose
 // partial sums (42 MB) took 58 us on the way out with K and 23 on the way in.
+// From 12288 rows on (K well past the last-level cache) about 1024, so that a
+// wave that waits for its rows of K, all a power of two apart at the usual
+// sizes, leaves another to run: 10 targets at n = 32768 take 775 us with 512
+// workgroups, 668 with 1024 (16384: 213 and 192; 24576: 436 and 459).
 int kmv_splits(int64_t n) {
   const int64_t ncb = (n + KMV_COLS - 1) / KMV_COLS;
-  int64_t S = (512 + ncb - 1) / ncb;
+  int64_t S = ((n >= 12288 ? 1024 : 512) + ncb - 1) / ncb;
   const int64_t maxS = (n + 63) / 64;
   if (S > maxS) S = maxS;
   if (S > 64) S = 64;
