@@ -197,31 +197,44 @@ __device__ __forceinline__ void fc_split2(float x0, float x1, unsigned& h, unsig
 
 // Tiles of 64 WB x 64 WB outputs, a quadrant of WB x WB blocks of 32 x 32 per
 // wave on v_mfma_f32_32x32x16_bf16.  The rows of both operands are read as
-// float32, split into three bfloat16 planes on the way into LDS, and the
+// float32, split into three bfloat16 parts on the way into LDS, and the
 // products h h', h m', m h', m m', h l', l h' accumulate in float32 (NP = 6);
 // the three left out are below 2^-24 of the product of the two numbers, with
 // either sign, which 64 or more features average out (NP = 9, all of them,
 // below).  The sum rounds once per 16 terms and product, less often than with
-// fp32 instructions.  Error against float64 at d = 3072: 9.5e-8 of the
+// fp32 instructions.  Error against float64 at d = 3072: 9.3e-8 of the
 // kernel, 9.6e-8 with fp32 instructions.
+// Exchanged operands.  A product and its counterpart (h l' and l h', h m' and m
+// h') stand in one instruction, in neighbouring registers of a lane: the 8 terms
+// of a lane are summed together whatever their order (measured: no bit differs
+// in 4e6 results when registers change places in both operands; a third of them
+// when the two halves of the wave do), so K(x2, x1) is the transpose of K(x1,
+// x2) bit for bit, and an entry's bits do not depend on where the block is cut.
+// The two after one another left 2 % of the entries different.  It costs the
+// moves that pair l with h and exchange one side's halves, 5 %: 7.3-7.5 ms for
+// the Gram below against 6.9-7.15 (a sum per side needs no moves, but three
+// accumulators do not fit the registers of two waves; the operands read from LDS
+// as they are used in place of the moves: 11 %).
 // Non-finite inputs: an infinity or NaN makes its row's diagonal non-finite,
 // and from one ReLU on the entry no longer depends on the dot product; without
 // ReLU layers such an entry's product is formed anew in float32.
-// LDS: [buffer][operand][plane][row] of 16 KT features, rows padded by 16 bytes
-// so that 8 lanes' 16-byte reads fall on different banks.  Two buffers, one
+// LDS: [buffer][operand], rows of 16 KT features: h and m in turn, two features
+// each (plane Q), and l (plane L), rows padded by 16 bytes so that 8 lanes'
+// 16-byte reads fall on different banks.  Two buffers, one
 // barrier per tile of features: the next tile is split and stored while the
 // current one multiplies, the one after it is on its way from memory (its
 // loads stay in flight across the barrier, which waits for LDS only); two
 // workgroups per CU.
 // Bound: the matrix instructions, 6 x 2 n1 n2 d operations at the bf16 rate, by
-// the reads that feed them.  FC-3 Gram of 20000 x 3072 (symmetric): 7.05 ms,
-// 1050 TFLOP/s of bf16 products, what a large library product reaches on this
-// card (1081); with fp32 instructions 12.3 ms, 0.65 of their peak.
+// the reads that feed them.  FC-3 Gram of 20000 x 3072 (symmetric): 7.3-7.5 ms,
+// about 1000 TFLOP/s of bf16 products (a large library product reaches 1081 on this
+// card); with fp32 instructions 12.3 ms, 0.65 of their peak.
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
 template <int WB, int KT, int NP>
 __global__ __launch_bounds__(256, WB == 1 ? 4 : 2) void fc_split_kernel(const FcArgs a) {
-  constexpr int TM = 64 * WB, BK = 16 * KT, ROW = 2 * BK + 16, PLANE = TM * ROW, BUF = 6 * PLANE;
+  constexpr int TM = 64 * WB, BK = 16 * KT, QROW = 4 * BK + 16, LROW = 2 * BK + 16;
+  constexpr int OPND = TM * (QROW + LROW), BUF = 2 * OPND;
   constexpr int TPR = BK / 4, RPP = 256 / TPR, NQ = TM / RPP;  // threads a row, rows a pass, passes an operand
   __shared__ __attribute__((aligned(16))) char lds[2 * BUF];
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
@@ -264,20 +277,21 @@ __global__ __launch_bounds__(256, WB == 1 ? 4 : 2) void fc_split_kernel(const Fc
         }
     }
   };
-  auto put = [&](const f4u& x, char* p) {
+  auto put = [&](const f4u& x, char* q, char* l) {
     unsigned h0, m0, l0, h1, m1, l1;
     fc_split2(x.x, x.y, h0, m0, l0);
     fc_split2(x.z, x.w, h1, m1, l1);
-    *reinterpret_cast<uint2*>(p) = make_uint2(h0, h1);
-    *reinterpret_cast<uint2*>(p + PLANE) = make_uint2(m0, m1);
-    *reinterpret_cast<uint2*>(p + 2 * PLANE) = make_uint2(l0, l1);
+    *reinterpret_cast<uint4*>(q) = make_uint4(h0, m0, h1, m1);
+    *reinterpret_cast<uint2*>(l) = make_uint2(l0, l1);
   };
-  char* sp = lds + srow * ROW + 2 * sk;
+  char* sq = lds + srow * QROW + 4 * sk;
+  char* sl = lds + TM * QROW + srow * LROW + 2 * sk;
   auto store = [&](const Regs& v, int buf) {
 #pragma unroll
     for (int m = 0; m < NQ; ++m) {
-      put(v.a[m], sp + buf * BUF + RPP * m * ROW);
-      put(v.b[m], sp + buf * BUF + 3 * PLANE + RPP * m * ROW);
+      const int o = buf * BUF;
+      put(v.a[m], sq + o + RPP * m * QROW, sl + o + RPP * m * LROW);
+      put(v.b[m], sq + o + OPND + RPP * m * QROW, sl + o + OPND + RPP * m * LROW);
     }
   };
   f16v acc[WB][WB];
@@ -288,28 +302,85 @@ __global__ __launch_bounds__(256, WB == 1 ? 4 : 2) void fc_split_kernel(const Fc
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
   const int wr = 32 * WB * (w >> 1), wc = 32 * WB * (w & 1), li = lane & 31, kh = lane >> 5;
-  const char* fa = lds + (wr + li) * ROW + 16 * kh;
-  const char* fb = lds + 3 * PLANE + (wc + li) * ROW + 16 * kh;
+  const char* qa = lds + (wr + li) * QROW + 32 * kh;
+  const char* la = lds + TM * QROW + (wr + li) * LROW + 16 * kh;
+  const char* qb = lds + OPND + (wc + li) * QROW + 32 * kh;
+  const char* lb = lds + OPND + TM * QROW + (wc + li) * LROW + 16 * kh;
+  // this lane's 8 features of a row: {h, m, h, m} of features 0 .. 3 and of 4 .. 7, and l
+  struct Frag {
+    uint4 q[2], l;
+  };
+  // Features 0 .. 3 (half 0) or 4 .. 7 as one operand of an instruction: two
+  // features' part x and the same two's part y, in turn; against (x, y) of one
+  // side stands (y, x) of the other.
+  enum { HM, HL, ML };
+  auto pairs = [](const Frag& f, int half, int kind, bool other) {
+    const uint4 q = f.q[half];
+    const unsigned l0 = half ? f.l.z : f.l.x, l1 = half ? f.l.w : f.l.y;
+    const unsigned x0 = kind == ML ? q.y : q.x, x1 = kind == ML ? q.w : q.z;
+    const unsigned y0 = kind == HM ? q.y : l0, y1 = kind == HM ? q.w : l1;
+    return __builtin_bit_cast(bf8, other ? make_uint4(y0, x0, y1, x1) : make_uint4(x0, y0, x1, y1));
+  };
+  auto product = [&](const bf8 (&x)[WB], const bf8 (&y)[WB]) {
+#pragma unroll
+    for (int i = 0; i < WB; ++i)
+#pragma unroll
+      for (int j = 0; j < WB; ++j)
+        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[i], y[j], acc[i][j], 0, 0, 0);
+  };
   auto multiply = [&](int buf) {
 #pragma unroll
     for (int kk = 0; kk < KT; ++kk) {
-      bf8 av[3][WB], bv[3][WB];
+      Frag a[WB], b[WB];
 #pragma unroll
-      for (int p = 0; p < 3; ++p)
+      for (int i = 0; i < WB; ++i) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          a[i].q[h] = *reinterpret_cast<const uint4*>(qa + buf * BUF + i * 32 * QROW + 64 * kk + 16 * h);
+          b[i].q[h] = *reinterpret_cast<const uint4*>(qb + buf * BUF + i * 32 * QROW + 64 * kk + 16 * h);
+        }
+        a[i].l = *reinterpret_cast<const uint4*>(la + buf * BUF + i * 32 * LROW + 32 * kk);
+        b[i].l = *reinterpret_cast<const uint4*>(lb + buf * BUF + i * 32 * LROW + 32 * kk);
+      }
+      bf8 ahm[2][WB], bhm[2][WB], bmh[2][WB], ahl[2][WB], blh[2][WB];
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
 #pragma unroll
         for (int i = 0; i < WB; ++i) {
-          av[p][i] = *reinterpret_cast<const bf8*>(fa + buf * BUF + p * PLANE + i * 32 * ROW + 32 * kk);
-          bv[p][i] = *reinterpret_cast<const bf8*>(fb + buf * BUF + p * PLANE + i * 32 * ROW + 32 * kk);
+          ahm[h][i] = pairs(a[i], h, HM, false);
+          bhm[h][i] = pairs(b[i], h, HM, false);
+          bmh[h][i] = pairs(b[i], h, HM, true);
+          ahl[h][i] = pairs(a[i], h, HL, false);
+          blh[h][i] = pairs(b[i], h, HL, true);
         }
       // smallest products first
-      constexpr int PA[9] = {2, 1, 2, 0, 2, 1, 0, 1, 0}, PB[9] = {2, 2, 1, 2, 0, 1, 1, 0, 0};
+      if constexpr (NP == 9) {
+        bf8 x[WB], y[WB];
 #pragma unroll
-      for (int p = 9 - NP; p < 9; ++p)
+        for (int i = 0; i < WB; ++i) {
+          x[i] = __builtin_bit_cast(bf8, a[i].l);
+          y[i] = __builtin_bit_cast(bf8, b[i].l);
+        }
+        product(x, y);  // l l'
 #pragma unroll
-        for (int i = 0; i < WB; ++i)
+        for (int h = 0; h < 2; ++h) {  // m l', l m'
 #pragma unroll
-          for (int j = 0; j < WB; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[PA[p]][i], bv[PB[p]][j], acc[i][j], 0, 0, 0);
+          for (int i = 0; i < WB; ++i) {
+            x[i] = pairs(a[i], h, ML, false);
+            y[i] = pairs(b[i], h, ML, true);
+          }
+          product(x, y);
+        }
+      }
+      // (the operands formed before the first product: with the moves between
+      // the products the large Gram takes 2 % longer)
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int h = 0; h < 2; ++h) product(ahl[h], blh[h]);  // h l', l h'
+#pragma unroll
+      for (int h = 0; h < 2; ++h) product(ahm[h], bmh[h]);  // h m', m h'
+#pragma unroll
+      for (int h = 0; h < 2; ++h) product(ahm[h], bhm[h]);  // h h', m m'
     }
   };
   Regs even, odd;  // the tiles of even and odd number on their way
