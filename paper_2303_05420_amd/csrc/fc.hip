@@ -446,13 +446,22 @@ static int64_t fc_tiles(const FcArgs& a, int64_t side) {
 }
 
 int launch_fc(const FcArgs& a, float* d1, float* d2, hipStream_t stream) {
-  // Kernel by size.  16 x 16 tiles read 16 + 16 rows for 256 outputs, eight
-  // times what the others read, but spread any d over a CU: at d = 3072 / 784,
-  // 512 x 512 outputs (1024 tiles) take 50 / 14 us against 80 / 29 with 64 x 64
-  // tiles, 4 x 20000 (1250) 46 / 16 against 133 / 47, 1000 x 1000 (3969) 183 /
-  // 45 against 86 / 32.
-  const int64_t small = fc_tiles(a, 16);
-  if (small <= 1536) {
+  // Kernel by size.  16 x 16 tiles read 16 + 16 rows for 256 outputs, four times
+  // what 64 x 64 ones do, but spread any d over a CU.  Their time goes with their
+  // number; that of 64 x 64 tiles is one tile's walk over d (13.8 / 31 / 87 us at
+  // d = 64 / 784 / 3072, 1600 or more of the small tiles) until the chip is
+  // full, and then grows by some four small tiles' time per tile.  So a block of
+  // up to 16 rows, four small tiles to a large one, stays with the small ones
+  // however long it is: 4 x 20000 10.7 / 17 / 45 us against 17 / 51 / 147, 4 x
+  // 100000 31 / 73 / 242 against 45 / 161 / 541.  Below the line: 32 x 20000 (2500
+  // small tiles) 16 / 30 / 112 against 18 / 51 / 147, 500 x 1000 (2016) 13 / 23 /
+  // 94 against 14 / 32 / 92; above it: 32 x 50000 (6250) 33 / 66 / 312 against 28 /
+  // 85 / 304, 300 x 2000 (2375) 15 / 29 / 118 against 14 / 33 / 96, 500 x 2000
+  // (4000) 22 / 43 / 184 against 14 / 33 / 97.  A symmetric block also writes its
+  // mirror, 64 bytes a row from small tiles, which shows where d is small: 900 at
+  // d = 64 (1653) 18 against 14; 1000 (2016) at 784 / 3072 27 / 88 against 32 / 90.
+  const int64_t small = fc_tiles(a, 16), t64 = fc_tiles(a, 64);
+  if (small <= (a.sym && a.d < 384 ? 1536 : 1600 + 4 * t64)) {
     hipLaunchKernelGGL(fc_small_kernel, dim3((unsigned)small), dim3(64 * FS_W), 0, stream, a);
     return hipGetLastError() == hipSuccess ? 0 : -3;
   }
@@ -466,7 +475,7 @@ int launch_fc(const FcArgs& a, float* d1, float* d2, hipStream_t stream) {
   // and hide the epilogue (four workgroups a CU): 4096 x 4096 at d = 3072 / 784
   // / 64: 620 / 192 / 69 us against 760 / 218 / 58; 3000 x 3000 (576 tiles):
   // 423 / 150 / 59 against 427 / 130 / 37.
-  const int64_t t128 = fc_tiles(a, 128), t64 = fc_tiles(a, 64);
+  const int64_t t128 = fc_tiles(a, 128);
   if (t128 >= 640 && a.d >= 384)
     hipLaunchKernelGGL((fc_split_kernel<2, 1, 6>), dim3((unsigned)t128), dim3(256), 0, stream, b);
   else if (a.d >= 64)
