@@ -475,9 +475,14 @@ int launch_fc(const FcArgs& a, float* d1, float* d2, hipStream_t stream) {
   // and hide the epilogue (four workgroups a CU): 4096 x 4096 at d = 3072 / 784
   // / 64: 620 / 192 / 69 us against 760 / 218 / 58; 3000 x 3000 (576 tiles):
   // 423 / 150 / 59 against 427 / 130 / 37.
+  // (A launch of 2^24 workgroups of 256 is past the grid's limit of 2^32 threads;
+  // 64 x 64 tiles reach it at 275 GB of outputs.)
   const int64_t t128 = fc_tiles(a, 128);
-  if (t128 >= 640 && a.d >= 384)
+  const bool wide = (t128 >= 640 && a.d >= 384) || t64 >= 1 << 24;
+  if (wide && a.d >= 64)
     hipLaunchKernelGGL((fc_split_kernel<2, 1, 6>), dim3((unsigned)t128), dim3(256), 0, stream, b);
+  else if (wide)
+    hipLaunchKernelGGL((fc_split_kernel<2, 1, 9>), dim3((unsigned)t128), dim3(256), 0, stream, b);
   else if (a.d >= 64)
     hipLaunchKernelGGL((fc_split_kernel<1, 1, 6>), dim3((unsigned)t64), dim3(256), 0, stream, b);
   else
