@@ -913,6 +913,8 @@ struct PcgPlan {
 
 // what: 0 = pivoted Cholesky only, 1 = full solver, 2 = product only.  small:
 // pivot steps of 256 rows a workgroup (the least a pivoted Cholesky accepts).
+// The full solver's pivot steps end before its vectors are first written, and
+// keep their maxima there.
 PcgPlan pcg_plan(int64_t n, int r, int what, bool small = false) {
   PcgPlan p{};
   Bump b;
@@ -921,8 +923,10 @@ PcgPlan pcg_plan(int64_t n, int r, int what, bool small = false) {
   const size_t G = kPcgGroup;
   if (what != 2) {
     p.d = b.take(sizeof(double) * n);
-    p.pv = b.take(sizeof(double) * 2 * nb);
-    p.pi = b.take(sizeof(int) * 2 * nb);
+    if (what == 0) {
+      p.pv = b.take(sizeof(double) * 2 * nb);
+      p.pi = b.take(sizeof(int) * 2 * nb);
+    }
     p.dpiv = b.take(sizeof(double) * std::max(r, 1));
   }
   if (what == 1) {
@@ -940,6 +944,8 @@ PcgPlan pcg_plan(int64_t n, int r, int what, bool small = false) {
     p.Z = b.take(sizeof(double) * n * G);
     p.P = b.take(sizeof(double) * n * G);
     p.Q = b.take(sizeof(double) * n * G);
+    p.pv = p.R;  // (2 nb <= n G entries each)
+    p.pi = p.X;
     p.part2 = b.take(sizeof(double) * nbz * G);
     p.st = b.take(sizeof(double) * 7 * G);
   }
