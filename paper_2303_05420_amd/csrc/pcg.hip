@@ -482,27 +482,48 @@ __global__ __launch_bounds__(PC_TPB) void kmv_reduce_kernel(const double* __rest
   pc_block_sums<C>(prod, red, pq_part + (int64_t)blockIdx.x * C);
 }
 
-// Row splits of the product: about 512 workgroups (8 waves per CU, each with
-// eight rows in flight), at least 64 rows each.  At n = 8192 that is 16 splits:
-// 57 us and 5 for their sum; with 1024 columns a workgroup there were 64, whose
-// partial sums (42 MB) took 58 us on the way out with K and 23 on the way in.
-// From 12288 rows on (K well past the last-level cache) about 1024, so that a
-// wave that waits for its rows of K, all a power of two apart at the usual
-// sizes, leaves another to run: 10 targets at n = 32768 take 775 us with 512
-// workgroups, 668 with 1024 (16384: 213 and 192; 24576: 436 and 459).
-int kmv_splits(int64_t n) {
+// Row splits of the product of C columns, at least 64 rows each.  All its
+// workgroups take the same time, so what counts is that they fill every CU with
+// the same number of them that it holds at once: `per`, and rather one too few
+// than one over.  Workgroups per CU and us, 10 columns: n = 12288 1.88 118, 2.06
+// 123, 3.0 107, 3.94 115; n = 20000 1.85 299, 2.78 261, 3.7 267, 4.01 326; n = 24576
+// 1.88 446, 3.0 376, 3.75 395, 4.12 457; 16 columns (two fit, by registers), n =
+// 24576: 1.88 540, 2.25 699, 3.0 591, 3.75 536; one column, n = 20000: 1.85 230, 2.16
+// 273, 2.78 234.  Up to 7 columns two are as good as three and write less partial
+// sums, and up to 8192 rows for all (n = 5000, 10 columns: 34 and 40; 8192: 58 and
+// 60).  Where `per` of them leave more than a tenth empty (n = 36000, 141 column
+// blocks: 1.65 of two) a larger number that the columns allow: 16 columns there
+// 1257 -> 1125, 4 columns 836 -> 755.
+static int kmv_splits(int64_t n, int C) {
+  constexpr int64_t cus = 256;
   const int64_t ncb = (n + KMV_COLS - 1) / KMV_COLS;
-  int64_t S = ((n >= 12288 ? 1024 : 512) + ncb - 1) / ncb;
-  const int64_t maxS = (n + 63) / 64;
-  if (S > maxS) S = maxS;
-  if (S > 64) S = 64;
-  return (int)(S < 1 ? 1 : S);
+  const int per = C >= 8 && C <= 13 && n > 8192 ? 3 : 2;
+  const int last = C >= 11 && C <= 13 ? 6 : 4, step = C >= 14 ? 2 : (C >= 11 ? 3 : 1);  // (of 11 to 13 three fit)
+  int64_t S = 0, q = 1;  // q workgroups a CU, of which S ncb / (q cus) are there
+  for (int p = per; p <= last; p += step) {
+    const int64_t s = p * cus / ncb;
+    if (S == 0 || 10 * s * q > 11 * S * p) {
+      S = s;
+      q = p;
+    }
+  }
+  const int64_t most = (n + 63) / 64 < 64 ? (n + 63) / 64 : 64;
+  return (int)(S < 1 ? 1 : (S > most ? most : S));
+}
+
+int kmv_splits(int64_t n) {
+  int S = 1;
+  for (int C = 1; C <= 16; ++C) {
+    const int s = kmv_splits(n, C);
+    S = s > S ? s : S;
+  }
+  return S;
 }
 
 template <int C>
 int launch_kmv_c(const float* K, int64_t n, int64_t ldk, const double* P, double lam, double* part, double* Q,
                  double* pq_part, const int* gate, hipStream_t s, ProfHook* hook) {
-  const int S = kmv_splits(n);
+  const int S = kmv_splits(n, C);
   const int64_t rows = (n + S - 1) / S;
   const bool vec = (ldk % 4 == 0) && ((reinterpret_cast<uintptr_t>(K) & 15) == 0);
   const dim3 grid((unsigned)((n + KMV_COLS - 1) / KMV_COLS), (unsigned)S);
