@@ -21,26 +21,52 @@ namespace nk {
 // COMP's sums; reading the operands from a cached 256 rows instead changes
 // nothing.
 // COMP: for sums whose result is later subtracted from a nearly equal
-// quantity.  Two chunks start from zero and their sum is added to the running
-// one with TwoSum, the rounding errors carried and added at the end: what is
-// left is the rounding inside 32 terms of a sum of K, and one rounding of the
-// result.  (A chain of compensated single products on the vector unit, 4
-// outputs per thread: 3.8 ms for the 1000 x 1000 x 12000 product of a
-// Nystrom solve, now 0.57.)
+// quantity, rounded once.  Every row x of op(A) and column y of op(B) is split
+// into the `bits` leading bits, counted from the largest magnitude in it (top_a,
+// top_b), and the rest, x = xh + xl.  A wave's sums of xh yh are then exact in
+// float64 (2 bits + log2(terms) <= 53, dn_bits); those of xh yl + xl y are
+// 2^-bits of them and carry the rounding errors, about 2^-(52 + bits) of the
+// terms' magnitudes in all.  The waves' exact sums meet by TwoSum, the rest is
+// added at the end.  Three products for one: the 1000 x 1000 x 12000 product of a
+// Nystrom solve takes 738 us.  (Every product's and every addition's error carried on
+// the vector unit: 3.8 ms; TwoSum once per 32 plainly summed terms, which loses
+// what is below 2^-53 of a larger neighbour: 564.)
 // sym: op(B) = op(A)^T; the tiles on and below the diagonal are formed and
-// mirrored.
+// mirrored (a launch of all tiles, half of which return at once, leaves the XCDs
+// unevenly loaded: 1222 us for the product above with 32 x 32 tiles, 946 so).
+
+// High word of a number's magnitude: its order, and the exponent above bit 20.
+__device__ __forceinline__ unsigned dn_word(double x) {
+  return (unsigned)(__builtin_bit_cast(unsigned long long, x) >> 32) & 0x7fffffffu;
+}
+
+// Constant whose addition and subtraction leave the leading `bits` bits of
+// numbers up to the one that `top` is the word of (NaN where that is not finite).
+__device__ __forceinline__ double dn_splitter(unsigned top, int bits) {
+  const unsigned e = (top >> 20) + 53 - (unsigned)bits;
+  const unsigned w = (top >> 20) == 0x7ff || e > 0x7fe ? 0x7ff80000u : (e << 20 | 0x80000u);
+  return __builtin_bit_cast(double, (unsigned long long)w << 32);
+}
+
 template <typename TA, typename TB, typename TO, bool A_T, bool B_T, bool COMP, int MB, int W>
-__global__ __launch_bounds__(64 * W, MB == 2 ? 3 : 1) void dn_gemm_kernel(const TA* __restrict__ A, int64_t lda,
+__global__ __launch_bounds__(64 * W, MB == 2 ? (COMP ? 2 : 3) : 1) void dn_gemm_kernel(const TA* __restrict__ A, int64_t lda,
                                                          const TB* __restrict__ B, int64_t ldb, TO* __restrict__ Cm,
                                                          int64_t ldc, int64_t M, int64_t N, int64_t K, double alpha,
                                                          double beta, double shift, int sym, int* __restrict__ info,
-                                                         unsigned ntc) {
+                                                         unsigned ntc, const unsigned* __restrict__ top_a,
+                                                         const unsigned* __restrict__ top_b, int bits) {
   constexpr int T = 16 * MB, E = T * T;
   extern __shared__ double red[];  // (COMP ? 2 : 1) * W / 2 * E
-  const unsigned tr = blockIdx.x / ntc, tc = blockIdx.x - tr * ntc;  // tile row and column
+  unsigned tr = blockIdx.x / ntc, tc = blockIdx.x - tr * ntc;  // tile row and column
+  if (sym) {  // (only the tiles on and below the diagonal are launched)
+    tr = (unsigned)((sqrtf(8.0f * (float)blockIdx.x + 1.0f) - 1.0f) * 0.5f);
+    while (tr * (tr + 1) / 2 > blockIdx.x) --tr;
+    while ((tr + 1) * (tr + 2) / 2 <= blockIdx.x) ++tr;
+    tc = blockIdx.x - tr * (tr + 1) / 2;
+  }
   if (info && blockIdx.x == 0 && threadIdx.x == 0) info[0] = 0;
-  if (sym && tc > tr) return;
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, i = lane & 15, g = lane >> 4;
+  const int tid = threadIdx.x, lane = tid & 63, i = lane & 15, g = lane >> 4;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int64_t r0 = (int64_t)tr * T, c0 = (int64_t)tc * T;
   int64_t ra[MB], cb[MB];  // this lane's rows of op(A) and columns of op(B) (past the end: the last one, not stored)
 #pragma unroll
@@ -52,77 +78,53 @@ __global__ __launch_bounds__(64 * W, MB == 2 ? 3 : 1) void dn_gemm_kernel(const 
     TA a[MB][4];
     TB b[MB][4];
   };
-  auto fetch = [&](int64_t q, Frag& f) {  // chunk q, a whole one
+  // Where this lane's elements of a chunk are, kept from chunk to chunk (64-bit
+  // index products at every load would cost more than the loads).
+  struct Place {
+    const TA* a[MB][A_T ? 4 : 1];
+    const TB* b[MB][B_T ? 1 : 4];
+  };
+  auto place = [&](int64_t q, Place& p) {
     const int64_t k = 16 * q + 4 * g;
+#pragma unroll
+    for (int x = 0; x < MB; ++x) {
+#pragma unroll
+      for (int t = 0; t < (A_T ? 4 : 1); ++t) p.a[x][t] = A_T ? A + (k + t) * lda + ra[x] : A + ra[x] * lda + k;
+#pragma unroll
+      for (int t = 0; t < (B_T ? 1 : 4); ++t) p.b[x][t] = B_T ? B + cb[x] * ldb + k : B + (k + t) * ldb + cb[x];
+    }
+  };
+  const int64_t step_a = 16 * W * (A_T ? lda : 1), step_b = 16 * W * (B_T ? 1 : ldb);
+  auto advance = [&](Place& p, bool on) {
+    const int64_t da = on ? step_a : 0, db = on ? step_b : 0;
+#pragma unroll
+    for (int x = 0; x < MB; ++x) {
+#pragma unroll
+      for (int t = 0; t < (A_T ? 4 : 1); ++t) p.a[x][t] += da;
+#pragma unroll
+      for (int t = 0; t < (B_T ? 1 : 4); ++t) p.b[x][t] += db;
+    }
+  };
+  auto fetch = [&](const Place& p, Frag& f) {  // a whole chunk
 #pragma unroll
     for (int x = 0; x < MB; ++x) {
       if constexpr (A_T) {
 #pragma unroll
-        for (int t = 0; t < 4; ++t) f.a[x][t] = A[(k + t) * lda + ra[x]];
+        for (int t = 0; t < 4; ++t) f.a[x][t] = *p.a[x][t];
       } else {
-        load4(A + ra[x] * lda + k, f.a[x]);
+        load4(p.a[x][0], f.a[x]);
       }
       if constexpr (B_T) {
-        load4(B + cb[x] * ldb + k, f.b[x]);
+        load4(p.b[x][0], f.b[x]);
       } else {
 #pragma unroll
-        for (int t = 0; t < 4; ++t) f.b[x][t] = B[(k + t) * ldb + cb[x]];
+        for (int t = 0; t < 4; ++t) f.b[x][t] = *p.b[x][t];
       }
     }
   };
-  d4 hi[MB][MB], lo[MB][MB];
-#pragma unroll
-  for (int x = 0; x < MB; ++x)
-#pragma unroll
-    for (int y = 0; y < MB; ++y) hi[x][y] = lo[x][y] = d4{0.0, 0.0, 0.0, 0.0};
-  auto multiply = [&](const Frag& f, d4 (&p)[MB][MB]) {
-#pragma unroll
-    for (int t = 0; t < 4; ++t)
-#pragma unroll
-      for (int x = 0; x < MB; ++x)
-#pragma unroll
-        for (int y = 0; y < MB; ++y) p[x][y] = mfma64((double)f.a[x][t], (double)f.b[y][t], p[x][y]);
-  };
-  d4 p[MB][MB];  // COMP: the running chunk pair
-  auto start = [&]() {
-#pragma unroll
-    for (int x = 0; x < MB; ++x)
-#pragma unroll
-      for (int y = 0; y < MB; ++y) p[x][y] = d4{0.0, 0.0, 0.0, 0.0};
-  };
-  auto add = [&]() {
-#pragma unroll
-    for (int x = 0; x < MB; ++x)
-#pragma unroll
-      for (int y = 0; y < MB; ++y) {
-        const d4 s = hi[x][y] + p[x][y];
-        const d4 bb = s - hi[x][y];
-        lo[x][y] += (hi[x][y] - (s - bb)) + (p[x][y] - bb);
-        hi[x][y] = s;
-      }
-  };
-  // whole chunks w, w + W, ...: two register sets, the next chunk's loads in
-  // flight while one multiplies (past the last: that one again, not used)
+  // the last chunk, of fewer than 16 (0 past the end)
   const int64_t whole = K / 16;
-  if (w < whole) {
-    Frag even, odd;
-    fetch(w, even);
-    for (int64_t q = w;;) {
-      const bool more = q + W < whole;
-      fetch(more ? q + W : q, odd);
-      if (COMP) start();
-      multiply(even, COMP ? p : hi);
-      if (more) {
-        q += 2 * W;
-        fetch(q < whole ? q : q - W, even);
-        multiply(odd, COMP ? p : hi);
-      }
-      if (COMP) add();
-      if (!more || q >= whole) break;
-    }
-  }
-  if (K % 16 != 0 && whole % W == w) {
-    Frag f;
+  auto fetch_rest = [&](Frag& f) {
     const int64_t k = 16 * whole + 4 * g;
 #pragma unroll
     for (int x = 0; x < MB; ++x)
@@ -132,10 +134,108 @@ __global__ __launch_bounds__(64 * W, MB == 2 ? 3 : 1) void dn_gemm_kernel(const 
         f.a[x][t] = in ? (A_T ? A[(k + t) * lda + ra[x]] : A[ra[x] * lda + k + t]) : (TA)0;
         f.b[x][t] = in ? (B_T ? B[cb[x] * ldb + k + t] : B[(k + t) * ldb + cb[x]]) : (TB)0;
       }
-    if (COMP) start();
-    multiply(f, COMP ? p : hi);
-    if (COMP) add();
+  };
+  const bool rest = K % 16 != 0 && whole % W == w;
+  // whole chunks w, w + W, ...: two register sets, the next chunk's loads in
+  // flight while one is used (past the last: that one again, not used)
+  auto walk = [&](auto&& use) {
+    if (w < whole) {
+      Frag even, odd;
+      Place p;
+      place(w, p);
+      fetch(p, even);
+      for (int64_t q = w;;) {
+        const bool more = q + W < whole;
+        advance(p, more);
+        fetch(p, odd);
+        use(even);
+        if (more) {
+          q += 2 * W;
+          advance(p, q < whole);
+          fetch(p, even);
+          use(odd);
+        }
+        if (!more || q >= whole) break;
+      }
+    }
+    if (rest) {
+      Frag f;
+      fetch_rest(f);
+      use(f);
+    }
+  };
+  double sa[MB], sb[MB];  // COMP: this lane's splitters
+  if constexpr (COMP) {
+    __shared__ unsigned top[2][T];
+    if (tid < 2 * T) top[tid / T][tid % T] = 0;
+    __syncthreads();
+    unsigned ta[MB], tb[MB];
+#pragma unroll
+    for (int x = 0; x < MB; ++x) ta[x] = tb[x] = 0;
+    if (!top_a || !top_b)
+      walk([&](const Frag& f) {
+#pragma unroll
+        for (int x = 0; x < MB; ++x)
+#pragma unroll
+          for (int t = 0; t < 4; ++t) {
+            const unsigned u = dn_word((double)f.a[x][t]), v = dn_word((double)f.b[x][t]);
+            ta[x] = u > ta[x] ? u : ta[x];
+            tb[x] = v > tb[x] ? v : tb[x];
+          }
+      });
+#pragma unroll
+    for (int x = 0; x < MB; ++x) {
+      atomicMax(&top[0][16 * x + i], ta[x]);
+      atomicMax(&top[1][16 * x + i], tb[x]);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int x = 0; x < MB; ++x) {
+      sa[x] = dn_splitter(top_a ? top_a[ra[x]] : top[0][16 * x + i], bits);
+      sb[x] = dn_splitter(top_b ? top_b[cb[x]] : top[1][16 * x + i], bits);
+    }
   }
+  d4 hi[MB][MB], lo[MB][MB];
+#pragma unroll
+  for (int x = 0; x < MB; ++x)
+#pragma unroll
+    for (int y = 0; y < MB; ++y) hi[x][y] = lo[x][y] = d4{0.0, 0.0, 0.0, 0.0};
+  walk([&](const Frag& f) {
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      double a[MB], b[MB];
+#pragma unroll
+      for (int x = 0; x < MB; ++x) {
+        a[x] = (double)f.a[x][t];
+        b[x] = (double)f.b[x][t];
+      }
+      if constexpr (COMP) {
+        double ah[MB], bh[MB];
+#pragma unroll
+        for (int x = 0; x < MB; ++x) {
+          ah[x] = (a[x] + sa[x]) - sa[x];
+          bh[x] = (b[x] + sb[x]) - sb[x];
+        }
+#pragma unroll
+        for (int x = 0; x < MB; ++x)
+#pragma unroll
+          for (int y = 0; y < MB; ++y) hi[x][y] = mfma64(ah[x], bh[y], hi[x][y]);
+#pragma unroll
+        for (int x = 0; x < MB; ++x)
+#pragma unroll
+          for (int y = 0; y < MB; ++y) lo[x][y] = mfma64(ah[x], b[y] - bh[y], lo[x][y]);
+#pragma unroll
+        for (int x = 0; x < MB; ++x)
+#pragma unroll
+          for (int y = 0; y < MB; ++y) lo[x][y] = mfma64(a[x] - ah[x], b[y], lo[x][y]);
+      } else {
+#pragma unroll
+        for (int x = 0; x < MB; ++x)
+#pragma unroll
+          for (int y = 0; y < MB; ++y) hi[x][y] = mfma64(a[x], b[y], hi[x][y]);
+      }
+    }
+  });
   // the upper half of the waves into the lower one, until one is left
 #pragma unroll 1
   for (int h = W / 2; h >= 1; h >>= 1) {
@@ -196,17 +296,27 @@ __global__ __launch_bounds__(64 * W, MB == 2 ? 3 : 1) void dn_gemm_kernel(const 
       }
 }
 
+// Leading bits b for exact sums of `terms` products of b bits each: 2 b +
+// log2(terms) <= 53 (20 up to 8192 terms a wave).
+static int dn_bits(int64_t terms) {
+  int b = 20;
+  while (b > 1 && (terms >> (53 - 2 * b)) > 0) --b;
+  return b;
+}
+
 template <typename TA, typename TB, typename TO, bool A_T, bool B_T, bool COMP, int MB, int W>
 static int dn_gemm_launch(const TA* A, int64_t lda, const TB* B, int64_t ldb, TO* C, int64_t ldc, int64_t M, int64_t N,
-                          int64_t K, double alpha, double beta, hipStream_t s, double shift, bool sym, int* info) {
+                          int64_t K, double alpha, double beta, hipStream_t s, double shift, bool sym, int* info,
+                          const unsigned* top_a, const unsigned* top_b) {
   static std::atomic<size_t> seen[kMaxDevices];
   constexpr int T = 16 * MB;
   const size_t lds = (size_t)(COMP ? 2 : 1) * W / 2 * T * T * sizeof(double);
   const auto kernel = dn_gemm_kernel<TA, TB, TO, A_T, B_T, COMP, MB, W>;
   if (allow_dyn_lds((const void*)kernel, lds, seen)) return -3;
   const int64_t mt = (M + T - 1) / T, nt = (N + T - 1) / T;
-  hipLaunchKernelGGL(kernel, dim3((unsigned)(mt * nt)), dim3(64 * W), lds, s, A, lda, B, ldb, C, ldc, M, N, K, alpha,
-                     beta, shift, sym ? 1 : 0, info, (unsigned)nt);
+  hipLaunchKernelGGL(kernel, dim3((unsigned)(sym ? mt * (mt + 1) / 2 : mt * nt)), dim3(64 * W), lds, s, A, lda, B, ldb,
+                     C, ldc, M, N, K, alpha, beta, shift, sym ? 1 : 0, info, (unsigned)nt, top_a, top_b,
+                     dn_bits((K / 16 + W) / W * 16));
   return hipGetLastError() == hipSuccess ? 0 : -3;
 }
 
@@ -215,23 +325,62 @@ static int dn_gemm_launch(const TA* A, int64_t lda, const TB* B, int64_t ldb, TO
 template <typename TA, typename TB, typename TO, bool A_T, bool B_T, bool COMP>
 static int dn_gemm_t(const TA* A, int64_t lda, const TB* B, int64_t ldb, TO* C, int64_t ldc, int64_t M, int64_t N,
                      int64_t K, double alpha, double beta, hipStream_t s, double shift = 0.0, bool sym = false,
-                     int* info = nullptr) {
+                     int* info = nullptr, const unsigned* top_a = nullptr, const unsigned* top_b = nullptr) {
   if (M <= 0 || N <= 0) return 0;
-  const int64_t m = (M + 31) / 32, n = (N + 31) / 32;
-  if (N > 16 && (sym ? m * (m + 1) / 2 : m * n) >= 256)
-    return dn_gemm_launch<TA, TB, TO, A_T, B_T, COMP, 2, 4>(A, lda, B, ldb, C, ldc, M, N, K, alpha, beta, s, shift, sym,
-                                                            info);
-  return K > 256 ? dn_gemm_launch<TA, TB, TO, A_T, B_T, COMP, 1, 16>(A, lda, B, ldb, C, ldc, M, N, K, alpha, beta, s,
-                                                                     shift, sym, info)
-                 : dn_gemm_launch<TA, TB, TO, A_T, B_T, COMP, 1, 4>(A, lda, B, ldb, C, ldc, M, N, K, alpha, beta, s,
-                                                                    shift, sym, info);
+  const int64_t m = (M + 31) / 32, n = (N + 31) / 32, h = (M + 15) / 16;
+  const auto go = [&](auto launch) {
+    return launch(A, lda, B, ldb, C, ldc, M, N, K, alpha, beta, s, shift, sym, info, top_a, top_b);
+  };
+  if constexpr (COMP && (A_T || B_T)) {  // (the forms that have symmetric results)
+    // Three products for one make the last round dear: 32 x 32 tiles of a
+    // symmetric result only from four a CU on.  1000 x 1000 x 12000, 528 of them
+    // 946 us, 2016 of 16 x 16 with four waves 766, with eight 738.
+    if (sym && h * (h + 1) / 2 >= 512 && m * (m + 1) / 2 < 1024)
+      return go(dn_gemm_launch<TA, TB, TO, A_T, B_T, COMP, 1, 8>);
+  }
+  if (N > 16 && (sym ? m * (m + 1) / 2 : m * n) >= 256) return go(dn_gemm_launch<TA, TB, TO, A_T, B_T, COMP, 2, 4>);
+  return K > 256 ? go(dn_gemm_launch<TA, TB, TO, A_T, B_T, COMP, 1, 16>)
+                 : go(dn_gemm_launch<TA, TB, TO, A_T, B_T, COMP, 1, 4>);
+}
+
+// top[c] = largest word of column c of A (n x r, lda), zero before.
+__global__ __launch_bounds__(256) void dn_column_top_kernel(const float* __restrict__ A, int64_t lda, int64_t n,
+                                                            int64_t r, int64_t rows, unsigned* __restrict__ top) {
+  __shared__ unsigned part[4][64];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int64_t c = (int64_t)blockIdx.x * 64 + lane, i0 = (int64_t)blockIdx.y * rows;
+  const int64_t i1 = i0 + rows < n ? i0 + rows : n;
+  const float* p = A + (c < r ? c : r - 1);
+  unsigned m = 0;
+#pragma unroll 8
+  for (int64_t i = i0 + w; i < i1; i += 4) {
+    const unsigned u = __builtin_bit_cast(unsigned, p[i * lda]) & 0x7fffffffu;
+    m = u > m ? u : m;
+  }
+  part[w][lane] = m;
+  __syncthreads();
+  if (w != 0 || c >= r) return;
+  for (int k = 1; k < 4; ++k) m = part[k][lane] > m ? part[k][lane] : m;
+  atomicMax(&top[c], dn_word((double)__builtin_bit_cast(float, m)));
+}
+
+int dn_column_top(const float* A, int64_t lda, int64_t n, int64_t r, unsigned* top, hipStream_t s) {
+  if (launch_zero_f64(reinterpret_cast<double*>(top), (r + 1) / 2, s)) return -3;
+  const int64_t cb = (r + 63) / 64;
+  int64_t parts = (1024 + cb - 1) / cb;
+  if (parts > (n + 63) / 64) parts = (n + 63) / 64;
+  const int64_t rows = (n + parts - 1) / parts;
+  hipLaunchKernelGGL(dn_column_top_kernel, dim3((unsigned)cb, (unsigned)parts), dim3(256), 0, s, A, lda, n, r, rows,
+                     top);
+  return hipGetLastError() == hipSuccess ? 0 : -3;
 }
 
 int dn_gemm_ff(const float* A, int64_t lda, bool a_t, const float* B, int64_t ldb, double* C, int64_t ldc, int64_t M,
-               int64_t N, int64_t K, double alpha, double beta, bool comp, hipStream_t s) {
+               int64_t N, int64_t K, double alpha, double beta, bool comp, hipStream_t s, const unsigned* top_a, const unsigned* top_b) {
   if (!a_t || !comp) return -1;  // (only the compensated A^T B is used)
   const bool sym = A == B && lda == ldb && M == N && beta == 0.0;
-  return dn_gemm_t<float, float, double, true, false, true>(A, lda, B, ldb, C, ldc, M, N, K, alpha, beta, s, 0.0, sym);
+  return dn_gemm_t<float, float, double, true, false, true>(A, lda, B, ldb, C, ldc, M, N, K, alpha, beta, s, 0.0, sym,
+                                                            nullptr, top_a, top_b);
 }
 
 int dn_gemm_fd(const float* A, int64_t lda, bool a_t, const double* B, int64_t ldb, double* C, int64_t ldc,

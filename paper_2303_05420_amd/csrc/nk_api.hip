@@ -862,9 +862,12 @@ int approx_low_rank_v(const float* K_nr, int64_t n, int64_t r, int64_t ld_nr, co
   double* D = at<double>(ws, ap.D);
   double* bb = at<double>(ws, ap.b);
   int* info = at<int>(ws, ap.info);
-  if (nk::dn_gemm_ff(K_nr, ld_nr, true, K_nr, ld_nr, A, r, r, r, n, 1.0, 0.0, true, s) ||
+  unsigned* top = at<unsigned>(ws, ap.v);    // (v is written last)
+  unsigned* top_y = at<unsigned>(ws, ap.Z);  // (the committee machine's)
+  if (nk::dn_column_top(K_nr, ld_nr, n, r, top, s) || nk::dn_column_top(Y, c, n, c, top_y, s) ||
+      nk::dn_gemm_ff(K_nr, ld_nr, true, K_nr, ld_nr, A, r, r, r, n, 1.0, 0.0, true, s, top, top) ||
       nk::dn_load_shift(K_rr, ld_rr, r, jitter, D, info, s) || nk::dn_axpby(A, D, r * r, 1.0, lam, s) ||
-      nk::dn_gemm_ff(K_nr, ld_nr, true, Y, c, bb, c, r, c, n, 1.0, 0.0, true, s) ||
+      nk::dn_gemm_ff(K_nr, ld_nr, true, Y, c, bb, c, r, c, n, 1.0, 0.0, true, s, top, top_y) ||
       nk::launch_cholesky(A, r, info, bb, c, s) || nk::launch_chol_backward(A, r, bb, c, at<double>(ws, ap.v), s))
     return -3;
   return 0;

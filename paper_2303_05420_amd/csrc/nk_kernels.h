@@ -260,10 +260,15 @@ int launch_kmv(const float* K, int64_t n, int64_t ldk, const double* P, int C, d
 int launch_diag_mean(const float* K, int64_t n, int64_t ldk, double* out, hipStream_t s);
 
 // Dense float64 helpers of the solvers (dense.hip).  GEMM: C (M x N, ldc) =
-// beta C + alpha op(A) B, op(A) = A (M x K) or A^T (A is K x M); comp carries
-// the sums' rounding errors (compensated).  -1: a form that is not compiled.
+// beta C + alpha op(A) B, op(A) = A (M x K) or A^T (A is K x M); comp rounds
+// the sums once (compensated).  -1: a form that is not compiled.
+// top_a, top_b (NULL: found on the way): dn_column_top of A and B.
 int dn_gemm_ff(const float* A, int64_t lda, bool a_t, const float* B, int64_t ldb, double* C, int64_t ldc, int64_t M,
-               int64_t N, int64_t K, double alpha, double beta, bool comp, hipStream_t s);
+               int64_t N, int64_t K, double alpha, double beta, bool comp, hipStream_t s, const unsigned* top_a = nullptr,
+               const unsigned* top_b = nullptr);
+// Largest magnitude in each column of A (n x r) as the compensated products
+// take it (r + 1 words of room).
+int dn_column_top(const float* A, int64_t lda, int64_t n, int64_t r, unsigned* top, hipStream_t s);
 int dn_gemm_fd(const float* A, int64_t lda, bool a_t, const double* B, int64_t ldb, double* C, int64_t ldc,
                int64_t M, int64_t N, int64_t K, double alpha, double beta, bool comp, hipStream_t s);
 int dn_gemm_dd(const double* A, int64_t lda, const double* B, int64_t ldb, double* C, int64_t ldc, int64_t M,
