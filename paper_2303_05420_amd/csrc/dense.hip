@@ -415,7 +415,8 @@ __global__ __launch_bounds__(256) void dn_load_shift_kernel(const float* __restr
   if (info && e == 0) info[0] = 0;
   if (e >= n * n) return;
   const int64_t i = e / n, j = e - i * n;
-  D[e] = (double)S[i * lds + j] + (i == j ? shift : 0.0);
+  const double v = (double)S[i * lds + j];
+  D[e] = i == j ? chol_diagonal(v + shift) : v;
 }
 
 int dn_load_shift(const float* S, int64_t lds, int64_t n, double shift, double* D, int* info, hipStream_t s) {
@@ -429,7 +430,7 @@ __global__ __launch_bounds__(256) void dn_shift_kernel(double* __restrict__ D, i
                                                        int* __restrict__ info) {
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (info && i == 0) info[0] = 0;
-  if (i < n) D[i * n + i] += shift;
+  if (i < n) D[i * n + i] = chol_diagonal(D[i * n + i] + shift);
 }
 
 int dn_shift(double* D, int64_t n, double shift, int* info, hipStream_t s) {

@@ -38,7 +38,7 @@ __global__ __launch_bounds__(256) void krr_build_kernel(const float* __restrict_
   if (e >= n * n) return;
   const int64_t i = e / n, j = e - i * n;
   double v = (double)K[e];
-  if (i == j) v += ridge_rel >= 0.0 ? ridge_rel * mean[0] : lam_abs;
+  if (i == j) v = chol_diagonal(v + (ridge_rel >= 0.0 ? ridge_rel * mean[0] : lam_abs));
   A[e] = v;
 }
 

@@ -201,6 +201,12 @@ int launch_finish_sigma(const double* sums, double sw2, float* dsigma, hipStream
 // out (cols x rows) = in^T (rows x cols), both dense; rows <= 65535 * 32.
 int launch_transpose_f32(const float* in, int64_t rows, int64_t cols, float* out, hipStream_t s);
 int launch_zero_f64(double* p, int64_t n, hipStream_t s);
+// Diagonal entry of a matrix to be factored: an infinite one (a kernel value
+// past float32) counts as 1e300, so that its unknown comes out as 0 and it takes
+// no part in the others, as when dividing by its root; the factorisation works
+// with reciprocals, which would make it NaN.
+__device__ inline double chol_diagonal(double v) { return v > 1e300 ? 1e300 : v; }
+
 // Cholesky factor of A (n x n, lower triangle) in place; info[0] = 1 at a
 // pivot that is not positive.  Z (n x c, row-major; NULL: none) <- L^{-1} Z.
 int launch_cholesky(double* A, int64_t n, int* info, double* Z, int64_t c, hipStream_t s);
