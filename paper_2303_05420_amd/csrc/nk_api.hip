@@ -375,21 +375,6 @@ BatchPlan plan_batched(const NetDesc& net, int64_t rows, int64_t ntiles, int64_t
   return p;
 }
 
-// Compute units of the current device (0 if unknown), queried once per device.
-int cu_count() {
-  static std::atomic<int> counts[nk::kMaxDevices];
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0) return 0;
-  if (dev < nk::kMaxDevices) {
-    const int c = counts[dev].load(std::memory_order_relaxed);
-    if (c > 0) return c;
-  }
-  int n = 0;
-  if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0) return 0;
-  if (dev < nk::kMaxDevices) counts[dev].store(n, std::memory_order_relaxed);
-  return n;
-}
-
 // Stage passes of chunks [p_lo, p_hi) of a batched pass.
 int run_batched_stages(const NetDesc& net, const nk::TileDesc* ddesc, int ntiles, const float2* tab, float* const* bufs,
                        const BatchParams& bp, int64_t p_lo, int64_t p_hi, int only_stage, hipStream_t stream) {
@@ -419,7 +404,7 @@ int run_batched_stages(const NetDesc& net, const nk::TileDesc* ddesc, int ntiles
       if (bp.persist) {
         const int occ =
             nk::stage_occupancy(net.hw >> s, net.depth[s], s == 0, pool, net.sb2 != 0.f, net.C, bp.ppm);
-        const int cus = cu_count();
+        const int cus = nk::cu_count();
         if (occ <= 0 || cus <= 0) return hip_fail("occupancy query");
         const int64_t ppwg = nk::stage_pairs_per_wg(net.hw >> s, pool, bp.ppm);
         const int64_t units = (np + ppwg - 1) / ppwg;
@@ -1173,7 +1158,7 @@ int nk_myrtle_nngp(const float* x1, int64_t n1, const float* x2, int64_t n2, con
   // to a multiple of the CU count.
   chunk = std::min(chunk, net.hw > 32 ? kDefaultChunk64 : kDefaultChunk);
   if (net.hw > 32) {
-    const int cus = cu_count();
+    const int cus = nk::cu_count();
     if (cus > 0 && chunk > cus) chunk -= chunk % cus;
   }
   const MyrtlePlan p = plan_myrtle(net, n1, n2, sym, chunk);

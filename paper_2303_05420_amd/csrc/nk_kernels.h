@@ -27,6 +27,21 @@ inline int allow_dyn_lds(const void* fn, size_t lds, std::atomic<size_t>* seen) 
   return 0;
 }
 
+// Compute units of the current device (0 if unknown), queried once per device.
+inline int cu_count() {
+  static std::atomic<int> counts[kMaxDevices];
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0) return 0;
+  if (dev < kMaxDevices) {
+    const int c = counts[dev].load(std::memory_order_relaxed);
+    if (c > 0) return c;
+  }
+  int n = 0;
+  if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0) return 0;
+  if (dev < kMaxDevices) counts[dev].store(n, std::memory_order_relaxed);
+  return n;
+}
+
 struct PrepArgs {
   const float* x1;    // images NHWC; n1 of them, then those of x2
   const float* x2;

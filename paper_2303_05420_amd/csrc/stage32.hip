@@ -570,15 +570,22 @@ int s32_attr(size_t lds) {
   return allow_dyn_lds((const void*)stage32_kernel<SEED, BIAS, C4, SPLIT>, lds, seen);
 }
 
-// Workgroups a CU holds (by LDS, but for the smallest depths by waves).
+// Workgroups a CU holds (by LDS, but for the smallest depths by waves), queried
+// once per device and depth.
 template <bool SEED, bool BIAS, bool C4>
 int s32_occ(int D) {
+  static std::atomic<int> known[kMaxDevices][NK_MAX_DEPTH + 1];
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess) return -3;
+  std::atomic<int>* rec = dev >= 0 && dev < kMaxDevices ? &known[dev][D] : nullptr;
+  if (rec && rec->load(std::memory_order_relaxed) > 0) return rec->load(std::memory_order_relaxed);
   const size_t lds = s32_lds_bytes(D, SEED);
   if (s32_attr<SEED, BIAS, C4, false>(lds)) return -3;
   int nb = 0;
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, stage32_kernel<SEED, BIAS, C4, false>, kThreads, lds) !=
       hipSuccess)
     return -3;
+  if (rec) rec->store(nb, std::memory_order_relaxed);
   return nb;
 }
 
@@ -592,9 +599,8 @@ int s32_go(const StageArgs& a, int64_t grid, hipStream_t stream) {
 
 template <bool SEED, bool BIAS, bool C4>
 int s32_launch(const StageArgs& a, hipStream_t stream) {
-  int dev = 0, cus = 0;
-  if (a.np <= 1024 && hipGetDevice(&dev) == hipSuccess &&
-      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && cus > 0) {
+  const int cus = a.np <= 1024 ? cu_count() : 0;
+  if (cus > 0) {
     const int occ = s32_occ<SEED, BIAS, C4>(a.D);
     const int parts = occ > 0 ? sweep_parts(a.np, (int64_t)cus * occ, kN) : 1;
     if (parts > 1) {

@@ -311,10 +311,8 @@ static int launch_s64_t(const StageArgs& a, hipStream_t s) {
   if (allow_dyn_lds((const void*)fn, lds, seen)) return -3;
   StageArgs p = a;
   p.parts = 1;
-  int dev = 0, cus = 0;
-  if (a.np <= 1024 && hipGetDevice(&dev) == hipSuccess &&
-      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && cus > 0)
-    p.parts = sweep_parts(a.np, cus, 64);  // (LDS: one workgroup per CU)
+  const int cus = a.np <= 1024 ? cu_count() : 0;
+  if (cus > 0) p.parts = sweep_parts(a.np, cus, 64);  // (LDS: one workgroup per CU)
   hipLaunchKernelGGL(fn, dim3((unsigned)(a.np * p.parts)), dim3(S64_THREADS), lds, s, p);
   return hipGetLastError() == hipSuccess ? 0 : -3;
 }
