@@ -357,8 +357,10 @@ int nk_myrtle_batched_tuning(const nk_myrtle_cfg* cfg, nk_batched_candidate* out
  * is done; nk_myrtle_batched_tuning then reports no candidates and this
  * choice).  Read from *choice: chunk in [1, 32768] (cut to what the
  * workspace holds at each call), pair_tile in [1, 256], persistent 0 or 1,
- * wg_pairs_mult 1 or 2; the other fields are ignored.  Results do not depend
- * on the choice.  NK_EINVAL on other values or a NULL pointer; no GPU call. */
+ * wg_pairs_mult 1 or 2; the other fields are ignored.  A stage pass of few
+ * pairs over 32 x 32 images, whose sweeps several workgroups share, runs one
+ * workgroup per unit under either schedule.  Results do not depend on the
+ * choice.  NK_EINVAL on other values or a NULL pointer; no GPU call. */
 int nk_myrtle_batched_set_schedule(const nk_myrtle_cfg* cfg, const nk_batched_candidate* choice);
 
 /*
