@@ -170,7 +170,8 @@ __device__ __forceinline__ void cv_readout(const CvArgs& a, const float (&A)[N],
 // (horizontal sum 3 with the bias riding in it, vertical 1.5, map 10) where a
 // layer at a time took 18.5 with the copies of the tile around its branch on
 // the first layer.  CV8, 1000 x 1030 pairs: 4515 us a call with a layer
-// at a time, 4270-4325 so (both with the tables' 60 to 120 us).
+// at a time, 4270-4325 so on the same card (both with the tables' 60 to 120 us;
+// 4.3 to 4.7 ms from card to card).
 constexpr int CV_ROWS = 8, CV_PIECE = 8 * CV_ROWS * 32;  // float2 per piece
 
 struct Cv32 {

@@ -204,7 +204,7 @@ __device__ __forceinline__ void fc_split2(float x0, float x1, unsigned& h, unsig
 // a row take many values; where they take few they add up, to 6e-8 of the entry
 // at most, but there the roundings of the sum weigh more, and it rounds less
 // often than with fp32 instructions.  Largest error against float64 of 3.3e6
-// entries (normalised, no ReLU layers) at d = 64 and 3072, fp32 instructions first: 
+// entries (normalised, no ReLU layers) at d = 64 and 3072, fp32 instructions first:
 // normal features 2.2e-7, 2.4e-7 and 2.0e-7, 1.8e-7; rows of one value 1.0e-6,
 // 4.6e-5 and 7.3e-7, 2.8e-5; of two values 8.9e-7, 3.8e-5 and 4.4e-7, 1.4e-5.
 // Exchanged operands.  A product and its counterpart (h l' and l h', h m' and m
@@ -230,8 +230,8 @@ __device__ __forceinline__ void fc_split2(float x0, float x1, unsigned& h, unsig
 // workgroups per CU.
 // Bound: the matrix instructions, 6 x 2 n1 n2 d operations at the bf16 rate, by
 // the reads that feed them.  FC-3 Gram of 20000 x 3072 (symmetric): 7.3-7.5 ms,
-// about 1000 TFLOP/s of bf16 products (a large library product reaches 1081 on this
-// card); with fp32 instructions 12.3 ms, 0.65 of their peak.
+// about 1000 TFLOP/s of bf16 products (a large library product reaches 1081 to
+// 1309 from card to card); with fp32 instructions 12.3 ms, 0.65 of their peak.
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
 template <int WB, int KT, int NP>

@@ -19,9 +19,9 @@
 // What bounds it: one workgroup per CU (LDS), two waves per SIMD, so neither
 // LDS nor global latency hides by itself.  With the seed formed before the
 // layers (16 rows of pixels requested, waited for and used at a time) the
-// vector units were busy 63 % of the time; formed row by row inside the first
+// vector units were busy 67 % of the time; formed row by row inside the first
 // layer, eight rows after its request, with the outputs that are added to
-// requested together, 76 %.  Myrtle at 64x64x3, depth 2,2,2, 24 x 21 pairs, whole
+// requested together, 80 % (1024 pairs).  Myrtle at 64x64x3, depth 2,2,2, 24 x 21 pairs, whole
 // call: 14.8 -> 12.2 ms.
 //
 // Pooling.  The y part runs in registers along the ky sweep as in the
