@@ -275,7 +275,7 @@ int launch_pchol(const float* K, int64_t n, int64_t ldk, int rank, double pivot_
                  double* d, double* pv, int* pi, int64_t maxima, double* dpiv, hipStream_t s);
 int launch_pc_setup(double* LU, int64_t n, int r, double lam, double* Ur, double* M, int* info, hipStream_t s);
 int launch_pcg_group(const PcgArgs& a, int64_t c0, int C, hipStream_t s);
-int kmv_splits(int64_t n);  // most row splits of a product, over the numbers of columns
+int kmv_splits(int64_t n);  // row splits that a product's workspace holds for 16 columns
 int launch_kmv(const float* K, int64_t n, int64_t ldk, const double* P, int C, double lam, double* part, double* Q,
                double* pq_part, hipStream_t s, ProfHook* hook);
 int launch_diag_mean(const float* K, int64_t n, int64_t ldk, double* out, hipStream_t s);

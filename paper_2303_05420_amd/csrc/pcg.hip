@@ -482,6 +482,15 @@ __global__ __launch_bounds__(PC_TPB) void kmv_reduce_kernel(const double* __rest
   pc_block_sums<C>(prod, red, pq_part + (int64_t)blockIdx.x * C);
 }
 
+// Room for row splits of 16 columns in a workspace (callers keep workspaces, so it
+// stays what it has been).
+int kmv_splits(int64_t n) {
+  const int64_t ncb = (n + KMV_COLS - 1) / KMV_COLS;
+  const int64_t most = (n + 63) / 64 < 64 ? (n + 63) / 64 : 64;
+  const int64_t S = ((n >= 12288 ? 1024 : 512) + ncb - 1) / ncb;
+  return (int)(S > most ? most : S);
+}
+
 // Row splits of the product of C columns, at least 64 rows each.  All its
 // workgroups take the same time, so what counts is that they fill every CU with
 // the same number of them that it holds at once: `per`, and rather one too few
@@ -496,15 +505,20 @@ __global__ __launch_bounds__(PC_TPB) void kmv_reduce_kernel(const double* __rest
 // 1257 -> 1125, 4 columns 836 -> 755.
 static int kmv_splits(int64_t n, int C) {
   constexpr int64_t cus = 256;
-  const int64_t ncb = (n + KMV_COLS - 1) / KMV_COLS;
+  const int64_t ncb = (n + KMV_COLS - 1) / KMV_COLS, room = (int64_t)kmv_splits(n) * 16 / C;
   // (10 columns are the most of which four fit: where four divide without rest
   // they take 662 us against 683 at n = 32768, 179 against 180 at 16384)
   const bool four = C == 10 && 4 * cus % ncb == 0;
-  const int per = C >= 8 && C <= 13 && n > 8192 ? (four ? 4 : 3) : 2;
-  const int last = C >= 14 ? 8 : (C >= 11 ? 6 : 4), step = C >= 14 ? 2 : (C >= 11 ? 3 : 1);  // (of 11 to 13 three fit)
+  int per = C >= 8 && C <= 13 && n > 8192 ? (four ? 4 : 3) : 2;
+  if (per * cus / ncb > room) per = 2;  // (12 and 13 columns up to 12287 rows)
+  const int last = C >= 11 && C <= 13 ? 6 : 4, step = C >= 14 ? 2 : (C >= 11 ? 3 : 1);  // (of 11 to 13 three fit)
   int64_t S = 0, q = 1;  // q workgroups a CU, of which S ncb / (q cus) are there
   for (int p = per; p <= last; p += step) {
     const int64_t s = p * cus / ncb;
+    if (S > 0 && s > room) {  // (13 columns, 70000 rows: two splits fill 0.71, 4314 us; the four of the room 3878)
+      if (4 * S * ncb < 3 * q * cus) S = room;
+      break;
+    }
     if (S == 0 || 10 * s * q > 11 * S * p) {
       S = s;
       q = p;
@@ -512,15 +526,6 @@ static int kmv_splits(int64_t n, int C) {
   }
   const int64_t most = (n + 63) / 64 < 64 ? (n + 63) / 64 : 64;
   return (int)(S < 1 ? 1 : (S > most ? most : S));
-}
-
-int kmv_splits(int64_t n) {
-  int S = 1;
-  for (int C = 1; C <= 16; ++C) {
-    const int s = kmv_splits(n, C);
-    S = s > S ? s : S;
-  }
-  return S;
 }
 
 template <int C>
